@@ -173,6 +173,7 @@ int hinqs_sigma(hinqs_ctx *ctx, int k, const void *X, void *S, int precision, in
         const bool sorted = (flags & HINQS_SORTED_ORDER) != 0;
         hipStream_t s = c.stream;
         const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)S % 16 == 0);
+        if (sigma_small(c, k, X, S, precision, sorted, s)) return HINQS_OK;
         if (sorted && K == k && aligned) {
             sigma_sorted(c, K, X, K, S, K, precision, s);
             return HINQS_OK;

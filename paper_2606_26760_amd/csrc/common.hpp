@@ -244,10 +244,15 @@ constexpr int SIGMA_CTR_WORDS = 8 * 32;
 // lane, resident workgroups per CU.
 struct SigmaCfg {
     int team = 0, unr = 0, occ = 0;
-    int pipe = 0;     // 0: one step of gathers in flight per team; 1: cross-row four-stage pipeline
-    int run = 4;      // rows a team takes from its XCD's row counter at a time (pipe 0)
+    int pipe = 0;     // 0: one step of gathers in flight per team; 1: cross-row four-stage pipeline;
+                      // 2: small sets, one wave per row
+    int run = -1;     // rows a team takes from its XCD's row counter at a time, 0: fixed strides,
+                      // -1: by the size of the set (pipe 0)
     double ms = 0.0;  // measured time of one launch when chosen by the tuner
 };
+
+// Sets of at most this many rows take the one-wave-per-row product by default.
+constexpr int64_t SIGMA_SMALL_ROWS = 8192;
 
 // Row mask of the sigma kernel for batched instances (rows of instance b are
 // inst_row[b] .. inst_row[b+1]); ranges holds 9 row bounds, one range per XCD.
@@ -420,6 +425,11 @@ void radix_sort_u64(hipStream_t s, uint64_t *keys, int32_t *vals, int64_t n, int
 // zero); nullptr = the context's own.
 void sigma_sorted(Ctx &c, int k, const void *X, int ldx, void *S, int lds, int precision,
                   hipStream_t s, unsigned long long *ctr = nullptr);
+
+// S = H X in one launch for a small set: X, S in caller order or sorted, any k
+// in [1, 16], any alignment.  False (nothing done) when the set or its tuned
+// shape takes the general kernel.
+bool sigma_small(const Ctx &c, int k, const void *X, void *S, int precision, bool sorted, hipStream_t s);
 
 // No-allocation sigma (noalloc.hip).  noalloc_setup: once per device, with
 // that device current (hinqs_create calls it).  sigma_noalloc: the whole

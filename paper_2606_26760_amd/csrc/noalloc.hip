@@ -122,6 +122,7 @@ void sigma_noalloc(Ctx &c, int k, const void *X, void *S, int precision, bool so
                                              " (sorted-order, 16-byte aligned X and S with k in {1,2,4,8,16} "
                                              "need no staging)");
     hipStream_t s = c.stream;
+    if (sigma_small(c, k, X, S, precision, sorted, s)) return;
     hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(SIGMA_CTR_WORDS), 0, s, (unsigned long long *)base,
                        SIGMA_CTR_WORDS);
     HQ_LAUNCH_CHECK();

@@ -98,8 +98,8 @@ struct XcdRows {
 // MASK (batched instances): the XCD row ranges come from device memory and the
 // rows of finished instances are skipped; a team jumps over a finished
 // instance in one step, so the cost does not grow with its size.
-// Row counters (ctr, not for MASK): instead of a fixed stride, the team
-// leader takes the XCD's next run of `run` rows from a counter, so the teams of an XCD stay
+// Row counters (ctr, not for MASK; sets above SIGMA_STATIC_NNZ couplings, see
+// row_run): instead of a fixed stride, the team leader takes the XCD's next run of `run` rows from a counter, so the teams of an XCD stay
 // on neighbouring rows however unequal the rows are; with fixed strides the
 // teams drift apart and the X rows in flight no longer share the XCD's L2
 // (a trace-driven model of the gathers gives 53 % L2 hits for strides and
@@ -434,6 +434,106 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma_xr(XcdRows ranges, SigmaM
     }
 }
 
+// Small sets (at most SIGMA_SMALL_ROWS rows): one wave per row, in whatever
+// order the caller's vectors are (perm: sorted position -> caller index; null:
+// sorted), any k up to K and any alignment (VEC: k == K and 16-byte aligned
+// rows).  Such a product is bound by launches, not by its gathers: staging
+// caller-order vectors took two more kernels (400 rows, k = 1: 12.8 us per call
+// with them, 5 us for this kernel alone), and the lookup perm[col] stays in L1.
+template <typename T, int K, bool VEC>
+__global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma_small(int64_t ndet, const int64_t *__restrict__ rowptr,
+                                                             const int32_t *__restrict__ col,
+                                                             const T *__restrict__ val, const T *__restrict__ diag,
+                                                             const int32_t *__restrict__ perm,
+                                                             const T *__restrict__ X, int k, T *__restrict__ S) {
+    constexpr int VW = Vec16<T>::n;
+    constexpr int LPN = (K >= VW) ? K / VW : 1;
+    constexpr int EPL = K / LPN;
+    constexpr int NPT = 64 / LPN;  // couplings per wave and step
+    constexpr int UNR = 4;
+    const int lane = threadIdx.x & 63, q = lane % LPN, g = lane / LPN;
+    const int64_t row = uniform_if<true>((int64_t)blockIdx.x * (SIGMA_BLOCK / 64) + (threadIdx.x >> 6));
+    if (row >= ndet) return;
+    const int c0 = q * EPL;
+    auto load = [&](int64_t r, T (&x)[EPL]) {
+        if constexpr (VEC) {
+            load_vec<T, EPL>(X + r * K + c0, x);
+        } else {
+#pragma unroll
+            for (int c = 0; c < EPL; ++c) x[c] = c0 + c < k ? X[r * k + c0 + c] : T(0);
+        }
+    };
+    const int64_t beg = rowptr[row], end = rowptr[row + 1];
+    const int64_t orow = perm ? perm[row] : row;
+    T acc[EPL], own[EPL];
+#pragma unroll
+    for (int c = 0; c < EPL; ++c) acc[c] = T(0);
+    load(orow, own);
+    const T d = diag ? diag[row] : T(0);
+    for (int64_t e = beg + g; e < end; e += UNR * NPT) {
+        int64_t j[UNR];
+        T w[UNR], x[UNR][EPL];
+        // past the row's end: the row itself with value 0
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const bool ok = e + u * NPT < end;
+            const int64_t i = ok ? e + u * NPT : e;
+            j[u] = ok ? (int64_t)col[i] : row;
+            w[u] = ok ? val[i] : T(0);
+        }
+        if (perm) {
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) j[u] = perm[j[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) load(j[u], x[u]);
+#pragma unroll
+        for (int u = 0; u < UNR; ++u)
+#pragma unroll
+            for (int c = 0; c < EPL; ++c) acc[c] += w[u] * x[u][c];
+    }
+#pragma unroll
+    for (int off = LPN; off < 64; off <<= 1) {
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) acc[c] += __shfl_xor(acc[c], off, 64);
+    }
+    if (g != 0) return;
+    if (diag) {
+#pragma unroll
+        for (int c = 0; c < EPL; ++c) acc[c] += d * own[c];
+    }
+    if constexpr (VEC) {
+        store_vec<T, EPL>(S + orow * K + c0, acc);
+    } else {
+#pragma unroll
+        for (int c = 0; c < EPL; ++c)
+            if (c0 + c < k) S[orow * k + c0 + c] = acc[c];
+    }
+}
+
+template <typename T, int K>
+void launch_small(const Ctx &c, const T *val, const T *diag, const T *X, int k, T *S, bool sorted, hipStream_t s) {
+    const bool vec = k == K && (uintptr_t)X % 16 == 0 && (uintptr_t)S % 16 == 0;
+    const dim3 grid((unsigned)((c.ndet + SIGMA_BLOCK / 64 - 1) / (SIGMA_BLOCK / 64))), block(SIGMA_BLOCK);
+    const int32_t *perm = sorted ? (const int32_t *)nullptr : (const int32_t *)c.perm.p;
+    if (vec)
+        hipLaunchKernelGGL((k_sigma_small<T, K, true>), grid, block, 0, s, c.ndet, c.rowptr.p, c.col.p, val, diag,
+                           perm, X, k, S);
+    else
+        hipLaunchKernelGGL((k_sigma_small<T, K, false>), grid, block, 0, s, c.ndet, c.rowptr.p, c.col.p, val, diag,
+                           perm, X, k, S);
+    HQ_LAUNCH_CHECK();
+}
+
+template <typename T>
+void dispatch_small(const Ctx &c, const T *val, const T *diag, const T *X, int k, T *S, bool sorted, hipStream_t s) {
+    if (k <= 1) launch_small<T, 1>(c, val, diag, X, k, S, sorted, s);
+    else if (k <= 2) launch_small<T, 2>(c, val, diag, X, k, S, sorted, s);
+    else if (k <= 4) launch_small<T, 4>(c, val, diag, X, k, S, sorted, s);
+    else if (k <= 8) launch_small<T, 8>(c, val, diag, X, k, S, sorted, s);
+    else launch_small<T, 16>(c, val, diag, X, k, S, sorted, s);
+}
+
 int env_int(const char *name, int dflt) {
     const char *v = std::getenv(name);
     return (v && *v) ? std::atoi(v) : dflt;
@@ -444,6 +544,21 @@ int kindex(int k) { return k <= 1 ? 0 : k <= 2 ? 1 : k <= 4 ? 2 : k <= 8 ? 3 : 4
 template <typename T, int K>
 constexpr int lanes_per_coupling() {
     return (K >= Vec16<T>::n) ? K / Vec16<T>::n : 1;
+}
+
+// Rows a team takes from its XCD's counter at a time; 0: fixed strides.  The
+// atomics on one counter come through at about 24 ns each (1e6 rows, runs of
+// one row: 3.0 ms, all of it the counters), so below SIGMA_STATIC_NNZ couplings
+// they cost more than the shared L2 gives: 3,000 rows k = 8 18.9 us with
+// counters, 5.1 with strides; 20,000 rows 118 / 69; 100,000 short rows 99 / 42;
+// equal at 3.5e7 couplings (353 / 336 us), and 1749 / 1842 us at 1.6e8.
+constexpr int64_t SIGMA_STATIC_NNZ = 32000000;
+constexpr double SIGMA_LONG_ROW = 256.0;  // mean couplings from which two rows make a run
+
+int row_run(const Ctx &c, const SigmaCfg &cfg) {
+    if (cfg.run >= 0) return cfg.run;
+    if (c.nnz <= SIGMA_STATIC_NNZ) return 0;
+    return (double)c.nnz >= SIGMA_LONG_ROW * (double)c.ndet ? 2 : 4;
 }
 
 template <typename T, int K, int TEAM, int UNR, bool MASK>
@@ -462,14 +577,14 @@ void launch_sigma_u(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, cons
     XcdRows ranges;
     for (int x = 0; x <= NUM_XCD; ++x) ranges.b[x] = c.xcd_rows[x];
     const int xmap = env_int("HINQS_SIGMA_XCDMAP", 1);
-    if (cfg.pipe)
+    const int run = MASK ? 0 : row_run(c, cfg);
+    if (cfg.pipe == 1)
         hipLaunchKernelGGL((k_sigma_xr<T, K, TEAM, UNR, MASK>), dim3((unsigned)nblk), dim3(SIGMA_BLOCK), 0, s,
                            ranges, mk, xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds);
     else
         hipLaunchKernelGGL((k_sigma<T, K, TEAM, UNR, MASK>), dim3((unsigned)nblk), dim3(SIGMA_BLOCK), 0, s,
                            ranges, mk, xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds,
-                           MASK ? (unsigned long long *)nullptr : (ctr ? ctr : c.sigma_ctr.p),
-                           std::max(1, cfg.run));
+                           run > 0 ? (ctr ? ctr : c.sigma_ctr.p) : (unsigned long long *)nullptr, std::max(1, run));
     HQ_LAUNCH_CHECK();
 }
 
@@ -516,16 +631,32 @@ void dispatch_k(const Ctx &c, int k, const SigmaCfg &cfg, const T *val, const T 
 
 }  // namespace
 
-// Default shape before tuning: team sized to about four unrolled steps per mean row.
+// Default shape before tuning.  Row by row from counters: a team of about four
+// unrolled steps per mean row.  Fixed strides: fewer lanes per row (more rows
+// in flight; 4e5 rows of 70 couplings, k = 8: 32 lanes 394 us, 64 lanes 441),
+// doubled while the rows' teams do not fill the chip (5,000 rows of 13: 16
+// lanes 5.9 us, 8 lanes 7.2), four couplings in flight per lane (1e5 rows of
+// 19: 41.8 against 46.4 us with two).
 SigmaCfg default_cfg(const Ctx &c, int k, int precision) {
     const int vw = precision == HINQS_FP64 ? 2 : 4;
     const int lpn = k >= vw ? k / vw : 1;
     const double avg = c.ndet > 0 ? (double)c.nnz / (double)c.ndet : 0.0;
     const double want = avg / 8.0 * lpn;
     SigmaCfg g;
-    g.team = want <= 8 ? 8 : want <= 16 ? 16 : want <= 32 ? 32 : 64;
-    g.unr = 2;
     g.occ = 4;
+    if (c.nnz <= SIGMA_STATIC_NNZ) {
+        g.team = want <= 3 ? 8 : want <= 12 ? 16 : want <= 72 ? 32 : 64;
+        while (g.team < 64 && c.ndet * g.team < (int64_t)256 * 1024) g.team *= 2;
+        g.unr = 4;
+        if (c.ndet <= SIGMA_SMALL_ROWS) g.pipe = 2;
+    } else {
+        // long rows, and the eight lanes of a 128-byte row of X, take four
+        // couplings in flight per lane (615 couplings per row: 1116 against
+        // 1163 us; k = 16 at 1e6 rows: 2352 against 2494; k = 8 there: 1789
+        // against 1749)
+        g.team = want <= 8 ? 8 : want <= 16 ? 16 : want <= (lpn == 1 ? 96 : 32) ? 32 : 64;
+        g.unr = lpn >= 8 || avg >= SIGMA_LONG_ROW ? 4 : 2;
+    }
     return g;
 }
 
@@ -533,6 +664,7 @@ SigmaCfg sigma_config(const Ctx &c, int k, int precision) {
     SigmaCfg g = c.sigma_cfg[precision == HINQS_FP64 ? 0 : 1][kindex(k)];
     if (g.team == 0) g = default_cfg(c, k, precision);
     // explicit overrides for experiments
+    if (std::getenv("HINQS_SIGMA_TEAM") && g.pipe == 2) g.pipe = 0;
     g.team = env_int("HINQS_SIGMA_TEAM", g.team);
     g.unr = env_int("HINQS_SIGMA_UNR", g.unr);
     g.occ = env_int("HINQS_SIGMA_OCC", g.occ);
@@ -541,25 +673,48 @@ SigmaCfg sigma_config(const Ctx &c, int k, int precision) {
     return g;
 }
 
+namespace {
+
+void launch_shape(const Ctx &c, int k, int precision, const SigmaCfg &cfg, const void *X, int ldx, void *S, int lds,
+                  hipStream_t s, unsigned long long *ctr) {
+    const bool small = cfg.pipe == 2 && ldx == k && lds == k;
+    if (precision == HINQS_FP64) {
+        if (small) dispatch_small<double>(c, c.val.p, c.diag.p, (const double *)X, k, (double *)S, true, s);
+        else dispatch_k<double>(c, k, cfg, c.val.p, c.diag.p, (const double *)X, ldx, (double *)S, lds, s,
+                                SigmaMask{}, ctr);
+    } else if (precision == HINQS_FP32) {
+        if (small) dispatch_small<float>(c, c.val32.p, c.diag32.p, (const float *)X, k, (float *)S, true, s);
+        else dispatch_k<float>(c, k, cfg, c.val32.p, c.diag32.p, (const float *)X, ldx, (float *)S, lds, s,
+                               SigmaMask{}, ctr);
+    } else {
+        throw Error(HINQS_E_INVALID_ARG, "precision must be HINQS_FP64 or HINQS_FP32");
+    }
+}
+
+}  // namespace
+
 // X, S in sorted order; k in {1,2,4,8,16}; leading dimensions keep 16-byte
 // alignment of every row (ldx, lds multiples of 16 / sizeof(T) when k >= that).
 void sigma_sorted(Ctx &c, int k, const void *X, int ldx, void *S, int lds, int precision,
                   hipStream_t s, unsigned long long *ctr) {
     if (!c.have_elements) throw Error(HINQS_E_NOT_READY, "matrix elements are not built");
-    const SigmaCfg cfg = sigma_config(c, k, precision);
+    launch_shape(c, k, precision, sigma_config(c, k, precision), X, ldx, S, lds, s, ctr);
+}
+
+bool sigma_small(const Ctx &c, int k, const void *X, void *S, int precision, bool sorted, hipStream_t s) {
+    const int K = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
+    if (sigma_config(c, K, precision).pipe != 2) return false;
     if (precision == HINQS_FP64)
-        dispatch_k<double>(c, k, cfg, c.val.p, c.diag.p, (const double *)X, ldx, (double *)S, lds, s,
-                           SigmaMask{}, ctr);
-    else if (precision == HINQS_FP32)
-        dispatch_k<float>(c, k, cfg, c.val32.p, c.diag32.p, (const float *)X, ldx, (float *)S, lds, s,
-                          SigmaMask{}, ctr);
+        dispatch_small<double>(c, c.val.p, c.diag.p, (const double *)X, k, (double *)S, sorted, s);
     else
-        throw Error(HINQS_E_INVALID_ARG, "precision must be HINQS_FP64 or HINQS_FP32");
+        dispatch_small<float>(c, c.val32.p, c.diag32.p, (const float *)X, k, (float *)S, sorted, s);
+    return true;
 }
 
 void sigma_offdiag_fp32(const Ctx &c, int k, const float *X, float *S, hipStream_t s) {
     if (!c.have_elements) throw Error(HINQS_E_NOT_READY, "matrix elements are not built");
     const SigmaCfg cfg = sigma_config(c, k, HINQS_FP32);
+    if (cfg.pipe == 2) return dispatch_small<float>(c, c.val32.p, (const float *)nullptr, X, k, S, true, s);
     dispatch_k<float>(c, k, cfg, c.val32.p, (const float *)nullptr, X, k, S, k, s);
 }
 
@@ -572,12 +727,7 @@ void sigma_masked_fp64(const Ctx &c, int k, const double *X, double *S, const Si
 void sigma_launch(const Ctx &c, int k, int precision, const SigmaCfg &cfg, const void *X, int ldx, void *S,
                   int lds, hipStream_t s) {
     if (!c.have_elements) throw Error(HINQS_E_NOT_READY, "matrix elements are not built");
-    if (precision == HINQS_FP64)
-        dispatch_k<double>(c, k, cfg, c.val.p, c.diag.p, (const double *)X, ldx, (double *)S, lds, s);
-    else if (precision == HINQS_FP32)
-        dispatch_k<float>(c, k, cfg, c.val32.p, c.diag32.p, (const float *)X, ldx, (float *)S, lds, s);
-    else
-        throw Error(HINQS_E_INVALID_ARG, "precision must be HINQS_FP64 or HINQS_FP32");
+    launch_shape(c, k, precision, cfg, X, ldx, S, lds, s, nullptr);
 }
 
 }  // namespace hinqs

@@ -1,0 +1,45 @@
+"""Edges of the kernels' size rules: the sizes where a launch shape, a tile or a
+class of rows changes, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2606_26760_amd as hq
+import workloads as W
+from tests.gpu_helpers import log, oracle_for, oracle_rows_as_tuples, row_bound, solver_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("ndet", [1, 5, 8192, 8193])
+def test_sigma_either_side_of_the_small_set_rule(ndet):
+    """One wave per row up to 8,192 rows, teams with staging above: widths that
+    are padded and that are not, both precisions, both orders, X and S one
+    element off 16-byte alignment, and the bits of the entry point that
+    allocates nothing."""
+    ints, a, b, cfg = W.config_inputs(1, ndet=ndet)
+    log(f"sigma at {ndet} rows")
+    s = solver_for(ints, a, b, cfg.na, cfg.nb)
+    o = oracle_for(ints, a, b, cfg.na, cfg.nb)
+    rows = np.unique(np.linspace(0, ndet - 1, 300).astype(np.int64))
+    perm = s.permutation().cpu().numpy()
+    _, r = oracle_rows_as_tuples(o, rows)
+    for k in (1, 3, 8, 16):
+        X = W.random_block(ndet, k, 900 + k)
+        for dtype, tol in ((torch.float64, 1e-12), (torch.float32, 2e-6)):
+            Xd = torch.from_numpy(X).to(dtype).cuda()
+            Xr = Xd.double().cpu().numpy()
+            ref, bound = o.sigma_rows(Xr, rows), row_bound(r, Xr, k)
+            flat = torch.empty(ndet * k + 1, dtype=dtype, device="cuda")
+            odd = flat[1:].view(ndet, k)
+            odd.copy_(Xd)
+            out = torch.empty(ndet * k + 1, dtype=dtype, device="cuda")[1:].view(ndet, k)
+            S = s.sigma(Xd)
+            products = [S, s.sigma(odd, out=out), s.sigma_noalloc(Xd, torch.empty_like(Xd))]
+            sorted_S = s.sigma(Xd[torch.from_numpy(perm).long().cuda()].contiguous(), sorted_order=True)
+            back = torch.empty_like(S)
+            back[torch.from_numpy(perm).long().cuda()] = sorted_S
+            for P in products + [back]:
+                err = np.abs(P.double().cpu().numpy()[rows] - ref)
+                assert np.all(err <= tol * bound + 1e-300), (k, dtype)
+            assert torch.equal(products[2], S)
