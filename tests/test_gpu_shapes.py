@@ -43,3 +43,29 @@ def test_sigma_either_side_of_the_small_set_rule(ndet):
                 err = np.abs(P.double().cpu().numpy()[rows] - ref)
                 assert np.all(err <= tol * bound + 1e-300), (k, dtype)
             assert torch.equal(products[2], S)
+
+
+@pytest.mark.parametrize("norb,na,nb,ndet", [(1, 1, 0, 1), (2, 1, 1, 4), (9, 4, 5, 63), (16, 8, 8, 65), (16, 7, 5, 3001),
+                                             (17, 6, 5, 2500)])
+def test_rdm12_either_side_of_the_table_rule(norb, na, nb, ndet):
+    """Class tables in LDS up to 16 orbitals, global copies above: uneven spins,
+    row counts around a wave, the smallest orbital counts."""
+    log(f"rdm12 norb {norb}, {ndet} determinants")
+    ints = W.gen_integrals(norb, 3, -2.0, -0.5, 77)
+    if ndet >= 64:
+        a, b = W.sample_determinants(norb, na, nb, ndet, 0.4, 0.1, 78)
+    else:
+        a, b = W.sample_determinants(norb, na, nb, ndet, 0.4, 0.0, 78)
+    s = solver_for(ints, a, b, na, nb)
+    o = oracle_for(ints, a, b, na, nb)
+    c = np.random.default_rng(5).standard_normal(ndet)
+    c /= np.linalg.norm(c)
+    for order in (False, True):
+        x = torch.from_numpy(c).cuda()
+        if order:
+            x = x[s.permutation().long()].contiguous()
+        d1, d2 = (t.cpu().numpy() for t in s.rdm12(x, sorted_order=order))
+        r1, r2 = o.rdm12(c)
+        # sums of at most ndet * couplings products of two coefficients
+        assert np.abs(d1 - r1).max() <= 1e-12 * max(1.0, np.abs(r1).max())
+        assert np.abs(d2 - r2).max() <= 1e-12 * max(1.0, np.abs(r2).max())
