@@ -358,7 +358,7 @@ struct Ctx {
     // once a size has been seen, repeating the call allocates nothing and has
     // no buffer to release, so it need not wait for the stream
     struct CallScratch {
-        DBuf<char> b[5];
+        DBuf<char> b[8];
         DBuf<unsigned long long> flags;  // small counters and error flags
         template <typename T>
         T *get(int i, size_t count) {

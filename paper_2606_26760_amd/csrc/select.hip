@@ -24,7 +24,7 @@ namespace hinqs {
 
 namespace {
 
-constexpr int EX_NT = 256;  // expansion: one workgroup per chosen determinant at a time
+constexpr int EX_NT = 1024; // expansion: one workgroup per chosen determinant at a time
 constexpr int PT_NT = 1024; // PT2: one wave per candidate at a time
 constexpr int NPAIR32 = 32 * 31 / 2;
 
@@ -143,12 +143,16 @@ struct ExpArgs {
 // r = 0 .. nexc-1 in five ranges: alpha singles, beta singles, alpha-alpha
 // doubles, beta-beta doubles, alpha-beta doubles.  y is kept when
 // <y|H|x> != 0 and y is not in B; kept keys (alpha << norb | beta) are
-// appended with one atomic per wave.
+// appended with one atomic per workgroup pass (one per wave, on the one
+// counter, took 1.1 ms for 1,000 determinants of 5,545 excitations;
+// 0.20 ms).
 template <bool USE_LDS>
 __global__ __launch_bounds__(EX_NT) void k_expand(ExpArgs a) {
     extern __shared__ double smem[];
     __shared__ uint16_t pairs[NPAIR32];      // k = j (j - 1) / 2 + i  ->  i | j << 8, i < j
     __shared__ uint8_t occ[2][32], vir[2][32];
+    __shared__ int wcnt[EX_NT / 64];
+    __shared__ unsigned long long wbase[EX_NT / 64];
     const double *eri, *h;
     stage_integrals<USE_LDS>(smem, a.eri, a.h, a.npack, a.norb, eri, h);
     for (int k = threadIdx.x; k < NPAIR32; k += blockDim.x) {
@@ -209,13 +213,23 @@ __global__ __launch_bounds__(EX_NT) void k_expand(ExpArgs a) {
                 }
             }
             const uint64_t m = __ballot(keep);
-            if (m) {
-                const int leader = __builtin_ctzll(m);
+            if (lane == 0) wcnt[threadIdx.x >> 6] = __popcll(m);
+            __syncthreads();
+            if (threadIdx.x < 64) {
+                const int n = threadIdx.x < EX_NT / 64 ? wcnt[threadIdx.x] : 0;
+                int incl = n;
+#pragma unroll
+                for (int off = 1; off < EX_NT / 64; off <<= 1) {
+                    const int x = __shfl_up(incl, off, 64);
+                    if (lane >= off) incl += x;
+                }
                 unsigned long long base = 0;
-                if (lane == leader) base = atomicAdd(a.count, (unsigned long long)__popcll(m));
-                base = __shfl(base, leader, 64);
-                if (keep) a.keys[base + __popcll(m & ((1ull << lane) - 1ull))] = key;
+                if (threadIdx.x == EX_NT / 64 - 1 && incl > 0) base = atomicAdd(a.count, (unsigned long long)incl);
+                base = __shfl(base, EX_NT / 64 - 1, 64);
+                if (threadIdx.x < EX_NT / 64) wbase[threadIdx.x] = base + (unsigned long long)(incl - n);
             }
+            __syncthreads();
+            if (keep) a.keys[wbase[threadIdx.x >> 6] + __popcll(m & ((1ull << lane) - 1ull))] = key;
         }
     }
 }
@@ -250,18 +264,69 @@ struct Pt2Args {
     const double *eri, *h;
     double *numer, *hxx, *score;
     unsigned *bad;
+    // per candidate in key order: H_xx, and (links done elsewhere) the same-spin numerator
+    double *dval, *part;
 };
 
 constexpr int SCAN_U = 8;  // group entries in flight per lane
 
-// acc += c_j <x|H|x_j> over the rows j in [lo, hi) of one alpha group (alpha
-// string aj) whose beta string differs from xb by a number of electrons in
-// the accepted set: SAME_ALPHA accepts 0 (the diagonal d), 1 or 2 electrons,
-// otherwise exactly one.
-template <bool SAME_ALPHA>
-__device__ inline void scan_alpha_group(const Pt2Args &a, const double *eri, const double *h, int32_t lo,
-                                        int32_t hi, uint32_t xa, uint32_t xb, uint32_t aj, double d, int lane,
-                                        double &acc) {
+// <x|H|x_j> for strings si (of x) and sj that differ by two electrons of one
+// spin, the other spin's string being the same.
+__device__ inline double same_spin_double(const double *eri, uint32_t si, uint32_t sj) {
+    const uint32_t holes = sj & ~si, parts = si & ~sj;
+    const int h1 = lowbit(holes), h2 = highbit(holes), p1 = lowbit(parts), p2 = highbit(parts);
+    const double v = eri[eri_index(p1, h1, p2, h2)] - eri[eri_index(p1, h2, p2, h1)];
+    return double_parity(sj, h1, h2, p1, p2) ? -v : v;
+}
+
+// ... by one electron; other: the string of the other spin.
+__device__ inline double same_spin_single(const double *eri, const double *h, int norb, uint32_t si, uint32_t sj,
+                                          uint32_t other) {
+    const int q = lowbit(sj & ~si), p = lowbit(si & ~sj);
+    const double v = single_value(eri, h, norb, p, q, si & sj, other);
+    return single_parity(sj, q, p) ? -v : v;
+}
+
+// acc += c_j <x|H|x_j> over the members at [lo, hi) of one group that share
+// the other spin's string: str their strings of this spin, own that of x, pos
+// their place in cs (null: the same, and a member equal to x takes the diagonal
+// d).  Doubles and singles are summed in passes of their own: a single costs
+// a sum over every electron, which each lane would otherwise wait for at nearly
+// every step.
+__device__ inline void scan_same_spin(const Pt2Args &a, const double *eri, const double *h, const uint32_t *str,
+                                      const int32_t *pos, int32_t lo, int32_t hi, uint32_t own, uint32_t other,
+                                      double d, int lane, double &acc) {
+    for (int32_t j0 = lo + lane; j0 < hi; j0 += 64 * SCAN_U) {
+        uint32_t sj[SCAN_U];
+#pragma unroll
+        for (int u = 0; u < SCAN_U; ++u) {
+            const int32_t j = j0 + 64 * u;
+            sj[u] = j < hi ? str[j] : ~own;
+        }
+        uint32_t m2 = 0, m1 = 0, m0 = 0;
+#pragma unroll
+        for (int u = 0; u < SCAN_U; ++u) {
+            const int n = popc32(own ^ sj[u]);
+            m2 |= n == 4 ? 1u << u : 0u;
+            m1 |= n == 2 ? 1u << u : 0u;
+            m0 |= n == 0 ? 1u << u : 0u;
+        }
+        for (; m2; m2 &= m2 - 1) {
+            const int32_t j = j0 + 64 * lowbit(m2);
+            acc += a.cs[pos ? pos[j] : j] * same_spin_double(eri, own, str[j]);
+        }
+        for (; m1; m1 &= m1 - 1) {
+            const int32_t j = j0 + 64 * lowbit(m1);
+            acc += a.cs[pos ? pos[j] : j] * same_spin_single(eri, h, a.norb, own, str[j], other);
+        }
+        if (m0 && !pos) acc += a.cs[j0 + 64 * lowbit(m0)] * d;
+    }
+}
+
+// acc += c_j <x|H|x_j> over the rows j in [lo, hi) of the alpha group of aj, one
+// move from xa, whose beta string is one move from xb.
+__device__ inline void scan_alpha_group(const Pt2Args &a, const double *eri, const double *h, int32_t lo, int32_t hi,
+                                        uint32_t xa, uint32_t xb, uint32_t aj, int lane, double &acc) {
     for (int32_t j0 = lo + lane; j0 < hi; j0 += 64 * SCAN_U) {
         uint32_t bj[SCAN_U];
 #pragma unroll
@@ -269,24 +334,13 @@ __device__ inline void scan_alpha_group(const Pt2Args &a, const double *eri, con
             const int32_t j = j0 + 64 * u;
             bj[u] = j < hi ? a.B.sb[j] : ~xb;
         }
-        uint32_t m = 0, m0 = 0;  // entries needing a coupling value / the diagonal
+        uint32_t m = 0;
 #pragma unroll
-        for (int u = 0; u < SCAN_U; ++u) {
-            const int db = popc32(xb ^ bj[u]);
-            if (SAME_ALPHA) {
-                m0 |= db == 0 ? 1u << u : 0u;
-                m |= (db != 0 && db <= 4) ? 1u << u : 0u;
-            } else {
-                m |= db == 2 ? 1u << u : 0u;
-            }
-        }
+        for (int u = 0; u < SCAN_U; ++u) m |= popc32(xb ^ bj[u]) == 2 ? 1u << u : 0u;
         // the hits in ascending order, so every lane sums its entries in group order
-        for (uint32_t mm = m | m0; mm; mm &= mm - 1) {
-            const int u = lowbit(mm);
-            const int32_t j = j0 + 64 * u;
-            const double v =
-                (m0 >> u) & 1u ? d : coupling_value(eri, h, a.norb, pair_desc(xa, xb, aj, a.B.sb[j]), xa, xb);
-            acc += a.cs[j] * v;
+        for (; m; m &= m - 1) {
+            const int32_t j = j0 + 64 * lowbit(m);
+            acc += a.cs[j] * coupling_value(eri, h, a.norb, pair_desc(xa, xb, aj, a.B.sb[j]), xa, xb);
         }
     }
 }
@@ -342,6 +396,34 @@ __global__ void k_pt2_groups(const BTables B, const uint64_t *ca, const uint64_t
     gb_of[u] = ok ? find_u32(B.ub, B.nub, (uint32_t)b) : -1;
 }
 
+// H_xx of every candidate, one thread each; malformed candidates get NaN
+// outputs and raise the flag.  (With all 64 lanes of a candidate's wave
+// computing the same sum this took 5.1 of 21.3 ms on 8.8e5 candidates.)
+template <bool USE_LDS>
+__global__ __launch_bounds__(256) void k_pt2_diag(Pt2Args a, const int32_t *order) {
+    extern __shared__ double smem[];
+    const double *eri, *h;
+    stage_integrals<USE_LDS>(smem, a.eri, a.h, a.npack, a.norb, eri, h);
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < a.ncand;
+         u += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t t = order[u];
+        const uint64_t a64 = a.ca[t], b64 = a.cb[t];
+        if ((a64 >> a.norb) != 0 || (b64 >> a.norb) != 0 || (int)__popcll(a64) != a.na ||
+            (int)__popcll(b64) != a.nb) {
+            atomicOr(a.bad, 1u);
+            const double nan = __longlong_as_double(0x7ff8000000000000ll);
+            if (a.numer) a.numer[t] = nan;
+            if (a.hxx) a.hxx[t] = nan;
+            if (a.score) a.score[t] = nan;
+            a.dval[u] = a.part[u] = nan;
+            continue;
+        }
+        const double d = diag_value(eri, h, a.norb, a.ecore, (uint32_t)a64, (uint32_t)b64);
+        a.dval[u] = d;
+        if (a.hxx) a.hxx[t] = d;
+    }
+}
+
 // Waves take runs of PT2_RUN consecutive candidates in key order from a
 // shared counter (every wave stops once the counter passes ncand), one
 // candidate at a time.  Its partners in B fall into three disjoint classes, each read from
@@ -351,13 +433,14 @@ __global__ void k_pt2_groups(const BTables B, const uint64_t *ca, const uint64_t
 //   one move in each spin    the alpha groups of the strings one move from xa
 //                            (link table when xa is an alpha string of B, else
 //                            searched), keeping beta strings one move from xb
+//                            (LINKS; otherwise k_pt2_links adds this class)
 // The diagonal enters through the first class when x lies in B.  Candidates
 // of a run mostly share xa, so the bounds of its alpha groups are loaded once
 // per distinct xa and kept in the lanes (slot r of lane l: move 64 r + l;
 // SLOTS * 64 >= na (norb - na)).
 constexpr int PT2_RUN = 16;
 
-template <bool USE_LDS, int SLOTS>
+template <bool USE_LDS, int SLOTS, bool LINKS>
 __global__ __launch_bounds__(PT_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_pt2(
     Pt2Args a, const int32_t *order, const int32_t *ga_of, const int32_t *gb_of, unsigned long long *next) {
     extern __shared__ double smem[];
@@ -384,19 +467,13 @@ __global__ __launch_bounds__(PT_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) v
         const int32_t t = order[u];
         const uint64_t a64 = a.ca[t], b64 = a.cb[t];
         const int32_t g = ga_of[u], gbx = gb_of[u];
+        const double d = a.dval[u];
+        double *const part = LINKS ? nullptr : a.part + u;
         ++u;
-        if ((a64 >> norb) != 0 || (b64 >> norb) != 0 || (int)__popcll(a64) != a.na || (int)__popcll(b64) != a.nb) {
-            if (lane == 0) {
-                atomicOr(a.bad, 1u);
-                const double nan = __longlong_as_double(0x7ff8000000000000ll);
-                if (a.numer) a.numer[t] = nan;
-                if (a.hxx) a.hxx[t] = nan;
-                if (a.score) a.score[t] = nan;
-            }
+        if ((a64 >> norb) != 0 || (b64 >> norb) != 0 || (int)__popcll(a64) != a.na || (int)__popcll(b64) != a.nb)
             continue;
-        }
         const uint32_t xa = (uint32_t)a64, xb = (uint32_t)b64;
-        if (!have || xa != cur_a) {  // alpha groups one move from xa
+        if (LINKS && (!have || xa != cur_a)) {  // alpha groups one move from xa
             have = true;
             cur_a = xa;
             nlink = g >= 0 ? a.alink_ptr[g] : nmov;
@@ -418,33 +495,13 @@ __global__ __launch_bounds__(PT_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) v
                 aj_m[r] = gm >= 0 ? a.B.ua[gm] : 0u;
             }
         }
-        const double d = diag_value(eri, h, norb, a.ecore, xa, xb);
         double acc = 0.0;
-        if (g >= 0) scan_alpha_group<true>(a, eri, h, a.B.ga[g], a.B.ga[g + 1], xa, xb, xa, d, lane, acc);
-        if (gbx >= 0) {
-            const int32_t end = a.B.gb[gbx + 1];
-            for (int32_t u0 = a.B.gb[gbx] + lane; u0 < end; u0 += 64 * SCAN_U) {
-                uint32_t aj[SCAN_U];
+        if (g >= 0)
+            scan_same_spin(a, eri, h, a.B.sb, nullptr, a.B.ga[g], a.B.ga[g + 1], xb, xa, d, lane, acc);
+        if (gbx >= 0)
+            scan_same_spin(a, eri, h, a.B.bm_alpha, a.B.bperm, a.B.gb[gbx], a.B.gb[gbx + 1], xa, xb, 0.0, lane, acc);
 #pragma unroll
-                for (int v = 0; v < SCAN_U; ++v) {
-                    const int32_t q = u0 + 64 * v;
-                    aj[v] = q < end ? a.B.bm_alpha[q] : xa;
-                }
-                uint32_t m = 0;
-#pragma unroll
-                for (int v = 0; v < SCAN_U; ++v) {
-                    const int da = popc32(xa ^ aj[v]);
-                    m |= (da != 0 && da <= 4) ? 1u << v : 0u;
-                }
-                for (; m; m &= m - 1) {
-                    const int32_t q = u0 + 64 * lowbit(m);
-                    acc += a.cs[a.B.bperm[q]] *
-                           coupling_value(eri, h, norb, pair_desc(xa, xb, a.B.bm_alpha[q], xb), xa, xb);
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < SLOTS; ++r) {
+        for (int r = 0; r < (LINKS ? SLOTS : 0); ++r) {
             const int32_t sz = hi_m[r] - lo_m[r];
             uint64_t found = __ballot(sz > PT2_SMALL);  // large groups: the whole wave, one at a time
             while (found) {
@@ -452,7 +509,7 @@ __global__ __launch_bounds__(PT_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) v
                 found &= found - 1;
                 const int32_t lo = __shfl(lo_m[r], src, 64), hi = __shfl(hi_m[r], src, 64);
                 const uint32_t aj = (uint32_t)__shfl((int)aj_m[r], src, 64);
-                scan_alpha_group<false>(a, eri, h, lo, hi, xa, xb, aj, d, lane, acc);
+                scan_alpha_group(a, eri, h, lo, hi, xa, xb, aj, lane, acc);
             }
             found = __ballot(sz > 0 && sz <= PT2_SMALL);  // small groups: 64 / PT2_GL at a time
             while (found) {
@@ -473,9 +530,229 @@ __global__ __launch_bounds__(PT_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) v
         }
         acc = wave_sum_d(acc);
         if (lane == 0) {
-            if (a.numer) a.numer[t] = acc;
-            if (a.hxx) a.hxx[t] = d;
-            if (a.score) a.score[t] = acc * acc / fabs(a.e0 - d);
+            if (!LINKS) {
+                *part = acc;
+            } else {
+                if (a.numer) a.numer[t] = acc;
+                if (a.score) a.score[t] = acc * acc / fabs(a.e0 - d);
+            }
+        }
+    }
+}
+
+// ------------------------------------- one move in each spin, through tables
+// Members of each alpha group as a bit per distinct beta string: word w of a
+// group holds strings 32 w .. 32 w + 31 (x: the bits, y: members before them).
+// The partners of a candidate in a group are then looked up by its own beta
+// moves (na (norb - na) tests) instead of read past (the group's rows).
+constexpr int PT2_MAX_WORDS = 1024;            // 32,768 distinct beta strings
+constexpr int64_t PT2_MAX_TABLE = 256 << 20;   // bytes
+constexpr int PT2_CS = 2304;                   // members of a group whose coefficients are staged
+constexpr int PT2_CPW = 4;                     // candidates of a wave
+constexpr int PT2_TILE = PT2_CPW * PT_NT / 64; // and of a workgroup
+constexpr int PT2_MAX_MOVES = 256;
+constexpr int PT2_MAX_PAIRS = 32 * 33 / 2;
+static_assert(PT2_MAX_PAIRS <= PT_NT && PT2_MAX_WORDS <= PT_NT && PT2_CS <= 3 * PT_NT, "staging");
+
+__global__ void k_pt2_bits(int64_t ndet, const int32_t *aidx, const int32_t *bidx, int words, uint2 *tab) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ndet) return;
+    const int32_t b = bidx[i];
+    atomicOr(&tab[(int64_t)aidx[i] * words + (b >> 5)].x, 1u << (b & 31));
+}
+
+// Members before each word, one wave per group.
+__global__ __launch_bounds__(256) void k_pt2_ranks(int32_t nua, int words, uint2 *tab) {
+    const int lane = threadIdx.x & 63;
+    const int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (g >= nua) return;
+    uint2 *row = tab + g * words;
+    int before = 0;
+    for (int w0 = 0; w0 < words; w0 += 64) {
+        const int w = w0 + lane;
+        const int n = w < words ? popc32(row[w].x) : 0;
+        int incl = n;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int x = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += x;
+        }
+        if (w < words) row[w].y = (uint32_t)(before + incl - n);
+        before += __shfl(incl, 63, 64);
+    }
+}
+
+// flag[u] = 1 where a tile starts: every PT2_TILE candidates of a run that shares its alpha string.
+__global__ void k_pt2_tile_flags(const uint64_t *keys, int64_t n, int norb, int32_t *flag) {
+    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= n) return;
+    const uint64_t first = (keys[u] >> norb) << norb;
+    int64_t lo = 0, hi = u;  // first candidate of the run
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (keys[mid] < first) lo = mid + 1;
+        else hi = mid;
+    }
+    flag[u] = (u - lo) % PT2_TILE == 0 ? 1 : 0;
+}
+
+__global__ void k_pt2_tile_list(const int32_t *flag, const int32_t *pos, int64_t n, int32_t *tiles, int32_t *ntiles) {
+    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= n) return;
+    if (flag[u]) tiles[pos[u]] = (int32_t)u;
+    if (u == n - 1) *ntiles = pos[u] + flag[u];
+}
+
+// Numerators over the alpha groups one move from the candidates' common alpha
+// string, added to the same-spin part.  A workgroup owns one tile and walks the
+// groups: the group's bits, its members' coefficients and the row of integrals
+// (pa ha|..) of the alpha move are staged in LDS (the next group's while this
+// one is used); lane l of a wave holds beta move 64 s + l of each of the wave's
+// four candidates -- the index of the string it leads to, its integral and its
+// sign -- tests the bit and, on a hit, adds coefficient times integral.
+// What bounds it: scanning the groups read every member for every candidate
+// through L1 (8.8e5 candidates, 1e6 rows: 13.4 of 21.3 ms); here a group is read
+// once for up to 64 candidates, and a test covers 64 moves where a scan step
+// covered 64 members, most of them not coupled: 4.1 ms.
+template <int SLOTS>
+__global__ __launch_bounds__(PT_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_pt2_links(
+    Pt2Args a, const uint64_t *keys, const int32_t *order, const int32_t *tiles, const int32_t *ntiles, int words,
+    const uint2 *tab) {
+    __shared__ uint2 s_bits[2][PT2_MAX_WORDS + 1];  // the word after the last is empty
+    __shared__ double s_cs[2][PT2_CS];
+    __shared__ double s_row[2][PT2_MAX_PAIRS];
+    __shared__ int32_t s_g[PT2_MAX_MOVES], s_lo[PT2_MAX_MOVES], s_sz[PT2_MAX_MOVES], s_mv[PT2_MAX_MOVES];
+    __shared__ int s_n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int norb = a.norb, nva = norb - a.na, nvb = norb - a.nb, nma = a.na * nva, nmb = a.nb * nvb;
+    const int npair = norb * (norb + 1) / 2;
+    const uint32_t full = norb >= 32 ? 0xffffffffu : ((1u << norb) - 1u);
+    const int nt = *ntiles;
+    if (tid < 2) s_bits[tid][words] = make_uint2(0, 0);
+    for (int tile = blockIdx.x; tile < nt; tile += gridDim.x) {
+        const int64_t u0 = tiles[tile];
+        const uint32_t xa = (uint32_t)(keys[u0] >> norb);
+        if (popc32(xa) != a.na) continue;  // malformed candidates (uniform over the workgroup)
+        __syncthreads();                   // the previous tile's lists are no longer read
+        if (wave == 0) {  // the groups one move away, in the order of the moves
+            int at = 0;
+            for (int m0 = 0; m0 < nma; m0 += 64) {
+                const int m = m0 + lane;
+                int32_t g = -1;
+                int r = 0, q = 0;
+                if (m < nma) {
+                    r = nth_bit(xa, m / nva);
+                    q = nth_bit(~xa & full, m % nva);
+                    g = find_u32(a.B.ua, a.B.nua, xa ^ (1u << r) ^ (1u << q));
+                }
+                const uint64_t on = __ballot(g >= 0);
+                if (g >= 0) {
+                    const int k = at + __popcll(on & ((1ull << lane) - 1ull));
+                    s_g[k] = g;
+                    s_lo[k] = a.B.ga[g];
+                    s_sz[k] = a.B.ga[g + 1] - a.B.ga[g];
+                    s_mv[k] = pair_index(r, q) | (int)(single_parity(xa ^ (1u << r) ^ (1u << q), q, r) << 16);
+                }
+                at += __popcll(on);
+            }
+            if (lane == 0) s_n = at;
+        }
+        // this wave's candidates: word | bit << 16 of the string each beta move
+        // leads to (the empty word: none), integral | sign << 31
+        int32_t at[PT2_CPW][SLOTS], mv[PT2_CPW][SLOTS];
+        double acc[PT2_CPW];
+        int mine = 0;
+#pragma unroll
+        for (int c = 0; c < PT2_CPW; ++c) {
+            acc[c] = 0.0;
+            const int64_t u = u0 + wave * PT2_CPW + c;
+            const uint64_t key = u < a.ncand ? keys[u] : ~0ull;
+            const uint32_t xb = (uint32_t)key & full;
+            const bool ok = u < a.ncand && (uint32_t)(key >> norb) == xa && popc32(xb) == a.nb;
+            mine |= ok ? 1 << c : 0;
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s) {
+                const int m = 64 * s + lane;
+                at[c][s] = words;
+                mv[c][s] = 0;
+                if (ok && m < nmb) {
+                    const int r = nth_bit(xb, m / nvb), q = nth_bit(~xb & full, m % nvb);
+                    const uint32_t bj = xb ^ (1u << r) ^ (1u << q);
+                    const int32_t b = find_u32(a.B.ub, a.B.nub, bj);
+                    if (b >= 0) at[c][s] = (b >> 5) | (b & 31) << 16;
+                    mv[c][s] = pair_index(r, q) | (int)(single_parity(bj, q, r) << 31);
+                }
+            }
+        }
+        __syncthreads();
+        const int nl = s_n;
+        uint2 rb = {};
+        double rc[3] = {}, rr = 0.0;
+        auto fetch = [&](int l) {
+            const int32_t lo = s_lo[l], sz = s_sz[l] <= PT2_CS ? s_sz[l] : 0, m = s_mv[l], A = m & 0xffff;
+            if (tid < words) rb = tab[(int64_t)s_g[l] * words + tid];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (tid + i * PT_NT < sz) rc[i] = a.cs[lo + tid + i * PT_NT];
+            if (tid < npair) {
+                const double v = a.eri[A >= tid ? A * (A + 1) / 2 + tid : tid * (tid + 1) / 2 + A];
+                rr = m >> 16 ? -v : v;
+            }
+        };
+        auto store = [&](int l, int buf) {
+            const int32_t sz = s_sz[l] <= PT2_CS ? s_sz[l] : 0;
+            if (tid < words) s_bits[buf][tid] = rb;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (tid + i * PT_NT < sz) s_cs[buf][tid + i * PT_NT] = rc[i];
+            if (tid < npair) s_row[buf][tid] = rr;
+        };
+        if (nl > 0) {
+            fetch(0);
+            store(0, 0);
+        }
+        __syncthreads();
+        for (int l = 0; l < nl; ++l) {
+            const int buf = l & 1;
+            if (l + 1 < nl) fetch(l + 1);
+            auto test = [&](auto staged) {
+                const double *gcs = a.cs + s_lo[l];
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    uint2 w[PT2_CPW];
+#pragma unroll
+                    for (int c = 0; c < PT2_CPW; ++c) w[c] = s_bits[buf][at[c][s] & 0xffff];
+#pragma unroll
+                    for (int c = 0; c < PT2_CPW; ++c) {
+                        const uint32_t below = w[c].x & ((1u << (at[c][s] >> 16)) - 1u);
+                        if ((w[c].x >> (at[c][s] >> 16)) & 1u) {
+                            const int pos = (int)w[c].y + popc32(below);
+                            double v;
+                            if constexpr (decltype(staged)::value) v = s_cs[buf][pos];
+                            else v = gcs[pos];
+                            v *= s_row[buf][mv[c][s] & 0xffff];
+                            acc[c] += mv[c][s] < 0 ? -v : v;
+                        }
+                    }
+                }
+            };
+            if (mine) {
+                if (s_sz[l] <= PT2_CS) test(std::true_type{});
+                else test(std::false_type{});
+            }
+            if (l + 1 < nl) store(l + 1, buf ^ 1);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int c = 0; c < PT2_CPW; ++c) {
+            if (!((mine >> c) & 1)) continue;
+            const int64_t u = u0 + wave * PT2_CPW + c;
+            const double sum = wave_sum_d(acc[c]) + a.part[u];
+            if (lane == 0) {
+                const int32_t t = order[u];
+                if (a.numer) a.numer[t] = sum;
+                if (a.score) a.score[t] = sum * sum / fabs(a.e0 - a.dval[u]);
+            }
         }
     }
 }
@@ -561,7 +838,7 @@ int64_t expand(Ctx &c, const double *coeffs, bool sorted, int64_t ntop, int64_t 
         const unsigned grid = (unsigned)std::min<int64_t>(ntop, (int64_t)cus * 2);
         hipLaunchKernelGGL(k_expand<true>, dim3(grid), dim3(EX_NT), lds, s, ea);
     } else {
-        const unsigned grid = (unsigned)std::min<int64_t>(ntop, (int64_t)cus * 8);
+        const unsigned grid = (unsigned)std::min<int64_t>(ntop, (int64_t)cus * 2);
         hipLaunchKernelGGL(k_expand<false>, dim3(grid), dim3(EX_NT), 0, s, ea);
     }
     HQ_LAUNCH_CHECK();
@@ -605,7 +882,7 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
     unsigned long long *next = words + 1;
     HQ_CHECK(hipMemsetAsync(bad, 0, sizeof(unsigned), s));
     Pt2Args pa{tables_of(c), c.norb, neri_packed(c.norb), c.na, c.nb, c.alink_max, c.alink_ptr.p, c.alink.p,
-               c.ecore, e0, ncand, ca, cb, csp, c.d_eri.p, c.d_h.p, numer, hxx, score, bad};
+               c.ecore, e0, ncand, ca, cb, csp, c.d_eri.p, c.d_h.p, numer, hxx, score, bad, nullptr, nullptr};
     // candidates in key order, and their groups in B
     uint64_t *keys = c.cs.get<uint64_t>(1, ncand);
     int32_t *order = c.cs.get<int32_t>(2, ncand);
@@ -621,33 +898,74 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
     const size_t lds = integral_lds(c);
     const int cus = device_cus(c);
     const bool use_lds = lds <= 150 * 1024;
+    pa.dval = c.cs.get<double>(5, 2 * ncand);
+    pa.part = pa.dval + ncand;
+    const unsigned dgrid = (unsigned)std::min<int64_t>((ncand + 255) / 256, (int64_t)cus * 8);
+    if (use_lds) {
+        HQ_CHECK(hipFuncSetAttribute((const void *)k_pt2_diag<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds));
+        hipLaunchKernelGGL(k_pt2_diag<true>, dim3(dgrid), dim3(256), lds, s, pa, order);
+    } else {
+        hipLaunchKernelGGL(k_pt2_diag<false>, dim3(dgrid), dim3(256), 0, s, pa, order);
+    }
+    HQ_LAUNCH_CHECK();
+    // lookups by the candidates' own moves while the tables stay small; sets of
+    // very many distinct strings keep the scan
+    const int nwords = (c.nub + 31) / 32;
+    const int moves = c.na * (c.norb - c.na), moves_b = c.nb * (c.norb - c.nb);
+    const bool lookup = nwords <= PT2_MAX_WORDS && (int64_t)c.nua * nwords * (int64_t)sizeof(uint2) <= PT2_MAX_TABLE &&
+                        moves <= PT2_MAX_MOVES && moves_b <= PT2_MAX_MOVES;
     // resident workgroups only (two per CU); they share the candidates through a counter
     const int64_t runs = (ncand + PT2_RUN - 1) / PT2_RUN;
     const unsigned grid =
         (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * 2, (runs + PT_NT / 64 - 1) / (PT_NT / 64)));
     HQ_CHECK(hipMemsetAsync(next, 0, sizeof(unsigned long long), s));
-    const int moves = c.na * (c.norb - c.na);
-    auto launch = [&](auto lds_tag, auto slots_tag) {
+    auto launch = [&](auto lds_tag, auto slots_tag, auto links_tag) {
         constexpr bool L = decltype(lds_tag)::value;
         constexpr int S = decltype(slots_tag)::value;
+        constexpr bool K = decltype(links_tag)::value;
         if (L)
-            HQ_CHECK(hipFuncSetAttribute((const void *)k_pt2<L, S>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            HQ_CHECK(hipFuncSetAttribute((const void *)k_pt2<L, S, K>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                          (int)lds));
-        hipLaunchKernelGGL((k_pt2<L, S>), dim3(grid), dim3(PT_NT), L ? lds : 0, s, pa, order, ga_of, gb_of, next);
+        hipLaunchKernelGGL((k_pt2<L, S, K>), dim3(grid), dim3(PT_NT), L ? lds : 0, s, pa, order, ga_of, gb_of, next);
+        HQ_LAUNCH_CHECK();
     };
     using T = std::true_type;
     using F = std::false_type;
     using S1 = std::integral_constant<int, 1>;
     using S2 = std::integral_constant<int, 2>;
     using S4 = std::integral_constant<int, 4>;
-    if (use_lds) {
-        if (moves <= 64) launch(T{}, S1{});
-        else if (moves <= 128) launch(T{}, S2{});
-        else launch(T{}, S4{});
+    if (lookup) {
+        uint2 *tab = c.cs.get<uint2>(6, (size_t)c.nua * nwords);
+        int32_t *flag = c.cs.get<int32_t>(7, 3 * ncand + 1);
+        int32_t *fpos = flag + ncand, *tiles = fpos + ncand, *ntiles = tiles + ncand;
+        HQ_CHECK(hipMemsetAsync(tab, 0, sizeof(uint2) * (size_t)c.nua * nwords, s));
+        hipLaunchKernelGGL(k_pt2_bits, dim3(grid_for(c.ndet, 256)), dim3(256), 0, s, c.ndet, c.aidx.p, c.bidx.p,
+                           nwords, tab);
+        HQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_pt2_ranks, dim3(grid_for((int64_t)c.nua * 64, 256)), dim3(256), 0, s, c.nua, nwords, tab);
+        HQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_pt2_tile_flags, dim3(grid_for(ncand, 256)), dim3(256), 0, s, keys, ncand, c.norb, flag);
+        HQ_LAUNCH_CHECK();
+        exclusive_scan_i32(s, flag, fpos, ncand, c.work);
+        hipLaunchKernelGGL(k_pt2_tile_list, dim3(grid_for(ncand, 256)), dim3(256), 0, s, flag, fpos, ncand, tiles,
+                           ntiles);
+        HQ_LAUNCH_CHECK();
+        if (use_lds) launch(T{}, S1{}, F{});
+        else launch(F{}, S1{}, F{});
+        const dim3 lg((unsigned)std::min<int64_t>((int64_t)cus * 2, ncand)), lb(PT_NT);
+        if (moves_b <= 64) hipLaunchKernelGGL(k_pt2_links<1>, lg, lb, 0, s, pa, keys, order, tiles, ntiles, nwords, tab);
+        else if (moves_b <= 128)
+            hipLaunchKernelGGL(k_pt2_links<2>, lg, lb, 0, s, pa, keys, order, tiles, ntiles, nwords, tab);
+        else hipLaunchKernelGGL(k_pt2_links<4>, lg, lb, 0, s, pa, keys, order, tiles, ntiles, nwords, tab);
+    } else if (use_lds) {
+        if (moves <= 64) launch(T{}, S1{}, T{});
+        else if (moves <= 128) launch(T{}, S2{}, T{});
+        else launch(T{}, S4{}, T{});
     } else {
-        if (moves <= 64) launch(F{}, S1{});
-        else if (moves <= 128) launch(F{}, S2{});
-        else launch(F{}, S4{});
+        if (moves <= 64) launch(F{}, S1{}, T{});
+        else if (moves <= 128) launch(F{}, S2{}, T{});
+        else launch(F{}, S4{}, T{});
     }
     HQ_LAUNCH_CHECK();
     unsigned hbad = 0;

@@ -69,3 +69,60 @@ def test_rdm12_either_side_of_the_table_rule(norb, na, nb, ndet):
         # sums of at most ndet * couplings products of two coefficients
         assert np.abs(d1 - r1).max() <= 1e-12 * max(1.0, np.abs(r1).max())
         assert np.abs(d2 - r2).max() <= 1e-12 * max(1.0, np.abs(r2).max())
+
+
+def _pt2_set(kind):
+    rng = np.random.default_rng(21)
+    if kind == "many strings":   # more distinct beta strings than the member tables hold: the scan
+        norb, na, nb = 18, 9, 9
+        a, b = W.sample_determinants(norb, na, nb, 60_000, 0.4, 1.0, 22)
+        assert len(np.unique(b)) > 32 * 1024
+    elif kind == "large group":  # one alpha group of 3,432 members, next to small ones
+        norb, na, nb = 14, 7, 7
+        sb = W.fci_strings(norb, nb)
+        ra, rb = W.sample_determinants(norb, na, nb, 1500, 0.4, 0.0, 23)
+        keep = ra != (1 << na) - 1
+        a = np.concatenate([np.full(len(sb), (1 << na) - 1, dtype=np.uint64), ra[keep]])
+        b = np.concatenate([sb, rb[keep]])
+    else:                        # more than 64 moves per spin
+        norb, na, nb = 20, 5, 10
+        a, b = W.sample_determinants(norb, na, nb, 3000, 0.3, 0.0, 24)
+    order = rng.permutation(len(a))
+    return norb, na, nb, a[order], b[order]
+
+
+@pytest.mark.parametrize("kind", ["many strings", "large group", "many moves"])
+def test_pt2_table_and_scan_paths(kind):
+    """Candidates in runs of 1, 63, 64, 65 and more that share an alpha string
+    (tile edges), members and repeats among them, in shuffled order; a malformed
+    candidate gives NaN for itself only."""
+    norb, na, nb, a, b = _pt2_set(kind)
+    log(f"pt2 {kind}: norb {norb}, {len(a)} determinants")
+    ints = W.gen_integrals(norb, 2, -2.0, -0.5, 88)
+    s = solver_for(ints, a, b, na, nb)
+    o = oracle_for(ints, a, b, na, nb)
+    rng = np.random.default_rng(25)
+    c = rng.standard_normal(len(a))
+    ref = np.uint64((1 << na) - 1)
+    single = ref ^ np.uint64(1) ^ np.uint64(1 << na)
+    far = ref ^ np.uint64(3) ^ np.uint64(3 << na)
+    betas = np.unique(b)
+    ca, cb = [a[:20]], [b[:20]]
+    for alpha, n in ((ref, 65), (single, 64), (far, 63), (np.uint64(ref << np.uint64(norb - na)), 1), (a[3], 130)):
+        ca.append(np.full(n, alpha, dtype=np.uint64))
+        cb.append(betas[rng.integers(0, len(betas), n)])
+    ca, cb = np.concatenate(ca), np.concatenate(cb)
+    order = rng.permutation(len(ca))
+    ca, cb = ca[order], cb[order]
+    e0 = float(o.pt2(c, 0.0, a[:200], b[:200])[1].min()) - 0.5
+    cd = torch.from_numpy(c).cuda()
+    num, hxx, score = (t.cpu().numpy() for t in s.pt2(cd, e0, ca, cb))
+    rn, rh, rs, absnum = o.pt2(c, e0, ca, cb, with_scale=True)
+    assert np.all(np.abs(num - rn) <= 1e-12 * absnum + 1e-300)
+    assert np.all(np.abs(hxx - rh) <= 1e-12 * np.abs(rh).max())
+    assert np.array_equal(score, num * num / np.abs(e0 - hxx))
+    bad_a = ca.copy()
+    bad_a[7] ^= np.uint64(1 << (norb - 1)) if not (int(bad_a[7]) >> (norb - 1)) & 1 else np.uint64(1)
+    with pytest.raises(hq.HinqsError) as ei:
+        s.pt2(cd, e0, bad_a, cb)
+    assert ei.value.name == "BAD_OCCUPATION"
