@@ -6,7 +6,8 @@ import torch
 
 import paper_2606_26760_amd as hq
 import workloads as W
-from tests.gpu_helpers import log, oracle_for, oracle_rows_as_tuples, row_bound, solver_for
+from tests.gpu_helpers import (gpu_rows_as_tuples, log, oracle_for, oracle_rows_as_tuples, row_bound,
+                               solver_for)
 
 pytestmark = pytest.mark.gpu
 
@@ -126,3 +127,51 @@ def test_pt2_table_and_scan_paths(kind):
     with pytest.raises(hq.HinqsError) as ei:
         s.pt2(cd, e0, bad_a, cb)
     assert ei.value.name == "BAD_OCCUPATION"
+
+
+@pytest.mark.parametrize("per_lane", [False, True])
+@pytest.mark.parametrize("ndet", [1, 2, 31, 33, 63, 64, 65, 255, 1025])
+def test_couplings_both_enumerators(ndet, per_lane, monkeypatch):
+    """One wave per row and one row per lane (asked for through its group
+    lookup limit) list the same couplings as the oracle, at row counts around a
+    wave, a scan step and a workgroup, with groups of one row to whole ones."""
+    if per_lane:
+        monkeypatch.setenv("HINQS_CONNECT_LOOKUP_MIN", "1000000")
+    log(f"couplings of {ndet} rows, per lane {per_lane}")
+    ints = W.gen_integrals(9, 3, -2.0, -0.5, 31)
+    a, b = W.sample_determinants(9, 4, 5, ndet, 0.6, 0.2, 32 + ndet)
+    s = solver_for(ints, a, b, 4, 5)
+    o = oracle_for(ints, a, b, 4, 5)
+    rows = np.arange(ndet)
+    ref, _ = oracle_rows_as_tuples(o, rows)
+    got = gpu_rows_as_tuples(s, rows)
+    for i in rows:
+        assert got[int(i)] == ref[int(i)], i
+
+
+@pytest.mark.parametrize("ndet", [65_536, 65_537])
+def test_sigma_either_side_of_the_enumerator_rule(ndet):
+    ints, a, b, cfg = W.config_inputs(3, ndet=ndet)
+    log(f"couplings and sigma at {ndet} rows")
+    s = solver_for(ints, a, b, cfg.na, cfg.nb)
+    o = oracle_for(ints, a, b, cfg.na, cfg.nb)
+    rows = np.random.default_rng(3).choice(ndet, 200, replace=False)
+    X = W.random_block(ndet, 2, 4)
+    _, r = oracle_rows_as_tuples(o, rows)
+    err = np.abs(s.sigma(torch.from_numpy(X).cuda()).cpu().numpy()[rows] - o.sigma_rows(X, rows))
+    assert np.all(err <= 1e-12 * row_bound(r, X, 2) + 1e-300)
+    rowptr = s.connectivity()[0].cpu().numpy()
+    assert np.array_equal(np.diff(rowptr)[rows], np.diff(r["rowptr"]) - 1)
+
+
+@pytest.mark.parametrize("n", [2, 511, 513, 8192, 8193, 70_001, (1 << 23) + 5])
+def test_ranking_at_the_sizes_of_the_sorts(n):
+    """One workgroup in LDS, small tiles, large tiles: stable, ties by index."""
+    log(f"top_k of {n} values")
+    v = torch.from_numpy(np.random.default_rng(n).integers(-40, 40, n).astype(np.float64)).cuda()
+    v[n // 2:] *= 1.5
+    ints, a, b, cfg = W.config_inputs(0)
+    s = solver_for(ints, a, b, cfg.na, cfg.nb)
+    for largest in (False, True):
+        ref = torch.sort(v, stable=True, descending=largest).indices.int()
+        assert torch.equal(s.top_k(v, n, largest=largest), ref)
