@@ -56,7 +56,7 @@ struct BatchState {
     // kernels, threads of the Rayleigh-Ritz kernel), per block-size index;
     // tuned[k] says the shape was timed for the current instances
     struct Shape {
-        int chunk = 2048;
+        int chunk = 0;  // 0: by the number of rows (default_chunk)
         int rr_threads = 1024;
         double ms_per_it = 0.0;
     };
@@ -98,130 +98,235 @@ struct BDev {
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
+// x of another lane of the wave by a DPP control; lanes without a source keep their own.
+template <int CTRL>
+__device__ double lane_of(double x) {
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+}
+constexpr int DPP_NEXT = 0x130, DPP_PREV = 0x138, DPP_ROW_ROR = 0x120;
+
+// Sum over one wave, the same value in every lane: rotations within rows of 16
+// lanes, then one lane of each row (a shuffle through LDS per step is 5x the latency).
+__device__ double wave_sum(double v) {
+    v += lane_of<DPP_ROW_ROR + 8>(v);
+    v += lane_of<DPP_ROW_ROR + 4>(v);
+    v += lane_of<DPP_ROW_ROR + 2>(v);
+    v += lane_of<DPP_ROW_ROR + 1>(v);
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    double s[4];
+    for (int q = 0; q < 4; ++q)
+        s[q] = __hiloint2double(__builtin_amdgcn_readlane(hi, 16 * q), __builtin_amdgcn_readlane(lo, 16 * q));
+    return (s[0] + s[1]) + (s[2] + s[3]);
+}
+
 // Sum over a workgroup of B threads; every thread receives the same value.
 template <int B = NT>
 __device__ double block_sum(double v, double *red) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    v = wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double s = 0.0;
+#pragma unroll
     for (int w = 0; w < B / 64; ++w) s += red[w];
     return s;
 }
 
-// Sum over one wave, broadcast from lane 0 so every lane holds the same value.
-__device__ double wave_sum(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return __shfl(v, 0);
+// 1 / sqrt(x), x in [1/4, 8]: the hardware's estimate (good to 2^-23) and one
+// step of third order.
+__device__ double inv_sqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// The rotation (c, s) that diagonalises [[app, apq], [apq, aqq]] by the smaller
+// angle.  From cos 2t = |d| / r and sin 2t = h / r with d = aqq - app, h = 2 apq,
+// r^2 = d^2 + h^2 (both scaled into [-1, 1], so nothing over- or underflows):
+// c^2 = (1 + |d| / r) / 2, s = h / (2 r c), two inverse roots and no division,
+// which is a third of the dependent instructions that t = 1 / (|th| + sqrt(th^2 + 1))
+// takes; every round of the eigensolver waits for them.
+__device__ void jacobi_rotation(double app, double aqq, double apq, double &c, double &s) {
+    double d = aqq - app, h = 2.0 * apq;
+    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(h)));
+    d = ldexp(d, ex);
+    h = ldexp(h, ex);
+    const double w = inv_sqrt(fma(d, d, h * h));
+    const double c2 = fma(0.5 * fabs(d), w, 0.5);
+    const double ic = inv_sqrt(c2);
+    c = c2 * ic;
+    s = (d >= 0.0 ? 0.5 : -0.5) * h * w * ic;
+}
+
+// Elements of the scratch that block_jacobi takes: two buffers of the upper
+// 2 x 2 blocks and the rotations.
+constexpr int jacobi_scratch(int maxn) {
+    return 2 * 4 * ((maxn + 1) / 2 * ((maxn + 1) / 2 + 1) / 2) + 2 * ((maxn + 1) / 2);
 }
 
 // Parallel cyclic Jacobi eigensolver for the symmetric n x n matrix A (LDS,
 // leading dimension LD, n <= MAXN <= 64).  Rotations follow a round-robin
-// pairing: each round pairs every index once, the n/2 disjoint rotations are
-// computed from the current matrix and applied together (columns, then
-// rows); each thread steps through its elements' (pair, index) positions
-// by a fixed stride, so a round costs only LDS traffic and one rotation per
-// pair.  Sweeps stop when the off-diagonal mass falls below 1e-32 of the
-// Frobenius norm.  On return A's diagonal holds the eigenvalues and row j of
-// ZT the eigenvector belonging to A[j][j].
+// pairing: each round pairs every index once (an odd n gets a zero row and
+// column), and the disjoint rotations, computed from the current matrix, are
+// applied together.  The matrix is kept as the 2 x 2 blocks of its pairs' upper
+// triangle, which depend on two rotations each: a task reads its block at a fixed
+// place and writes the rotated elements where the next round's pairing has them,
+// into the other of two buffers, so no addresses are computed between rounds.
+// Eigenvector rows stay in registers, a half wave per column with lane k holding
+// pair k, and move to the next pairing by one lane.  A round is two barriers and
+// the chain of a rotation (first wave) and a block: 0.52 / 0.52 / 0.62 us at
+// n = 16 / 32 / 48 with 1,024 threads; the same blocks at addresses taken from the
+// pairing, eigenvector rows in LDS, took 0.85 / 0.87 / 1.10 us.
+// Sweeps stop when the off-diagonal mass falls below 1e-32 of the Frobenius norm.
+// On return A's diagonal holds the eigenvalues and row j of ZT the eigenvector
+// belonging to A[j][j]; scratch: jacobi_scratch(MAXN) elements, 16-byte aligned.
 template <int LD, int MAXN, int B = NT>
-__device__ void block_jacobi(int n, double *A, double *ZT, int *pp, int *pq, double *pc, double *ps,
-                             double *red) {
-    constexpr int MAXE = ((MAXN + 1) / 2 * MAXN + B - 1) / B;  // elements per thread and phase
+__device__ void block_jacobi(int n, double *A, double *ZT, double *scratch, double *red) {
+    constexpr int MAXP = (MAXN + 1) / 2, W = B - 64;           // W: threads past the first wave
+    constexpr int NBLK = MAXP * (MAXP + 1) / 2;
+    constexpr int MAXB = (NBLK + W - 1) / W;                   // blocks per thread
+    constexpr int MAXZ = (2 * MAXP + W / 32 - 1) / (W / 32);   // columns per half wave
     const int tid = threadIdx.x;
-    for (int e = tid; e < n * n; e += B) {
-        const int i = e / n, j = e % n;
-        ZT[i * LD + j] = i == j ? 1.0 : 0.0;
-    }
-    double f = 0.0;
-    for (int e = tid; e < n * n; e += B) {
-        const double x = A[(e / n) * LD + e % n];
-        f += x * x;
-    }
-    const double fro = block_sum<B>(f, red);
-    if (n < 2) return;
     const int ne = n + (n & 1), np = ne / 2, nr = ne - 1;
-    // element e = tid + u B of a phase: column phase (pair e % np, row e / np,
-    // so neighbouring threads hit different banks), row phase (pair e / n,
-    // column e % n, contiguous rows); both advance by B per slot
-    const int ck0 = tid % np, cj0 = tid / np, cstep_k = B % np, cstep_j = B / np;
-    const int rj0 = tid % n, rk0 = tid / n, rstep_j = B % n, rstep_k = B / n;
-    for (int sweep = 0; sweep < 50; ++sweep) {
-        double o = 0.0;
-        for (int e = tid; e < n * n; e += B) {
-            const int i = e / n, j = e % n;
-            if (i < j) o += A[i * LD + j] * A[i * LD + j];
+    if (n < 2) {
+        if (tid == 0 && n == 1) ZT[0] = 1.0;
+        return;
+    }
+    double *cur = scratch, *nxt = scratch + 4 * NBLK;
+    double2 *rot = (double2 *)(scratch + 8 * NBLK);
+    // slots 2 k and 2 k + 1 are pair k; index at a slot in a sweep's first round
+    auto index_of = [&](int sl) {
+        const int k = sl >> 1;
+        return (sl & 1) == 0 ? k : (k == 0 ? ne - 1 : nr - k);
+    };
+    // slot in the next round: first members move down, second ones up; slot 1 stays
+    auto moved = [&](int sl) {
+        const int k = sl >> 1;
+        if (np == 1 || sl == 1) return sl;
+        if ((sl & 1) == 0) return k == 0 ? 3 : sl - 2;
+        return k == np - 1 ? sl - 1 : sl + 2;
+    };
+    auto element_of = [&](int i, int j) {  // where a block buffer has the element of slots i, j
+        const int lo = min(i, j), hi = max(i, j), k = lo >> 1, l = hi >> 1;
+        return (l * (l + 1) / 2 + k) * 4 + (lo & 1) * 2 + (hi & 1);
+    };
+    const bool lead = tid < 64;
+    const int nblk = np * (np + 1) / 2;
+    bool act[MAXB], own[MAXB];
+    int bk[MAXB], bl[MAXB], to[MAXB][4];
+    double x[MAXB][4];
+#pragma unroll
+    for (int u = 0; u < MAXB; ++u) {
+        const int t = max(tid - 64, 0) + u * W;
+        int l = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+        while (l * (l + 1) / 2 > t) --l;
+        while ((l + 1) * (l + 2) / 2 <= t) ++l;
+        const int k = t - l * (l + 1) / 2;
+        act[u] = !lead && t < nblk;
+        own[u] = k == l;
+        bk[u] = k;
+        bl[u] = l;
+        if (!act[u]) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            int si = 2 * k + (e >> 1), sj = 2 * l + (e & 1);
+            const int i = index_of(si), j = index_of(sj);
+            cur[4 * t + e] = i < n && j < n ? A[i * LD + j] : 0.0;
+            if (own[u] && e == 2) si = 2 * k, sj = 2 * k + 1;  // the pair's own element is kept once
+            to[u][e] = element_of(moved(si), moved(sj));
         }
+    }
+    // columns zc, zc + W / 32, ... of ZT; lane k of the half wave holds pair k
+    const int zc = (tid - 64) >> 5, zk = tid & 31;
+    double zt[MAXZ], zb[MAXZ];
+#pragma unroll
+    for (int u = 0; u < MAXZ; ++u) {
+        const int col = zc + u * (W / 32);
+        zt[u] = index_of(2 * zk) == col ? 1.0 : 0.0;
+        zb[u] = index_of(2 * zk + 1) == col ? 1.0 : 0.0;
+    }
+    double fro = 0.0;
+    for (int sweep = 0; sweep < 50; ++sweep) {
+        double o = 0.0, dg = 0.0;
+#pragma unroll
+        for (int u = 0; u < MAXB; ++u)
+            if (act[u]) {
+                const double *c = cur + 4 * (tid - 64 + u * W);
+                const double a = c[0] * c[0], b = c[1] * c[1], d = c[2] * c[2], e = c[3] * c[3];
+                o += 2.0 * (own[u] ? b : (a + b) + (d + e));
+                dg += own[u] ? a + e : 0.0;
+            }
         const double off = block_sum<B>(o, red);
+        if (sweep == 0) fro = off + block_sum<B>(dg, red);
         if (off == 0.0 || off <= 1e-32 * fro) break;
         for (int r = 0; r < nr; ++r) {
-            if (tid < np) {
-                int a, b;
-                if (tid == 0) {
-                    a = r;
-                    b = ne - 1;
-                } else {
-                    a = r + tid;
-                    if (a >= nr) a -= nr;
-                    b = r - tid;
-                    if (b < 0) b += nr;
+            if (lead) {
+                if (tid < np) {
+                    const double *c = cur + (tid * (tid + 1) / 2 + tid) * 4;
+                    const double app = c[0], apq = c[1], aqq = c[3];
+                    double cs = 1.0, sn = 0.0;
+                    if (apq != 0.0) jacobi_rotation(app, aqq, apq, cs, sn);
+                    rot[tid] = make_double2(cs, sn);
                 }
-                const int p = min(a, b), q = max(a, b);
-                double c = 1.0, s = 0.0;
-                if (q < n) {
-                    const double apq = A[p * LD + q];
-                    if (apq != 0.0) {
-                        const double th = (A[q * LD + q] - A[p * LD + p]) / (2.0 * apq);
-                        const double t = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-                        c = 1.0 / sqrt(t * t + 1.0);
-                        s = t * c;
+            } else {
+#pragma unroll
+                for (int u = 0; u < MAXB; ++u)
+                    if (act[u]) {
+                        const double2 *c = (const double2 *)cur + 2 * (tid - 64 + u * W);
+                        const double2 r0 = c[0], r1 = c[1];
+                        x[u][0] = r0.x;
+                        x[u][1] = r0.y;
+                        x[u][2] = own[u] ? r0.y : r1.x;
+                        x[u][3] = r1.y;
+                    }
+            }
+            __syncthreads();
+            if (!lead) {
+#pragma unroll
+                for (int u = 0; u < MAXB; ++u)
+                    if (act[u]) {
+                        const double2 rk = rot[bk[u]], rl = rot[bl[u]];
+                        const double ya = rl.x * x[u][0] - rl.y * x[u][1], yb = rl.y * x[u][0] + rl.x * x[u][1];
+                        const double yc = rl.x * x[u][2] - rl.y * x[u][3], yd = rl.y * x[u][2] + rl.x * x[u][3];
+                        nxt[to[u][0]] = rk.x * ya - rk.y * yc;
+                        nxt[to[u][1]] = own[u] ? 0.0 : rk.x * yb - rk.y * yd;
+                        nxt[to[u][2]] = own[u] ? 0.0 : rk.y * ya + rk.x * yc;
+                        nxt[to[u][3]] = rk.y * yb + rk.x * yd;
+                    }
+                const double2 rk = rot[min(zk, np - 1)];
+#pragma unroll
+                for (int u = 0; u < MAXZ; ++u) {
+                    if (zc + u * (W / 32) >= ne) break;
+                    const double p = rk.x * zt[u] - rk.y * zb[u], q = rk.y * zt[u] + rk.x * zb[u];
+                    const double up = lane_of<DPP_PREV>(zk == 0 ? p : q), down = lane_of<DPP_NEXT>(p);
+                    zt[u] = zk == np - 1 ? q : down;
+                    zb[u] = zk == 0 ? q : up;
+                    if (np == 1) {
+                        zt[u] = p;
+                        zb[u] = q;
                     }
                 }
-                pp[tid] = p;
-                pq[tid] = (q < n && s != 0.0) ? q : -1;  // -1: nothing to rotate
-                pc[tid] = c;
-                ps[tid] = s;
             }
-            __syncthreads();
-            for (int u = 0, k = ck0, j = cj0; u < MAXE && j < n; ++u) {  // columns p, q
-                const int q = pq[k];
-                if (q >= 0) {
-                    const int o1 = j * LD + pp[k], o2 = j * LD + q;
-                    const double c = pc[k], s = ps[k];
-                    const double x1 = A[o1], x2 = A[o2];
-                    A[o1] = c * x1 - s * x2;
-                    A[o2] = s * x1 + c * x2;
-                }
-                k += cstep_k;
-                j += cstep_j;
-                if (k >= np) {
-                    k -= np;
-                    ++j;
-                }
-            }
-            __syncthreads();
-            for (int u = 0, k = rk0, j = rj0; u < MAXE && k < np; ++u) {  // rows p, q and eigenvector rows
-                const int q = pq[k];
-                if (q >= 0) {
-                    const int o1 = pp[k] * LD + j, o2 = q * LD + j;
-                    const double c = pc[k], s = ps[k];
-                    const double x1 = A[o1], x2 = A[o2], z1 = ZT[o1], z2 = ZT[o2];
-                    A[o1] = c * x1 - s * x2;
-                    A[o2] = s * x1 + c * x2;
-                    ZT[o1] = c * z1 - s * z2;
-                    ZT[o2] = s * z1 + c * z2;
-                }
-                j += rstep_j;
-                k += rstep_k;
-                if (j >= n) {
-                    j -= n;
-                    ++k;
-                }
-            }
+            double *t = cur;
+            cur = nxt;
+            nxt = t;
             __syncthreads();
         }
     }
+    if (tid < np)
+        for (int h = 0; h < 2; ++h) {
+            const int i = index_of(2 * tid + h);
+            if (i < n) A[i * LD + i] = cur[(tid * (tid + 1) / 2 + tid) * 4 + 3 * h];
+        }
+    if (!lead && zk < np)
+#pragma unroll
+        for (int u = 0; u < MAXZ; ++u) {
+            const int col = zc + u * (W / 32), i = index_of(2 * zk), j = index_of(2 * zk + 1);
+            if (col >= n) break;
+            if (i < n) ZT[i * LD + col] = zt[u];
+            if (j < n) ZT[j * LD + col] = zb[u];
+        }
 }
 
 // --------------------------------------------------------- chunked dense kernels
@@ -434,13 +539,15 @@ __device__ inline double chunk_sum(const double *__restrict__ part, int stride, 
 
 constexpr int RR_LD = MS + 1;
 // Threads of the Rayleigh-Ritz kernel (RR_NT in {256, 512, 1024}, chosen by
-// the batch tuner): its Jacobi rounds are bound by LDS traffic and latency,
-// so a full 16-wave workgroup per instance usually beats fewer waves despite
-// the barriers (at m = 48: 1024 threads 0.55 ms, 256 threads 0.82 ms, one
-// wave 3.0 ms).
+// the batch tuner): its Jacobi rounds are bound by latency, and a full 16-wave
+// workgroup has one block or column per thread, so it usually beats fewer waves
+// despite the barriers (eigensolver at m = 48: 1024 / 512 / 256 threads
+// 0.20 / 0.24 / 0.33 ms).  Averaged over the subspace sizes 8..48 of a solve and
+// its restarts a step takes 0.15 ms, with the eigensolver and the Gram-Schmidt
+// that went before 0.29 ms.
 constexpr size_t rr_lds_bytes(int nt) {
-    return sizeof(double) * (2 * MS * RR_LD + 2 * MS * KB + 2 * KB * KB + KB + nt / 64 + MS) +
-           sizeof(int) * (2 * MS + 2 * MS);
+    return sizeof(double) * (2 * MS * RR_LD + 2 * MS * KB + 2 * KB * KB + KB + nt / 64 + jacobi_scratch(MS)) +
+           sizeof(int) * 2 * MS;
 }
 
 // Rayleigh-Ritz of instance b at subspace size m: the last K columns of
@@ -461,11 +568,8 @@ __global__ __launch_bounds__(RR_NT) void k_brr(BDev st, int m, int restart, cons
     double *Y2 = Yn + MS * KB;             // 2KK x KK
     double *th = Y2 + 2 * KB * KB;         // KK
     double *red = th + KB;                 // RR_NT/64
-    double *pc = red + RR_NT / 64;            // MS/2
-    double *ps = pc + MS / 2;              // MS/2
-    int *pp = (int *)(ps + MS / 2);        // MS/2
-    int *pq = pp + MS / 2;                 // MS/2
-    int *vidx = pq + MS / 2;               // MS
+    double *jac = red + RR_NT / 64;        // eigensolver scratch
+    int *vidx = (int *)(jac + jacobi_scratch(MS));  // MS
     int *misc = vidx + MS;                 // [0] nv, [1] kept mask
     const int tid = threadIdx.x;
     const int base = m - KK;
@@ -492,7 +596,7 @@ __global__ __launch_bounds__(RR_NT) void k_brr(BDev st, int m, int restart, cons
         A[i * RR_LD + j] = gval(vidx[i], vidx[j]);
     }
     __syncthreads();
-    block_jacobi<RR_LD, MS, RR_NT>(nv, A, ZT, pp, pq, pc, ps, red);
+    block_jacobi<RR_LD, MS, RR_NT>(nv, A, ZT, jac, red);
     __syncthreads();
     for (int e = tid; e < MS * KK; e += RR_NT) Yn[e] = 0.0;
     if (tid < KK) th[tid] = 0.0;
@@ -535,30 +639,41 @@ __global__ __launch_bounds__(RR_NT) void k_brr(BDev st, int m, int restart, cons
         const int r = e / m, c = e % m;
         Gs[r * RR_LD + c] = gval(r, c);
     }
-    if (tid < 64) {  // modified Gram-Schmidt, twice, by wave 0; lane a owns row a
-        const int a = tid;
-        unsigned kept = 0u;
-        for (int c = 0; c < Q2; ++c) {
-            double v = 0.0;
-            if (a < m) v = c < KK ? Yn[a * KK + c] : Yb[a * KB + (c - KK)];
-            const double n0 = sqrt(wave_sum(v * v));
-            bool keep = n0 > 0.0;
-            if (keep) {
-                for (int pass = 0; pass < 2; ++pass)
-                    for (int u = 0; u < c; ++u) {
-                        if (!((kept >> u) & 1u)) continue;
-                        const double qu = a < m ? Qs[a * Q2 + u] : 0.0;
-                        const double d = wave_sum(qu * v);
-                        v -= d * qu;
-                    }
-                const double n1 = sqrt(wave_sum(v * v));
-                keep = n1 > 1e-8 * n0;
-                if (keep) v /= n1;
-            }
-            if (a < m) Qs[a * Q2 + c] = keep ? v : 0.0;
-            if (keep) kept |= 1u << c;
+    // Modified Gram-Schmidt, twice, the columns dealt out over the waves with one
+    // row per lane: once a column is final every later one takes its part out, so
+    // the chain is two sums over a wave and a barrier per column (one wave that took
+    // a column's products one after another needed 115 us for 2 x 8 columns).
+    if (tid == 0) misc[1] = 0;
+    {
+        constexpr int NW = RR_NT / 64, CW = (Q2 + NW - 1) / NW;
+        const int wave = tid >> 6, a = tid & 63;
+        double v[CW], n0[CW];
+#pragma unroll
+        for (int u = 0; u < CW; ++u) {
+            const int c = wave + u * NW;
+            v[u] = 0.0;
+            if (a < m && c < Q2) v[u] = c < KK ? Yn[a * KK + c] : Yb[a * KB + (c - KK)];
+            n0[u] = sqrt(wave_sum(v[u] * v[u]));
         }
-        if (a == 0) misc[1] = (int)kept;
+        for (int pass = 0; pass < 2; ++pass) {
+            __syncthreads();
+            for (int c = 0; c < Q2; ++c) {
+#pragma unroll
+                for (int u = 0; u < CW; ++u)
+                    if (wave + u * NW == c) {
+                        const double n1 = sqrt(wave_sum(v[u] * v[u]));
+                        const bool keep = pass == 0 ? n0[u] > 0.0 && n1 > 1e-8 * n0[u] : n1 > 0.0;
+                        v[u] = keep ? v[u] / n1 : 0.0;
+                        if (a < m) Qs[a * Q2 + c] = v[u];
+                        if (keep && pass == 1 && a == 0) misc[1] |= (int)(1u << c);
+                    }
+                __syncthreads();
+                const double q = a < m ? Qs[a * Q2 + c] : 0.0;
+#pragma unroll
+                for (int u = 0; u < CW; ++u)
+                    if (wave + u * NW > c) v[u] -= wave_sum(q * v[u]) * q;
+            }
+        }
     }
     __syncthreads();
     const unsigned kept = (unsigned)misc[1];
@@ -668,8 +783,8 @@ __global__ __launch_bounds__(NT) void k_bpost_orth(BDev st, const int32_t *__res
     if (gate[b]) return;
     constexpr int LD = KK + 1;
     __shared__ double A[KK * LD], ZT[KK * LD], sc[KK], red[NT / 64];
-    __shared__ double pc[KK], ps[KK];
-    __shared__ int pp[KK], pq[KK], nk_s;
+    __shared__ __attribute__((aligned(16))) double jac[jacobi_scratch(KK)];
+    __shared__ int nk_s;
     const int tid = threadIdx.x;
     const int c0 = st.inst_chunk[b], c1 = st.inst_chunk[b + 1];
     if (tid < KK) sc[tid] = st.scl[b * KB + tid];
@@ -680,7 +795,7 @@ __global__ __launch_bounds__(NT) void k_bpost_orth(BDev st, const int32_t *__res
         A[i * LD + j] = sc[i] * sc[j] * 0.5 * (ZT[i * LD + j] + ZT[j * LD + i]);
     }
     __syncthreads();
-    block_jacobi<LD, KK>(KK, A, ZT, pp, pq, pc, ps, red);
+    block_jacobi<LD, KK>(KK, A, ZT, jac, red);
     __syncthreads();
     double *Zb = st.Z + (int64_t)b * KB * KB;
     for (int e = tid; e < KB * KB; e += NT) Zb[e] = 0.0;
@@ -1024,6 +1139,15 @@ struct Resources {  // released on every exit path
     }
 };
 
+// Rows per chunk before tuning: one workgroup works on a chunk, so a batch of
+// fewer than 256 * 2,048 rows takes smaller ones and keeps about one per CU
+// (67,500 rows in 12 instances, solve of 58 iterations with chunks of 2048 / 1024 /
+// 512 / 256 / 128 / 64 rows: 40.7 / 34.0 / 30.9 / 30.1 / 30.4 / 32.6 ms; the sums over
+// chunks grow with their number).
+int default_chunk(int64_t rows) {
+    return (int)std::min<int64_t>(2048, std::max<int64_t>(128, (rows / 256 + 63) / 64 * 64));
+}
+
 template <int KK>
 int batch_solve_k(Ctx &c, BatchState &B, const hinqs_opts &o, int mmax, const BatchState::Shape &shape,
                   double *energies, double *coeffs, int *status, int *iters_out, hinqs_batch_stats *stats,
@@ -1037,7 +1161,7 @@ int batch_solve_k(Ctx &c, BatchState &B, const hinqs_opts &o, int mmax, const Ba
     const SigmaCfg scfg = sigma_config(B.g, KK, HINQS_FP64);
 
     // ---- chunk list: runs of at most CH rows of one instance
-    const int CH = std::max(64, env_or("HINQS_BATCH_CHUNK", shape.chunk));
+    const int CH = std::max(64, env_or("HINQS_BATCH_CHUNK", shape.chunk > 0 ? shape.chunk : default_chunk(N)));
     const int RRT = env_or("HINQS_BATCH_RR_THREADS", shape.rr_threads);
     if (RRT != 256 && RRT != 512 && RRT != 1024)
         throw Error(HINQS_E_INVALID_ARG, "Rayleigh-Ritz threads must be 256, 512 or 1024");

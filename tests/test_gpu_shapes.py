@@ -175,3 +175,29 @@ def test_ranking_at_the_sizes_of_the_sorts(n):
     for largest in (False, True):
         ref = torch.sort(v, stable=True, descending=largest).indices.int()
         assert torch.equal(s.top_k(v, n, largest=largest), ref)
+
+
+@pytest.mark.parametrize("block,max_space,threads", [(1, 3, "1024"), (1, 7, "256"), (2, 10, "512"), (4, 20, "256"),
+                                                     (8, 48, "1024"), (8, 56, "512"), (16, 64, "1024"),
+                                                     (16, 64, "256")])
+def test_batch_subspaces_of_every_size(block, max_space, threads, monkeypatch):
+    """Sets from the smallest that the subspace allows up to 301 rows together:
+    subspaces of odd and of even size, full ones with columns that drop out,
+    and chunks of fewer rows than a wave.  A dense eigenvalue lies within the residual's
+    norm (tol) of each value, which is at most the lowest diagonal element."""
+    monkeypatch.setenv("HINQS_BATCH_RR_THREADS", threads)
+    ints = W.gen_integrals(9, 3, -2.0, -0.5, 31)
+    s, ref = hq.Hinqs(), []
+    for n in sorted({max_space, max_space + 1, 31, 47, 64, 65, 129, 301}):
+        if n < max_space:
+            continue
+        a, b = W.sample_determinants(9, 4, 5, n, 0.4, 0.0, 32 + n)
+        s.batch_add(ints.h, ints.eri, ints.e_core, a, b, 4, 5)
+        o = oracle_for(ints, a, b, 4, 5)
+        ref.append((o.spectrum(n), o.diag().min()))
+    log(f"batch block {block}, max_space {max_space}, {threads} threads")
+    e, _, info = s.batch_lowest_eigenpair(block=block, max_space=max_space, tol=1e-9, max_iter=600)
+    assert info["converged"]
+    for x, (spectrum, dmin) in zip(e, ref):
+        slack = 1e-12 * np.abs(spectrum).max()
+        assert np.abs(spectrum - x).min() <= 1e-9 + slack and x <= dmin + slack, (x, spectrum[:4], dmin)
