@@ -372,7 +372,7 @@ struct Ctx {
     } cs;
     // Davidson workspace (basis, images, staging), kept between solves
     struct DavidsonWork {
-        DBuf<double> Vb, Wb, T, Wn, small, partial, nrm, argv, xfin, signbuf;
+        DBuf<double> Vb, Wb, T, Wn, small, partial, argv, xfin, signbuf;
         DBuf<float> X32, S32;
         DBuf<int32_t> guess_idx;
         DBuf<int64_t> argi;

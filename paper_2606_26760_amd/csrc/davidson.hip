@@ -10,7 +10,7 @@
 // the caches, and its output Wn is appended to W afterwards.
 //
 // Per iteration:
-//   Rayleigh-Ritz on G = V^T W         host Householder + implicit QL (cyclic
+//   Rayleigh-Ritz on G = V^T W         host Householder + implicit QL, lowest vectors (cyclic
 //                                      Jacobi if QL does not converge), m <= 96
 //   T = (W y - theta V y) / (theta - H_ii)   fused Ritz/residual/preconditioner
 //                                      (V y, W y on FP64 MFMA, like every
@@ -48,6 +48,64 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 constexpr int GRAM_BLOCK = 256;
 constexpr int GRAM_MAX_BLOCKS = 512;
 constexpr int GRAM_UNROLL = 4;
+// Workgroups of the tall kernels that leave a partial result each: four per CU
+// keep the loads in flight, and the sum over them stays short.
+constexpr int TALL_MAX_BLOCKS = 1024;
+
+// out[e] = sum_blk partial[blk][e], e < n: a workgroup sums RED_COLS neighbouring
+// elements, so a row of them is one segment of memory, over a fixed tree.  dev and
+// host (pinned memory) each take the result if they are set: the host reads it
+// after its wait for the stream, and no copy is launched for it.
+constexpr int RED_COLS = 8;
+__global__ __launch_bounds__(256) void k_reduce_partials(const double *__restrict__ partial, int nblk, int n,
+                                                         double *__restrict__ dev, double *__restrict__ host) {
+    __shared__ double red[256];
+    const int e = blockIdx.x * RED_COLS + threadIdx.x % RED_COLS;
+    constexpr int PARTS = 256 / RED_COLS, U = 4;
+    double acc[U] = {0.0, 0.0, 0.0, 0.0};
+    if (e < n)
+        for (int b = threadIdx.x / RED_COLS; b < nblk; b += PARTS * U)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int bb = b + u * PARTS;
+                acc[u] += bb < nblk ? partial[(int64_t)bb * n + e] : 0.0;
+            }
+    red[threadIdx.x] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    __syncthreads();
+    for (int w = 128; w >= RED_COLS; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x < RED_COLS && e < n) {
+        if (dev) dev[e] = red[threadIdx.x];
+        if (host) host[e] = red[threadIdx.x];
+    }
+}
+void launch_reduce(hipStream_t s, const double *partial, int nblk, int n, double *dev, double *host) {
+    hipLaunchKernelGGL(k_reduce_partials, dim3((n + RED_COLS - 1) / RED_COLS), dim3(256), 0, s, partial, nblk, n, dev,
+                       host);
+    HQ_LAUNCH_CHECK();
+}
+
+// Sum over the four waves of a workgroup of MT 16 x 16 products in MFMA
+// accumulators (element r of lane l: row 16 t + l / 16 + 4 r, column l % 16), to
+// out[a * nb + b] for a < ma, b < nb.
+template <int MT>
+__device__ void store_products(const dbl4 (&acc)[MT], int ma, int nb, double (&red)[4][MT][64][4],
+                               double *__restrict__ out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][t][lane][r] = acc[t][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < MT * 256; e += 256) {
+        const int t = e / 256, rem = e % 256, ln = rem / 4, r = rem % 4;
+        const int a = t * 16 + (ln >> 4) + 4 * r, b = ln & 15;
+        const double v = (red[0][t][ln][r] + red[1][t][ln][r]) + (red[2][t][ln][r] + red[3][t][ln][r]);
+        if (a < ma && b < nb) out[a * nb + b] = v;
+    }
+}
 
 // partial[blk][a][b] = sum over this block's rows of A(i, a) * B(i, b)
 // (a < ma <= 16*MT, b < nb <= 16).  MFMA operand layout (16x16x4 f64):
@@ -56,11 +114,9 @@ constexpr int GRAM_UNROLL = 4;
 // GRAM_UNROLL steps are issued before their MFMAs to keep loads in flight.
 template <int MT>
 __global__ __launch_bounds__(GRAM_BLOCK) void k_gram(int64_t nrows, Mat A, int ma, Mat B, int nb,
-                                                     int64_t rows_per_wave, double *__restrict__ partial,
-                                                     const int *__restrict__ gate) {
-    if (gate && *gate == 0) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t gw = (int64_t)blockIdx.x * (GRAM_BLOCK / 64) + wave;
+                                                     int64_t rows_per_wave, double *__restrict__ partial) {
+    const int lane = threadIdx.x & 63;
+    const int64_t gw = (int64_t)blockIdx.x * (GRAM_BLOCK / 64) + (threadIdx.x >> 6);
     const int64_t r0 = gw * rows_per_wave;
     const int64_t r1 = min(nrows, r0 + rows_per_wave);
     const int col = lane & 15, kk = lane >> 4;
@@ -88,38 +144,7 @@ __global__ __launch_bounds__(GRAM_BLOCK) void k_gram(int64_t nrows, Mat A, int m
                 acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][t], bv[u], acc[t], 0, 0, 0);
     }
     __shared__ double red[GRAM_BLOCK / 64][MT][64][4];
-#pragma unroll
-    for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave][t][lane][r] = acc[t][r];
-    __syncthreads();
-    for (int e = threadIdx.x; e < MT * 256; e += GRAM_BLOCK) {
-        const int t = e / 256, rem = e % 256, ln = rem / 4, r = rem % 4;
-        double s = 0.0;
-#pragma unroll
-        for (int w = 0; w < GRAM_BLOCK / 64; ++w) s += red[w][t][ln][r];
-        const int a = t * 16 + (ln >> 4) + 4 * r;
-        const int b = ln & 15;
-        if (a < ma && b < nb) partial[(int64_t)blockIdx.x * ma * nb + a * nb + b] = s;
-    }
-}
-
-// out[e] = sum_blk partial[blk][e]: one workgroup per output, fixed-shape tree.
-__global__ __launch_bounds__(256) void k_reduce_partials(const double *__restrict__ partial, int nblk,
-                                                         int n, double *__restrict__ out,
-                                                         const int *__restrict__ gate) {
-    if (gate && *gate == 0) return;
-    __shared__ double red[256];
-    const int e = blockIdx.x;
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += 256) s += partial[(int64_t)b * n + e];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[e] = red[0];
+    store_products(acc, ma, nb, red, partial + (int64_t)blockIdx.x * ma * nb);
 }
 
 // Fused Ritz vector, residual, norm and diagonal preconditioner for the
@@ -129,26 +154,36 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const double *__restric
 // operand layout of k_tsmm (16-row tiles, Y held in registers, m <= 4 STEPS);
 // the elementwise part works on the accumulators, whose element r of lane l is
 // row r0 + l/16 + 4r, column l%16.  partial[blk][c] = sum over the block's
-// rows of r_c^2 and partial[blk][KB + c] the same for T[:, c]^2.
-template <int KB, int STEPS>
-__global__ __launch_bounds__(256) void k_ritz(int64_t nrows, int m, Mat V, Mat W, const double *__restrict__ Y,
+// rows of r_c^2 and partial[blk][KB + c] the same for T[:, c]^2.  PROJ: after them
+// the block's part of V^T T (m x KB): an accumulator's T elements are the second
+// operand of that product as they lie, and V's tile, just read, comes again from
+// the caches in the first operand's order.  Bound by memory; at 1e6 rows and 8
+// roots, averaged over m = 8..48, 171 us with the product in it, 163 us without
+// and 65 us for a pass of its own.  Y lies in LDS in operand order: held in
+// registers it leaves two waves per SIMD instead of four (203 us).
+template <int KB, int STEPS, bool PROJ>
+__global__ __launch_bounds__(256, STEPS <= 12 ? 4 : 2) void k_ritz(int64_t nrows, int m, Mat V, Mat W, const double *__restrict__ Y,
                                               const double *__restrict__ theta, const double *__restrict__ diag,
                                               double floor_, int nroots, double *__restrict__ T,
                                               double *__restrict__ partial) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 15, kk = lane >> 4;
-    double yv[STEPS];
-#pragma unroll
-    for (int s = 0; s < STEPS; ++s) {
+    __shared__ double yv[STEPS][64];  // Y in operand order
+    for (int s = wave; s < STEPS; s += 4) {
         const int j = 4 * s + kk;
-        yv[s] = (j < m && col < KB) ? Y[j * KB + col] : 0.0;
+        yv[s][lane] = (j < m && col < KB) ? Y[j * KB + col] : 0.0;
     }
+    __syncthreads();
     const bool live = col < nroots;
     const double th = col < KB ? theta[col] : 0.0;
     const int nsteps = (m + 3) / 4;
     const int64_t ntiles = (nrows + 15) / 16;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     double rn2 = 0.0, tn2 = 0.0;
+    constexpr int MT = PROJ ? STEPS / 4 : 1;
+    dbl4 vt[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) vt[t] = dbl4{0.0, 0.0, 0.0, 0.0};
     for (int64_t tile = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; tile < ntiles; tile += nwaves) {
         const int64_t r0 = tile * 16, ra = r0 + col;
         const bool rok = ra < nrows;
@@ -166,10 +201,11 @@ __global__ __launch_bounds__(256) void k_ritz(int64_t nrows, int m, Mat V, Mat W
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                ax = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[u], yv[s0 + u], ax, 0, 0, 0);
-                aw = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[u], yv[s0 + u], aw, 0, 0, 0);
+                ax = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[u], yv[s0 + u][lane], ax, 0, 0, 0);
+                aw = __builtin_amdgcn_mfma_f64_16x16x4f64(wv[u], yv[s0 + u][lane], aw, 0, 0, 0);
             }
         }
+        double tv[4] = {0.0, 0.0, 0.0, 0.0};
         if (col < KB) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -184,10 +220,26 @@ __global__ __launch_bounds__(256) void k_ritz(int64_t nrows, int m, Mat V, Mat W
                     rn2 += res * res;
                     tn2 += t * t;
                 }
-                T[row * KB + col] = t;
+                T[row * KB + col] = tv[r] = t;
+            }
+        }
+        if constexpr (PROJ) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                if (16 * t >= m) break;
+                const int j = 16 * t + col;
+                double av[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t row = r0 + kk + 4 * r;
+                    av[r] = row < nrows && j < m ? *V.at(row, j) : 0.0;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) vt[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[r], tv[r], vt[t], 0, 0, 0);
             }
         }
     }
+    const int width = 2 * KB + (PROJ ? m * KB : 0);
     // block sums per column: the lanes of column c are c, c + 16, c + 32, c + 48 in every wave
     __shared__ double red[2][4][64];
     red[0][wave][lane] = rn2;
@@ -201,28 +253,12 @@ __global__ __launch_bounds__(256) void k_ritz(int64_t nrows, int m, Mat V, Mat W
                 rs += red[0][w][c + 16 * q];
                 ts += red[1][w][c + 16 * q];
             }
-        partial[(int64_t)blockIdx.x * 2 * KB + c] = rs;
-        partial[(int64_t)blockIdx.x * 2 * KB + KB + c] = ts;
+        partial[(int64_t)blockIdx.x * width + c] = rs;
+        partial[(int64_t)blockIdx.x * width + KB + c] = ts;
     }
-}
-
-// gate[0] = 1 when the projection T -= V (V^T T) needs a second pass: some
-// column q (tn2[q] = ||T_q||^2 > 0 before the first pass) kept less than half
-// of its norm, ||T_q||^2 - ||(V^T T)_q||^2 < ||T_q||^2 / 4 (NaN counts as
-// less); else 0.  C is the first pass's m x nc product V^T T; one wave.
-__global__ void k_proj_gate(const double *__restrict__ C, int m, int nc, const double *__restrict__ tn2,
-                            int *__restrict__ gate, int *__restrict__ count) {
-    const int q = threadIdx.x;
-    bool need = false;
-    if (q < nc && tn2[q] > 0.0) {
-        double c2 = 0.0;
-        for (int a = 0; a < m; ++a) c2 += C[a * nc + q] * C[a * nc + q];
-        need = !(tn2[q] - c2 >= 0.25 * tn2[q]);
-    }
-    const bool any = __ballot(need) != 0ull;
-    if (threadIdx.x == 0) {
-        *gate = any ? 1 : 0;
-        *count += any ? 1 : 0;  // second passes run in this solve
+    if constexpr (PROJ) {
+        __shared__ double redv[4][MT][64][4];
+        store_products(vt, m, KB, redv, partial + (int64_t)blockIdx.x * width + 2 * KB);
     }
 }
 
@@ -230,11 +266,13 @@ __global__ void k_proj_gate(const double *__restrict__ C, int m, int nc, const d
 // with FP64 MFMA (16x16x4): each wave takes 16-row tiles in turn; for k-step s lane l supplies
 // A(r0 + l%16, 4s + l/16), holds B[4s + l/16][16t + l%16] for every step in registers, and
 // receives rows r0 + l/16 + 4r of output column 16t + l%16.  A tile's rows are all read before
-// any is written, so Out may alias A.  B is m x nc row-major.
-template <int NT, int STEPS>
+// any is written, so Out may alias A.  B is m x nc row-major.  GRAM (nc <= 16):
+// partial[blk] = the block's part of Out^T Out (nc x nc), both operands of which
+// are the accumulators as they lie (1e6 rows, 8 columns: 80 us; a pass of its own
+// over Out added 39 us to 47).
+template <int NT, int STEPS, bool GRAM = false>
 __global__ __launch_bounds__(256) void k_tsmm(int64_t nrows, int m, Mat A, const double *__restrict__ B, int nc,
-                                              double alpha, double beta, Mat Out, const int *__restrict__ gate) {
-    if (gate && *gate == 0) return;
+                                              double alpha, double beta, Mat Out, double *__restrict__ partial) {
     const int lane = threadIdx.x & 63;
     const int col = lane & 15, kk = lane >> 4;
     double bv[STEPS][NT];
@@ -245,6 +283,7 @@ __global__ __launch_bounds__(256) void k_tsmm(int64_t nrows, int m, Mat A, const
             const int j = 4 * s + kk, c = 16 * t + col;
             bv[s][t] = (j < m && c < nc) ? B[j * nc + c] : 0.0;
         }
+    dbl4 oo[1] = {dbl4{0.0, 0.0, 0.0, 0.0}};
     const int nsteps = (m + 3) / 4;
     const int64_t ntiles = (nrows + 15) / 16;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -272,15 +311,25 @@ __global__ __launch_bounds__(256) void k_tsmm(int64_t nrows, int m, Mat A, const
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int c = 16 * t + col;
-            if (c >= nc) continue;
+            double ov[4] = {0.0, 0.0, 0.0, 0.0};
+            if (c < nc) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t row = r0 + kk + 4 * r;
-                if (row >= nrows) continue;
-                double *o = Out.at(row, c);
-                *o = (beta == 0.0 ? 0.0 : beta * *o) + alpha * acc[t][r];
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t row = r0 + kk + 4 * r;
+                    if (row >= nrows) continue;
+                    double *o = Out.at(row, c);
+                    *o = ov[r] = (beta == 0.0 ? 0.0 : beta * *o) + alpha * acc[t][r];
+                }
+            }
+            if constexpr (GRAM) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) oo[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ov[r], ov[r], oo[0], 0, 0, 0);
             }
         }
+    }
+    if constexpr (GRAM) {
+        __shared__ double red[4][1][64][4];
+        store_products(oo, nc, nc, red, partial + (int64_t)blockIdx.x * nc * nc);
     }
 }
 
@@ -438,7 +487,7 @@ int gram_blocks_for(int64_t nrows) {
 // G (ma x nb) = A^T B over nrows rows: MFMA partials per block, then a
 // fixed-order reduction.  partial must hold nblk * ma * nb doubles.
 void launch_gram(hipStream_t s, int64_t nrows, int nblk, Mat A, int ma, Mat B, int nb, double *partial,
-                 double *out, const int *gate = nullptr) {
+                 double *dev, double *host) {
     if (nb > 16 || ma > 96 || ma < 1 || nb < 1) throw Error(HINQS_E_UNSUPPORTED, "Gram block shape");
     int64_t waves = (int64_t)nblk * (GRAM_BLOCK / 64);
     int64_t rpw = (nrows + waves - 1) / waves;
@@ -446,17 +495,15 @@ void launch_gram(hipStream_t s, int64_t nrows, int nblk, Mat A, int ma, Mat B, i
     const int mt = (ma + 15) / 16;
     dim3 g(nblk), b(GRAM_BLOCK);
     switch (mt) {
-        case 1: hipLaunchKernelGGL(k_gram<1>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial, gate); break;
-        case 2: hipLaunchKernelGGL(k_gram<2>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial, gate); break;
-        case 3: hipLaunchKernelGGL(k_gram<3>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial, gate); break;
-        case 4: hipLaunchKernelGGL(k_gram<4>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial, gate); break;
-        case 5: hipLaunchKernelGGL(k_gram<5>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial, gate); break;
-        default: hipLaunchKernelGGL(k_gram<6>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial, gate); break;
+        case 1: hipLaunchKernelGGL(k_gram<1>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial); break;
+        case 2: hipLaunchKernelGGL(k_gram<2>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial); break;
+        case 3: hipLaunchKernelGGL(k_gram<3>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial); break;
+        case 4: hipLaunchKernelGGL(k_gram<4>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial); break;
+        case 5: hipLaunchKernelGGL(k_gram<5>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial); break;
+        default: hipLaunchKernelGGL(k_gram<6>, g, b, 0, s, nrows, A, ma, B, nb, rpw, partial); break;
     }
     HQ_LAUNCH_CHECK();
-    const int n = ma * nb;
-    hipLaunchKernelGGL(k_reduce_partials, dim3(n), dim3(256), 0, s, partial, nblk, n, out, gate);
-    HQ_LAUNCH_CHECK();
+    launch_reduce(s, partial, nblk, ma * nb, dev, host);
 }
 
 // Cyclic Jacobi eigendecomposition of a symmetric n x n matrix (row-major).
@@ -508,62 +555,92 @@ void jacobi_eig(int n, std::vector<double> A, std::vector<double> &w, std::vecto
     }
 }
 
-// Symmetric eigendecomposition by Householder reduction to tridiagonal form
-// followed by the implicit-shift QL iteration (the classic tridiagonal
-// eigenvalue method of Bowdler, Martin, Reinsch and Wilkinson), with the
-// transformations accumulated into the eigenvectors: O(n^3) with a small
-// constant, several times faster than cyclic Jacobi at the subspace sizes of
-// the solver.  Same outputs as jacobi_eig; returns false if an eigenvalue
+// Inner loops of the host eigensolver, built for the wide vectors of current
+// processors as well.
+#ifdef __HIP_DEVICE_COMPILE__
+#define HINQS_WIDE
+#else
+#define HINQS_WIDE __attribute__((target_clones("avx512f", "avx2", "default")))
+#endif
+// p[0:n) = sum_j x[j] a_j[0:n), rows a_j of a with leading dimension lda
+HINQS_WIDE void rows_combine(int n, int rows, const double *__restrict__ a, int lda,
+                             const double *__restrict__ x, double *__restrict__ p) {
+    for (int i = 0; i < n; ++i) p[i] = 0.0;
+    for (int j = 0; j < rows; ++j)
+        for (int i = 0; i < n; ++i) p[i] += x[j] * a[(size_t)j * lda + i];
+}
+// a -= v q^T + q v^T
+HINQS_WIDE void rank2_update(int n, double *__restrict__ a, int lda, const double *__restrict__ v,
+                             const double *__restrict__ q) {
+    for (int i = 0; i < n; ++i)
+        for (int j = 0; j < n; ++j) a[(size_t)i * lda + j] -= v[i] * q[j] + q[i] * v[j];
+}
+// rows z0, z1 <- c z0 + s z1, c z1 - s z0
+HINQS_WIDE void rotate_pair(int n, double c, double s, double *__restrict__ z0, double *__restrict__ z1) {
+    for (int q = 0; q < n; ++q) {
+        const double x = z0[q], y = z1[q];
+        z0[q] = c * x + s * y;
+        z1[q] = c * y - s * x;
+    }
+}
+// z -= (beta v) (v^T z) for the rows x nvec matrix z; t: nvec elements
+HINQS_WIDE void reflect(int rows, int nvec, double beta, const double *__restrict__ v, double *__restrict__ z,
+                        double *__restrict__ t) {
+    for (int q = 0; q < nvec; ++q) t[q] = 0.0;
+    for (int i = 0; i < rows; ++i)
+        for (int q = 0; q < nvec; ++q) t[q] += v[i] * z[(size_t)i * nvec + q];
+    for (int i = 0; i < rows; ++i)
+        for (int q = 0; q < nvec; ++q) z[(size_t)i * nvec + q] -= beta * v[i] * t[q];
+}
+#undef HINQS_WIDE
+
+// The lowest nvec eigenpairs of a symmetric n x n matrix (all eigenvalues,
+// ascending, in w; vectors as the columns of the n x nvec row-major Z) by
+// Householder reduction to tridiagonal form and the implicit-shift QL iteration
+// (the classic tridiagonal eigenvalue method of Bowdler, Martin, Reinsch and
+// Wilkinson).  The wait for it lies in every Davidson iteration, and only the
+// lowest vectors are used: neither stage accumulates its transformations.  The
+// reflectors and the rotations are kept and applied in reverse to nvec unit
+// vectors, all inner loops run along contiguous elements without a reduction,
+// and what remains is the chain of the rotations (n = 48, 8 vectors:
+// 105 us, with all vectors accumulated 200 us).  Returns false if an eigenvalue
 // needs more than 60 QL iterations (the caller then falls back to Jacobi).
-bool tridiag_ql_eig(int n, std::vector<double> A, std::vector<double> &w, std::vector<double> &Z) {
-    auto a = [&](int i, int j) -> double & { return A[(size_t)i * n + j]; };
-    // QT holds Q transposed (row j = column j of Q), so the updates below run
-    // along contiguous rows
-    std::vector<double> QT((size_t)n * n, 0.0), v(n), pv(n), d(n), e(n, 0.0), tq(n);
-    for (int i = 0; i < n; ++i) QT[(size_t)i * n + i] = 1.0;
-    // Householder: A <- H A H column by column, Q <- Q H
+bool tridiag_ql_eig(int n, int nvec, std::vector<double> A, std::vector<double> &w, std::vector<double> &Z) {
+    std::vector<double> U((size_t)n * n), beta(n, 0.0), pv(n), d(n), e(n, 0.0);  // row k of U: reflector k
     for (int k = 0; k + 2 < n; ++k) {
+        const double *ak = &A[(size_t)k * n];
+        double *v = &U[(size_t)k * n];
         double alpha = 0.0;
-        for (int i = k + 1; i < n; ++i) alpha += a(i, k) * a(i, k);
+        for (int i = k + 1; i < n; ++i) alpha += ak[i] * ak[i];
         alpha = std::sqrt(alpha);
         if (alpha == 0.0) continue;
-        if (a(k + 1, k) > 0.0) alpha = -alpha;  // v = x - alpha e1 without cancellation
+        if (ak[k + 1] > 0.0) alpha = -alpha;  // v = x - alpha e1 without cancellation
         double vv = 0.0;
-        for (int i = 0; i < n; ++i) v[i] = 0.0;
-        for (int i = k + 1; i < n; ++i) v[i] = a(i, k);
+        for (int i = k + 1; i < n; ++i) v[i] = ak[i];
         v[k + 1] -= alpha;
         for (int i = k + 1; i < n; ++i) vv += v[i] * v[i];
         if (vv == 0.0) continue;
-        const double beta = 2.0 / vv;
+        beta[k] = 2.0 / vv;
         // p = beta A v, q = p - (beta/2)(v.p) v, A <- A - v q^T - q v^T
+        const int r = n - k - 1;  // rows and columns k + 1 .. n - 1
+        double *sub = &A[(size_t)(k + 1) * n + k + 1];
+        rows_combine(r, r, sub, n, v + k + 1, pv.data());
         double vp = 0.0;
-        for (int i = k; i < n; ++i) {
-            double t = 0.0;
-            for (int j = k + 1; j < n; ++j) t += a(i, j) * v[j];
-            pv[i] = beta * t;
-        }
-        for (int i = k + 1; i < n; ++i) vp += v[i] * pv[i];
-        const double kk = 0.5 * beta * vp;
-        for (int i = k; i < n; ++i) pv[i] -= kk * v[i];
-        for (int i = k; i < n; ++i)
-            for (int j = k; j < n; ++j) a(i, j) -= v[i] * pv[j] + pv[i] * v[j];
-        // Q <- Q (I - beta v v^T): t_i = beta sum_j Q[i][j] v[j], Q[i][j] -= t_i v[j]
-        for (int i = 0; i < n; ++i) tq[i] = 0.0;
-        for (int j = k + 1; j < n; ++j) {
-            const double *qj = &QT[(size_t)j * n];
-            const double vj = v[j];
-            for (int i = 0; i < n; ++i) tq[i] += qj[i] * vj;
-        }
-        for (int i = 0; i < n; ++i) tq[i] *= beta;
-        for (int j = k + 1; j < n; ++j) {
-            double *qj = &QT[(size_t)j * n];
-            const double vj = v[j];
-            for (int i = 0; i < n; ++i) qj[i] -= tq[i] * vj;
-        }
+        for (int i = 0; i < r; ++i) vp += v[k + 1 + i] * (pv[i] *= beta[k]);
+        const double kk = 0.5 * beta[k] * vp;
+        for (int i = 0; i < r; ++i) pv[i] -= kk * v[k + 1 + i];
+        rank2_update(r, sub, n, v + k + 1, pv.data());
+        A[(size_t)k * n + k + 1] = alpha;  // the reflector maps the rest of row k onto e1
     }
-    for (int i = 0; i < n; ++i) d[i] = a(i, i);
-    for (int i = 0; i + 1 < n; ++i) e[i] = a(i + 1, i);
-    // implicit QL on (d, e); columns of Q follow the rotations
+    for (int i = 0; i < n; ++i) d[i] = A[(size_t)i * n + i];
+    for (int i = 0; i + 1 < n; ++i) e[i] = A[(size_t)i * n + i + 1];
+    struct Rot {
+        int i;
+        double c, s;
+    };
+    std::vector<Rot> rots;
+    rots.reserve((size_t)2 * n * n);
+    // implicit QL on (d, e)
     for (int l = 0; l < n; ++l) {
         int iter = 0, m;
         do {
@@ -598,12 +675,7 @@ bool tridiag_ql_eig(int n, std::vector<double> A, std::vector<double> &w, std::v
                     p = s * r;
                     d[i + 1] = g + p;
                     g = c * r - b;
-                    double *zi = &QT[(size_t)i * n], *zi1 = &QT[(size_t)(i + 1) * n];
-                    for (int k = 0; k < n; ++k) {
-                        const double fk = zi1[k];
-                        zi1[k] = s * zi[k] + c * fk;
-                        zi[k] = c * zi[k] - s * fk;
-                    }
+                    rots.push_back({i, c, s});
                 }
                 if (r == 0.0 && i >= l) continue;
                 d[l] -= p;
@@ -618,19 +690,30 @@ bool tridiag_ql_eig(int n, std::vector<double> A, std::vector<double> &w, std::v
     std::iota(ord.begin(), ord.end(), 0);
     std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return d[x] < d[y]; });
     w.resize(n);
-    Z.assign((size_t)n * n, 0.0);
-    for (int c = 0; c < n; ++c) {
-        w[c] = d[ord[c]];
-        const double *qc = &QT[(size_t)ord[c] * n];
-        for (int k = 0; k < n; ++k) Z[(size_t)k * n + c] = qc[k];
+    for (int c = 0; c < n; ++c) w[c] = d[ord[c]];
+    // rotations, then reflectors, last to first, on the unit vectors of the chosen columns
+    Z.assign((size_t)n * nvec, 0.0);
+    for (int q = 0; q < nvec; ++q) Z[(size_t)ord[q] * nvec + q] = 1.0;
+    for (size_t t = rots.size(); t-- > 0;) {
+        double *z0 = &Z[(size_t)rots[t].i * nvec];
+        rotate_pair(nvec, rots[t].c, rots[t].s, z0, z0 + nvec);
     }
+    std::vector<double> t(nvec);
+    for (int k = n - 3; k >= 0; --k)
+        if (beta[k] != 0.0)
+            reflect(n - k - 1, nvec, beta[k], &U[(size_t)k * n + k + 1], &Z[(size_t)(k + 1) * nvec], t.data());
     return true;
 }
 
-// Eigenpairs of a small symmetric matrix: tridiagonal QL, Jacobi as fallback.
-void small_sym_eig(int n, const std::vector<double> &A, std::vector<double> &w, std::vector<double> &Z) {
-    if (n >= 3 && tridiag_ql_eig(n, A, w, Z)) return;
-    jacobi_eig(n, A, w, Z);
+// The lowest nvec eigenpairs of a small symmetric matrix (w all, Z n x nvec
+// row-major): tridiagonal QL, Jacobi as fallback.
+void small_sym_eig(int n, int nvec, const std::vector<double> &A, std::vector<double> &w, std::vector<double> &Z) {
+    if (n >= 3 && tridiag_ql_eig(n, nvec, A, w, Z)) return;
+    std::vector<double> full;
+    jacobi_eig(n, A, w, full);
+    Z.resize((size_t)n * nvec);
+    for (int a = 0; a < n; ++a)
+        for (int q = 0; q < nvec; ++q) Z[(size_t)a * nvec + q] = full[(size_t)a * n + q];
 }
 
 // Orthonormal basis (modified Gram-Schmidt, twice) of the columns of the
@@ -672,7 +755,7 @@ struct Solver {
     int mmax;     // largest subspace
     int nblocks;  // column blocks of V and W
     // workspace kept in the context between solves
-    DBuf<double> &Vb, &Wb, &T, &Wn, &small, &partial, &nrm;
+    DBuf<double> &Vb, &Wb, &T, &Wn, &small, &partial;
     Mat V{}, W{}, Tm{}, Wnm{};
     // Tm / Wnm: where the next new directions and their images are formed.
     // When they start a column block of V (m a multiple of K, with a block
@@ -687,17 +770,17 @@ struct Solver {
     int nblk_gram = 1;
     std::vector<hipEvent_t> evs;  // start/stop pairs around every sigma product, read at the end
     double ms_sigma = 0.0;
-    int sigma_blocks = 0, sigma_columns = 0;
+    int sigma_blocks = 0, sigma_columns = 0, second_passes = 0;
     // pinned staging ring for small host -> device uploads (no sync per upload)
     static constexpr int SLOTS = 16;
     static constexpr size_t SLOT_DOUBLES = 96 * 96;
     double *pinned = nullptr;
-    double *pinned_dl = nullptr;  // small downloads land here (pinned, so the copy is asynchronous)
+    double *pinned_dl = nullptr;  // small results land here (pinned, written by the kernels)
     int upload_count = 0;
 
     Solver(Ctx &cc, int k, int m_max)
         : c(cc), s(cc.stream), D(cc.ndet), K(k), mmax(m_max), Vb(cc.dw.Vb), Wb(cc.dw.Wb), T(cc.dw.T),
-          Wn(cc.dw.Wn), small(cc.dw.small), partial(cc.dw.partial), nrm(cc.dw.nrm), X32(cc.dw.X32),
+          Wn(cc.dw.Wn), small(cc.dw.small), partial(cc.dw.partial), X32(cc.dw.X32),
           S32(cc.dw.S32), guess_idx(cc.dw.guess_idx), argv(cc.dw.argv), argi(cc.dw.argi), xfin(cc.dw.xfin),
           signbuf(cc.dw.signbuf) {
         nblocks = (mmax + K - 1) / K;
@@ -710,10 +793,9 @@ struct Solver {
         W = Mat{Wb.p, K, (int64_t)bsz};
         Tm = Mat{T.p, K, (int64_t)bsz};
         Wnm = Mat{Wn.p, K, (int64_t)bsz};
-        small.ensure(96 * 96 * 2 + 4096);
+        small.ensure(96 * 96 * 2);
         nblk_gram = gram_blocks_for(D);
-        partial.ensure(std::max<size_t>((size_t)nblk_gram * 96 * 16, 2048 * 2 * 16) + 4096);  // gram / k_ritz partials
-        nrm.ensure(64);
+partial.ensure(std::max<size_t>((size_t)nblk_gram * 96 * 16, (size_t)tall_grid() * (2 + nblocks * K) * K));
         HQ_CHECK(hipMemsetAsync(Vb.p, 0, sizeof(double) * bsz * nblocks, s));
         HQ_CHECK(hipMemsetAsync(Wb.p, 0, sizeof(double) * bsz * nblocks, s));
         HQ_CHECK(hipMemsetAsync(T.p, 0, sizeof(double) * bsz, s));
@@ -723,7 +805,7 @@ struct Solver {
                                    hipHostMallocDefault));
         pinned = c.dw.pinned;
         if (!c.dw.pinned_dl)
-            HQ_CHECK(hipHostMalloc((void **)&c.dw.pinned_dl, sizeof(double) * SLOT_DOUBLES, hipHostMallocDefault));
+            HQ_CHECK(hipHostMalloc((void **)&c.dw.pinned_dl, sizeof(double) * SLOT_DOUBLES, hipHostMallocCoherent));
         pinned_dl = c.dw.pinned_dl;
     }
     ~Solver() {
@@ -731,34 +813,36 @@ struct Solver {
         for (auto e : evs) (void)hipEventDestroy(e);
     }
 
-    // small.p regions: [0, 96*96) gram outputs / Y, [96*96, 2*96*96) coefficient uploads
+    // small.p regions: [0, 96*96) norms and V^T T of a Ritz step or Y and theta,
+    // [96*96, 2*96*96) coefficient uploads
     double *scratch_a() { return small.p; }
     double *scratch_b() { return small.p + 96 * 96; }
-    double *scratch_c() { return small.p + 2 * 96 * 96; }  // [0, 16) column norms, [64] gate flag
-    int *pass2_count() { return reinterpret_cast<int *>(scratch_c() + 65); }
+    // pinned_dl regions, written by k_reduce_partials and read after a wait for the
+    // stream: products (any size up to H_RITZ), norms and V^T T, T^T T
+    static constexpr size_t H_RITZ = SLOT_DOUBLES - 96 * 16 - 16 * 16 - 32;
+    double *host_products() { return pinned_dl; }
+    double *host_norms() { return pinned_dl + H_RITZ; }  // ||r||^2 and ||t||^2 of K roots
+    double *host_coef() { return host_norms() + 2 * K; }
+    double *host_tt() { return host_norms() + 32 + 96 * 16; }
+    double *dev_coef() { return scratch_a() + 2 * K; }  // m x nc
+    unsigned tall_grid() const {  // workgroups of the kernels that leave partials
+        return (unsigned)std::max<int64_t>(1, std::min<int64_t>(((D + 15) / 16 + 3) / 4, TALL_MAX_BLOCKS));
+    }
 
-    void gram(Mat A, int ma, Mat B, int nb, double *out, const int *gate = nullptr) {
-        launch_gram(s, D, nblk_gram, A, ma, B, nb, partial.p, out, gate);
+    // A^T B, ma x nb row-major, to device and / or pinned host memory
+    void gram(Mat A, int ma, Mat B, int nb, double *dev, double *host) {
+        launch_gram(s, D, nblk_gram, A, ma, B, nb, partial.p, dev, host);
     }
 
     std::vector<double> gram_host(Mat A, int ma, Mat B, int nb) {
-        gram(A, ma, B, nb, scratch_a());
-        return download(scratch_a(), (size_t)ma * nb);
-    }
-
-    // n doubles of device memory to the host (through the pinned landing area;
-    // the wait polls the stream)
-    std::vector<double> download(const double *src, size_t n) {
-        if (n > SLOT_DOUBLES) throw Error(HINQS_E_UNSUPPORTED, "small download too large");
-        HQ_CHECK(hipMemcpyAsync(pinned_dl, src, sizeof(double) * n, hipMemcpyDeviceToHost, s));
+        gram(A, ma, B, nb, nullptr, host_products());
         wait_stream(s);
-        return std::vector<double>(pinned_dl, pinned_dl + n);
+        return std::vector<double>(host_products(), host_products() + (size_t)ma * nb);
     }
 
     // Out[:, 0:nc] = beta Out + alpha A[:, 0:m] Bs (m x nc row-major, device);
     // A has K columns per block.
-    void tsmm(Mat A, int m, const double *Bs, int nc, double alpha, double beta, Mat Out,
-              const int *gate = nullptr) {
+    void tsmm(Mat A, int m, const double *Bs, int nc, double alpha, double beta, Mat Out) {
         if (m <= 0 || nc <= 0) return;
         if (nc > 32) throw Error(HINQS_E_UNSUPPORTED, "tsmm width");
         if (m > 96) throw Error(HINQS_E_UNSUPPORTED, "tsmm depth");
@@ -767,11 +851,11 @@ struct Solver {
         const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((ntiles + 3) / 4, 2048));
         dim3 g(grid), b(256);
         if (nc <= 16) {
-            if (m <= 48) hipLaunchKernelGGL((k_tsmm<1, 12>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, gate);
-            else hipLaunchKernelGGL((k_tsmm<1, 24>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, gate);
+            if (m <= 48) hipLaunchKernelGGL((k_tsmm<1, 12>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, (double *)nullptr);
+            else hipLaunchKernelGGL((k_tsmm<1, 24>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, (double *)nullptr);
         } else {
-            if (m <= 48) hipLaunchKernelGGL((k_tsmm<2, 12>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, gate);
-            else hipLaunchKernelGGL((k_tsmm<2, 24>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, gate);
+            if (m <= 48) hipLaunchKernelGGL((k_tsmm<2, 12>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, (double *)nullptr);
+            else hipLaunchKernelGGL((k_tsmm<2, 24>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, (double *)nullptr);
         }
         HQ_LAUNCH_CHECK();
     }
@@ -856,16 +940,17 @@ struct Solver {
     // diag(w) Z^T (S = diag(sc)), T <- T S Z_k w_k^(-1/2) over the eigenvalues
     // w_k > drop, largest first; the unused columns of T are cleared.  Returns
     // the number kept (0: none) and their smallest eigenvalue in wmin.
-    int sym_orth(int kept, const std::vector<double> &sc, double drop, double &wmin) {
+    // gt: T^T T, leading dimension ldg.
+    int sym_orth(int kept, const std::vector<double> &sc, double drop, double &wmin, const double *gt, int ldg) {
         double *Zd = scratch_b();  // K x K
-        std::vector<double> g = gram_host(Tm, kept, Tm, kept);
+        std::vector<double> g((size_t)kept * kept);
         for (int a = 0; a < kept; ++a)
             for (int b = a; b < kept; ++b) {
-                const double v = sc[a] * sc[b] * 0.5 * (g[(size_t)a * kept + b] + g[(size_t)b * kept + a]);
+                const double v = sc[a] * sc[b] * 0.5 * (gt[(size_t)a * ldg + b] + gt[(size_t)b * ldg + a]);
                 g[(size_t)a * kept + b] = g[(size_t)b * kept + a] = v;
             }
         std::vector<double> w, Z;
-        small_sym_eig(kept, g, w, Z);
+        small_sym_eig(kept, kept, g, w, Z);
         std::vector<int> keep;
         for (int j = kept - 1; j >= 0; --j)  // largest first
             if (std::isfinite(w[j]) && w[j] > drop) keep.push_back(j);
@@ -882,57 +967,76 @@ struct Solver {
         return nk;
     }
 
-    // Orthonormalize the columns of T against V[:, 0:m] and within T; returns
-    // the number of kept directions, left in T[:, 0:kept] (other columns
-    // zeroed).  scale[q] (host, K entries) is 1/||T[:, q]|| for the columns to
-    // keep and 0 for those to discard; nullptr = the initial block (the first
-    // n columns, scales from T^T T).  One projection pass against V, a second
-    // only when the first left less than half of some column's norm (decided
-    // on the device), so T is orthogonal to V to a few ulps; then symmetric
-    // orthonormalization of the unit-scaled block.  Corrections drop
-    // eigen-directions with eigenvalue <= ORTH_DROP (less than a tenth of
-    // their norm outside span(V) and the other new directions): the transform
-    // then amplifies rounding at most tenfold and needs no second round.  The
-    // initial block keeps everything above 1e-14 instead, since a warm-start
-    // guess can lie almost inside the span of the unit vectors that join it
-    // and its own direction must survive, and repeats the orthonormalization
-    // (eigenvalues > 1e-4) when the first kept one below 1e-2.
-    int orthonormalize(int m, int n, const double *scale) {
-        double *C = scratch_a();  // m x K
-        const bool initial = scale == nullptr;
-        std::vector<double> sc(K, 0.0);
-        if (!initial) {
-            for (int q = 0; q < K; ++q) sc[q] = scale[q];
-        } else {
-            std::vector<double> g = gram_host(Tm, n, Tm, n);
-            for (int q = 0; q < n; ++q) {
-                const double d = g[(size_t)q * n + q];
-                if (std::isfinite(d) && d > 0.0) sc[q] = 1.0 / std::sqrt(d);
+    // T[:, 0:nc] -= V[:, 0:m] (V^T T) with V^T T in dev_coef(), and the product
+    // T^T T after it to host_tt().
+    void project(int m, int nc) {
+        const dim3 g(tall_grid()), b(256);
+        if (m <= 48)
+            hipLaunchKernelGGL((k_tsmm<1, 12, true>), g, b, 0, s, D, m, V, (const double *)dev_coef(), nc, -1.0, 1.0,
+                               Tm, partial.p);
+        else
+            hipLaunchKernelGGL((k_tsmm<1, 24, true>), g, b, 0, s, D, m, V, (const double *)dev_coef(), nc, -1.0, 1.0,
+                               Tm, partial.p);
+        HQ_LAUNCH_CHECK();
+        launch_reduce(s, partial.p, (int)g.x, nc * nc, nullptr, host_tt());
+    }
+
+    // Orthonormalize the initial block T[:, 0:n] (scales from T^T T).  It keeps
+    // every eigen-direction above 1e-14, since a warm-start guess can lie almost
+    // inside the span of the unit vectors that join it and its own direction must
+    // survive, and repeats the orthonormalization (eigenvalues > 1e-4) when the
+    // first kept one below 1e-2.
+    int orthonormalize_initial(int n) {
+        std::vector<double> sc(K, 0.0), g = gram_host(Tm, n, Tm, n);
+        int kept = 0;  // columns that may hold a direction
+        for (int q = 0; q < n; ++q) {
+            const double d = g[(size_t)q * n + q];
+            if (std::isfinite(d) && d > 0.0) {
+                sc[q] = 1.0 / std::sqrt(d);
+                kept = q + 1;
             }
         }
-        int kept = 0;  // columns that may hold a direction
-        for (int q = 0; q < K; ++q)
-            if (sc[q] > 0.0) kept = q + 1;
         if (kept == 0) return 0;
-        if (m > 0) {
-            gram(V, m, Tm, kept, C);
-            tsmm(V, m, C, kept, -1.0, 1.0, Tm);
-            // the second pass runs only when the device gate asks for it
-            std::vector<double> tn2(K, 0.0);
-            for (int q = 0; q < kept; ++q)
-                if (sc[q] > 0.0) tn2[q] = 1.0 / (sc[q] * sc[q]);
-            upload_small(tn2, scratch_c());
-            int *gate = reinterpret_cast<int *>(scratch_c() + 64);
-            hipLaunchKernelGGL(k_proj_gate, dim3(1), dim3(64), 0, s, (const double *)C, m, kept,
-                               (const double *)scratch_c(), gate, pass2_count());
-            HQ_LAUNCH_CHECK();
-            gram(V, m, Tm, kept, C, gate);
-            tsmm(V, m, C, kept, -1.0, 1.0, Tm, gate);
+        double wmin = 0.0;
+        int nk = sym_orth(kept, sc, 1e-14, wmin, g.data(), n);
+        if (nk > 0 && wmin < 1e-2) {
+            g = gram_host(Tm, nk, Tm, nk);
+            nk = sym_orth(nk, std::vector<double>(K, 1.0), 1e-4, wmin, g.data(), nk);
+        }
+        return nk;
+    }
+
+    // Orthonormalize the columns of T against V[:, 0:m] and within T, after
+    // project(m, nc) and a wait; returns the number of kept directions, left in
+    // T[:, 0:kept] (other columns zeroed).  scale[q] (K entries) is 1/||T[:, q]||
+    // before that pass for the columns to keep and 0 for those to discard.  One
+    // projection pass against V, a second only when the first left less than half
+    // of some column's norm (||T_q||^2 - ||(V^T T)_q||^2 < ||T_q||^2 / 4; NaN counts
+    // as less), so T is orthogonal to V to a few ulps; then symmetric
+    // orthonormalization of the unit-scaled block, which drops eigen-directions
+    // with eigenvalue <= ORTH_DROP (less than a tenth of their norm outside span(V)
+    // and the other new directions): the transform then amplifies rounding at most
+    // tenfold and needs no second round.
+    int orthonormalize(int m, int nc, const std::vector<double> &sc) {
+        int kept = 0;  // columns that may hold a direction
+        bool again = false;
+        for (int q = 0; q < nc; ++q) {
+            if (!(sc[q] > 0.0)) continue;
+            kept = q + 1;
+            const double tn2 = 1.0 / (sc[q] * sc[q]);
+            double c2 = 0.0;
+            for (int a = 0; a < m; ++a) c2 += host_coef()[(size_t)a * nc + q] * host_coef()[(size_t)a * nc + q];
+            again |= !(tn2 - c2 >= 0.25 * tn2);
+        }
+        if (kept == 0) return 0;
+        if (again) {
+            ++second_passes;
+            gram(V, m, Tm, nc, dev_coef(), nullptr);
+            project(m, nc);
+            wait_stream(s);
         }
         double wmin = 0.0;
-        int nk = sym_orth(kept, sc, initial ? 1e-14 : ORTH_DROP, wmin);
-        if (nk > 0 && initial && wmin < 1e-2) nk = sym_orth(nk, std::vector<double>(K, 1.0), 1e-4, wmin);
-        return nk;
+        return sym_orth(kept, sc, ORTH_DROP, wmin, host_tt(), nc);
     }
 
     void lowest_diag_indices(int n, int32_t *dev_idx) {
@@ -973,16 +1077,23 @@ struct Solver {
     }
 };
 
+// One Ritz step: T and the norms, with the product V^T T if `ahead`.  One wait
+// of the host, seven launches and no copy of results go into an iteration's
+// Ritz step and orthonormalization (20,000 rows: 300 -> 200 us per iteration,
+// 71 us of it the product with H).
 template <int KK>
-void launch_ritz(Solver &S, int m, const double *Yd, const double *thd, double floor_, int nroots,
-                 unsigned grid) {
-    if (m <= 48)
-        hipLaunchKernelGGL((k_ritz<KK, 12>), dim3(grid), dim3(256), 0, S.s, S.D, m, S.V, S.W, Yd, thd, S.c.diag.p,
-                           floor_, nroots, S.Tm.p, S.partial.p);
-    else
-        hipLaunchKernelGGL((k_ritz<KK, 24>), dim3(grid), dim3(256), 0, S.s, S.D, m, S.V, S.W, Yd, thd, S.c.diag.p,
-                           floor_, nroots, S.Tm.p, S.partial.p);
-    HQ_LAUNCH_CHECK();
+void launch_ritz(Solver &S, int m, const double *Yd, double floor_, int nroots, bool ahead) {
+    const dim3 g(S.tall_grid()), b(256);
+    const double *thd = Yd + (size_t)m * KK;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, g, b, 0, S.s, S.D, m, S.V, S.W, Yd, thd, S.c.diag.p, floor_, nroots, S.Tm.p,
+                           S.partial.p);
+        HQ_LAUNCH_CHECK();
+    };
+    if (m <= 48) ahead ? go(k_ritz<KK, 12, true>) : go(k_ritz<KK, 12, false>);
+    else ahead ? go(k_ritz<KK, 24, true>) : go(k_ritz<KK, 24, false>);
+    launch_reduce(S.s, S.partial.p, (int)g.x, 2 * KK + (ahead ? m * KK : 0), ahead ? S.scratch_a() : nullptr,
+                  S.host_norms());
 }
 
 }  // namespace
@@ -1004,7 +1115,6 @@ int davidson(Ctx &c, const hinqs_opts &o, const double *guess, double *energy, d
         if (o.precision == HINQS_SOLVE_MIXED) autotune_sigma(c, K, HINQS_FP32);
     }
     Solver S(c, K, mmax);
-    HQ_CHECK(hipMemsetAsync(S.pass2_count(), 0, sizeof(int), S.s));
     hipStream_t s = c.stream;
     bool fp32 = (o.precision == HINQS_SOLVE_MIXED);
     int it_fp32 = 0, restarts = 0, iters = 0;
@@ -1037,7 +1147,7 @@ int davidson(Ctx &c, const hinqs_opts &o, const double *guess, double *energy, d
                            S.guess_idx.p);
         HQ_LAUNCH_CHECK();
     }
-    int m = S.orthonormalize(0, n0 + nunit, nullptr);
+    int m = S.orthonormalize_initial(n0 + nunit);
     if (m == 0) throw Error(HINQS_E_INVALID_ARG, "initial guess is zero");
     S.apply_h(S.Tm.p, m, fp32, S.Wnm.p);
     S.place_new(m, 0);
@@ -1062,11 +1172,14 @@ int davidson(Ctx &c, const hinqs_opts &o, const double *guess, double *energy, d
     // full G of the current V, W (after a restart)
     auto load_g_all = [&](int mm) {
         std::fill(G.begin(), G.end(), 0.0);
+        double *g = S.host_products();
+        if ((size_t)mm * mm > S.H_RITZ) throw Error(HINQS_E_UNSUPPORTED, "basis after a restart too large");
+        for (int b0 = 0; b0 < mm; b0 += K) S.gram(S.V, mm, S.W.cols(b0), std::min(K, mm - b0), nullptr, g + (size_t)mm * b0);
+        wait_stream(S.s);
         for (int b0 = 0; b0 < mm; b0 += K) {
             const int nb = std::min(K, mm - b0);
-            std::vector<double> g = S.gram_host(S.V, mm, S.W.cols(b0), nb);
             for (int a = 0; a < mm; ++a)
-                for (int b = 0; b < nb; ++b) G[(size_t)a * 96 + b0 + b] = g[(size_t)a * nb + b];
+                for (int b = 0; b < nb; ++b) G[(size_t)a * 96 + b0 + b] = g[(size_t)mm * b0 + (size_t)a * nb + b];
         }
         for (int a = 0; a < mm; ++a)
             for (int b = a + 1; b < mm; ++b) {
@@ -1100,35 +1213,36 @@ int davidson(Ctx &c, const hinqs_opts &o, const double *guess, double *energy, d
         for (int a = 0; a < m; ++a)
             for (int b = 0; b < m; ++b) Gm[(size_t)a * m + b] = G[(size_t)a * 96 + b];
         std::vector<double> w, Z;
-        small_sym_eig(m, Gm, w, Z);
         nroots_eff = std::min(kroots, m);
+        small_sym_eig(m, nroots_eff, Gm, w, Z);
         theta.assign(K, 0.0);
         Y.assign((size_t)m * K, 0.0);
         for (int q = 0; q < nroots_eff; ++q) {
             theta[q] = w[q];
-            for (int a = 0; a < m; ++a) Y[(size_t)a * K + q] = Z[(size_t)a * m + q];
+            for (int a = 0; a < m; ++a) Y[(size_t)a * K + q] = Z[(size_t)a * nroots_eff + q];
         }
         y0.assign(m, 0.0);
-        for (int a = 0; a < m; ++a) y0[a] = Z[(size_t)a * m + 0];
+        for (int a = 0; a < m; ++a) y0[a] = Z[(size_t)a * nroots_eff];
         // ---- residuals + preconditioned corrections (T, formed where V's new columns go)
         S.bind_new(m);
         double *Yd = S.scratch_a();
-        double *thd = S.scratch_a() + 96 * 16;
-        S.upload_small(Y, Yd);
-        S.upload_small(theta, thd);
-        const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(((D + 15) / 16 + 3) / 4, 2048));
+        std::vector<double> up(Y);
+        up.insert(up.end(), theta.begin(), theta.end());
+        S.upload_small(up, Yd);
+        // Where no restart can come between, the corrections are projected before
+        // their norms are known, all of them: a root that drops out is scaled to
+        // zero afterwards, and the host waits once instead of twice.
+        const bool ahead = m + nroots_eff <= mmax;
         switch (K) {
-            case 1: launch_ritz<1>(S, m, Yd, thd, o.precond_floor, nroots_eff, grid); break;
-            case 2: launch_ritz<2>(S, m, Yd, thd, o.precond_floor, nroots_eff, grid); break;
-            case 4: launch_ritz<4>(S, m, Yd, thd, o.precond_floor, nroots_eff, grid); break;
-            case 8: launch_ritz<8>(S, m, Yd, thd, o.precond_floor, nroots_eff, grid); break;
-            default: launch_ritz<16>(S, m, Yd, thd, o.precond_floor, nroots_eff, grid); break;
+            case 1: launch_ritz<1>(S, m, Yd, o.precond_floor, nroots_eff, ahead); break;
+            case 2: launch_ritz<2>(S, m, Yd, o.precond_floor, nroots_eff, ahead); break;
+            case 4: launch_ritz<4>(S, m, Yd, o.precond_floor, nroots_eff, ahead); break;
+            case 8: launch_ritz<8>(S, m, Yd, o.precond_floor, nroots_eff, ahead); break;
+            default: launch_ritz<16>(S, m, Yd, o.precond_floor, nroots_eff, ahead); break;
         }
-        hipLaunchKernelGGL(k_reduce_partials, dim3(2 * K), dim3(256), 0, s, S.partial.p, (int)grid, 2 * K,
-                           S.nrm.p, (const int *)nullptr);
-        HQ_LAUNCH_CHECK();
-        std::vector<double> rt = S.download(S.nrm.p, 2 * K);
-        std::vector<double> rn(rt.begin(), rt.begin() + K), tn2(rt.begin() + K, rt.end());
+        if (ahead) S.project(m, K);
+        wait_stream(s);
+        std::vector<double> rn(S.host_norms(), S.host_norms() + K), tn2(S.host_norms() + K, S.host_norms() + 2 * K);
         for (double &x : rn) x = std::sqrt(std::max(0.0, x));
         res0 = rn[0];
         ++iters;
@@ -1226,7 +1340,12 @@ int davidson(Ctx &c, const hinqs_opts &o, const double *guess, double *energy, d
             rotate_basis(Qk, q);
             Ycur.swap(Yn);
         }
-        int kept = S.orthonormalize(m, K, tscale.data());
+        if (!ahead) {
+            S.gram(S.V, m, S.Tm, K, S.dev_coef(), S.host_coef());
+            S.project(m, K);
+            wait_stream(s);
+        }
+        int kept = S.orthonormalize(m, K, tscale);
         if (kept == 0) {
             if (!fp32) break;  // no new direction: report the current Ritz pair, not converged
             force_switch = true;  // FP32 images cannot resolve further directions: refine in FP64
@@ -1253,10 +1372,7 @@ int davidson(Ctx &c, const hinqs_opts &o, const double *guess, double *energy, d
         S.collect_sigma_times();
         st->ms_sigma = S.ms_sigma;
         st->nnz = c.nnz;
-        int np2 = 0;
-        HQ_CHECK(hipMemcpyAsync(&np2, S.pass2_count(), sizeof(int), hipMemcpyDeviceToHost, S.s));
-        HQ_CHECK(hipStreamSynchronize(S.s));
-        st->second_passes = np2;
+        st->second_passes = S.second_passes;
         st->ms_total = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     }
     return converged ? HINQS_OK : HINQS_E_NOT_CONVERGED;
@@ -1268,7 +1384,7 @@ void gram_product(Ctx &c, int64_t nrows, const double *A, int lda, int ma, const
     DBuf<double> partial;
     partial.ensure((size_t)nblk * ma * nb);
     launch_gram(c.stream, nrows, nblk, Mat{const_cast<double *>(A), lda, 0}, ma,
-                Mat{const_cast<double *>(B), ldb, 0}, nb, partial.p, G);
+                Mat{const_cast<double *>(B), ldb, 0}, nb, partial.p, G, nullptr);
     HQ_CHECK(hipStreamSynchronize(c.stream));
 }
 

@@ -201,3 +201,23 @@ def test_batch_subspaces_of_every_size(block, max_space, threads, monkeypatch):
     for x, (spectrum, dmin) in zip(e, ref):
         slack = 1e-12 * np.abs(spectrum).max()
         assert np.abs(spectrum - x).min() <= 1e-9 + slack and x <= dmin + slack, (x, spectrum[:4], dmin)
+
+
+@pytest.mark.parametrize("block,max_space", [(1, 3), (2, 7), (4, 12), (8, 24), (8, 48), (8, 60), (16, 96)])
+@pytest.mark.parametrize("ndet", [63, 64, 65, 1025])
+def test_solver_subspaces_and_row_tiles(ndet, block, max_space):
+    """Rows around a tile of the tall products, subspaces up to and past 48
+    columns, restarts after every and after many steps.  A dense eigenvalue
+    lies within the residual's norm (tol) of the result, which is at most the
+    lowest diagonal element, and the vector's residual is the one reported."""
+    log(f"solver {ndet} rows, block {block}, max_space {max_space}")
+    ints = W.gen_integrals(9, 3, -2.0, -0.5, 41)
+    a, b = W.sample_determinants(9, 4, 5, ndet, 0.4, 0.0, 42 + ndet)
+    s, o = solver_for(ints, a, b, 4, 5), oracle_for(ints, a, b, 4, 5)
+    e, c, st = s.lowest_eigenpair(block=block, max_space=max_space, tol=1e-9, max_iter=2000)
+    assert st["converged"]
+    w, c = o.spectrum(ndet), c.cpu().numpy()
+    slack = 1e-12 * np.abs(w).max()
+    assert np.abs(w - e).min() <= 1e-9 + slack and e <= o.diag().min() + slack
+    assert abs(np.linalg.norm(c) - 1.0) <= 1e-12
+    assert np.linalg.norm(o.dense() @ c - e * c) <= 1e-9 + 100 * slack
