@@ -141,9 +141,6 @@ __host__ __device__ inline int lowbit(uint32_t x) {  // index of lowest set bit,
 #endif
 }
 
-// Candidates tested per step of a group scan before the hits are emitted.
-constexpr int SCAN_W = 16;
-
 // Davidson: a new direction is kept when the eigenvalue of its unit-scaled
 // block Gram exceeds this (more than a tenth of its norm lies outside the
 // span of the basis and of the other new directions), so the orthonormalizing
@@ -400,6 +397,9 @@ void build_determinants(Ctx &c, int64_t ndet, const uint64_t *alpha, const uint6
 // xcd_rows: also split the rows over the XCDs for sigma (a host read; not
 // needed for a set that is only an instance of a batch being assembled).
 void build_connectivity(Ctx &c, bool xcd_rows = true);
+// Couplings of nrows listed rows (sorted positions): their number to
+// counts[row], or the entries themselves at c.rowptr.
+void connect_listed_rows(Ctx &c, const int32_t *rows, int64_t nrows, int64_t *counts, bool fill);
 void build_elements(Ctx &c);
 // Values of the entries of each row after its first skip[row] (whose values
 // are already in place), and every diagonal element.

@@ -26,10 +26,13 @@
 #include <cstdlib>
 
 #include "common.hpp"
+#include "enumerate.hpp"
 
 namespace hinqs {
 
 namespace {
+
+constexpr int CONNECT_W = 32;  // strings tested per step of a scan
 
 // Group scans test CONNECT_W candidates without branching, then emit the hits of
 // that step from a bit mask: the emission code (descriptor and two stores)
@@ -45,6 +48,7 @@ struct ConnArgs {
     int alink_max;
     int norb;
     int32_t lookup_min;  // alpha groups at least this long are searched, not scanned
+    const int32_t *rows = nullptr;  // k_connect_rows: the ndet rows to enumerate, nullptr: all
 };
 
 // Alpha+beta couplings of a row with beta string bi into the alpha group
@@ -89,69 +93,6 @@ __device__ inline void ab_lookup(const uint32_t *__restrict__ sb, int32_t g0, in
     }
 }
 
-// Couplings a wave has found and not written yet: up to EMIT_CAP per lane (one
-// row per lane) in LDS.  Written straight from the lanes, every 4-byte store of
-// a wave went to 64 different rows (1.56e8 couplings: 5.0 ms, against 2.7 ms
-// for the same tests without the stores); a flush writes up to sixteen
-// consecutive couplings of a row with sixteen neighbouring lanes.
-constexpr int CONNECT_W = 32;  // strings tested per step of a scan
-constexpr int EMIT_CAP = 16;
-constexpr int EMIT_STRIDE = EMIT_CAP + 1;  // keeps the lanes' slots in different banks
-struct EmitBuf {
-    int32_t col[64 * EMIT_STRIDE];
-    uint32_t desc[64 * EMIT_STRIDE];
-};
-
-// out: the lane's next place in the matrix; n: couplings it holds.  Called by
-// the whole wave.
-__device__ inline void emit_flush(EmitBuf &b, int64_t &out, int &n, int lane, int32_t *col, uint32_t *desc) {
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll 4
-    for (int r0 = 0; r0 < 64; r0 += 64 / EMIT_CAP) {
-        const int r = r0 + lane / EMIT_CAP, k = lane % EMIT_CAP;
-        const int nr = __shfl(n, r, 64);
-        const int64_t at = __shfl(out, r, 64) + k;
-        if (k < nr) {
-            col[at] = b.col[r * EMIT_STRIDE + k];
-            desc[at] = b.desc[r * EMIT_STRIDE + k];
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    out += n;
-    n = 0;
-}
-
-// Tests every string in str[lo, hi) (per lane) against own, CONNECT_W at a
-// time: hits(j0, mask) with bit u of the mask set where accept(bits that differ)
-// of str[j0 + u] holds, at most EMIT_CAP of them.  Lanes that share the range
-// (rows of one group) read it through the scalar cache.  Called by the whole
-// wave; str is readable CONNECT_W strings past its end.
-template <typename Accept, typename Hits>
-__device__ inline void scan_strings(const uint32_t *__restrict__ str, int32_t lo, int32_t hi, uint32_t own,
-                                    Accept &&accept, Hits &&hits) {
-    auto test = [&](int32_t j0, int32_t end) {
-        uint32_t m = 0;
-#pragma unroll
-        for (int u = 0; u < CONNECT_W; ++u) m |= accept(popc32(own ^ str[j0 + u])) ? 1u << u : 0u;
-        return end - j0 < CONNECT_W ? m & ((1u << (end - j0)) - 1u) : m;
-    };
-    auto report = [&](int32_t j0, uint32_t m) {
-        if (__any(popc32(m) > EMIT_CAP)) {
-            hits(j0, m & 0xffffu);
-            hits(j0 + 16, m >> 16);
-        } else {
-            hits(j0, m);
-        }
-    };
-    static_assert(CONNECT_W == 32 && EMIT_CAP >= 16, "halves fit");
-    const int32_t ulo = __builtin_amdgcn_readfirstlane(lo), uhi = __builtin_amdgcn_readfirstlane(hi);
-    if (__all(lo == ulo && hi == uhi)) {
-        for (int32_t j0 = ulo; j0 < uhi; j0 += CONNECT_W) report(j0, test(j0, uhi));
-    } else {
-        for (int32_t j0 = lo; __any(j0 < hi); j0 += CONNECT_W) report(j0, j0 < hi ? test(j0, hi) : 0u);
-    }
-}
-
 // Alpha-only moves (x_j shares beta_i), one thread per entry of the
 // beta-major listing: neighbouring threads share beta_i and scan the same
 // beta group, where one thread per sorted row would scan a different beta group
@@ -170,7 +111,7 @@ __global__ __launch_bounds__(256) void k_connect_beta(ConnArgs a, int32_t *n1, c
     const int32_t bg = a.bidx[i];
     int64_t out = FILL ? rowptr[i] : 0;
     int n = 0;
-    scan_strings(
+    scan_strings<CONNECT_W>(
         a.bm_alpha, live ? a.gb[bg] : 0, live ? a.gb[bg + 1] : 0, ai, [](int d) { return d == 2 || d == 4; },
         [&](int32_t t0, uint32_t m) {
             if (!FILL) {
@@ -217,7 +158,7 @@ __global__ __launch_bounds__(256) void k_connect(ConnArgs a, const int32_t *n1, 
         ++held;
     };
     // beta-only: determinants with the same alpha string
-    scan_strings(
+    scan_strings<CONNECT_W>(
         a.sb, live ? a.ga[ag] : 0, live ? a.ga[ag + 1] : 0, bi, [](int d) { return d == 2 || d == 4; },
         [&](int32_t j0, uint32_t m) {
             found(m);
@@ -259,7 +200,7 @@ __global__ __launch_bounds__(256) void k_connect(ConnArgs a, const int32_t *n1, 
                 t1 = t0;
             }
         }
-        scan_strings(
+        scan_strings<CONNECT_W>(
             a.sb, t0, t1, bi, [](int d) { return d == 2; },
             [&](int32_t j0, uint32_t m) {
                 found(m);
@@ -274,77 +215,177 @@ __global__ __launch_bounds__(256) void k_connect(ConnArgs a, const int32_t *n1, 
     else if (live) counts[i] = n1[i] + n;
 }
 
-// Every coupling of a row by one wave, for sets with too few rows to fill the
-// chip one per lane (CONNECT_ROWS_MAX).  The lanes stride each group; the groups
-// one move away are looked up 64 at a time, one per lane, so that only a group's
-// strings are on the path of the loop.  Same order of the entries as above.
-template <bool FILL>
+// Hits of RW rows on their way to the matrix, a ring per row.
+template <int RW>
+struct RowQueue {
+    int32_t j[RW][128];
+    uint32_t str[RW][128], info[RW][128];
+};
+
+// Every coupling of RW rows by one wave, for sets with too few rows to fill the
+// chip one per lane (CONNECT_ROWS_MAX) and for listed rows, which share their
+// strings with few others of the list.  The lanes stride each group; the groups
+// one move away are looked up 64 at a time, one per lane, and the next group's
+// strings are on their way while one's are tested.  Rows of the wave with the same
+// alpha string are tested against a group's strings together.  Bound by the
+// instructions of a step, so hits, two or three per row and group, only go to a
+// queue: their descriptors are computed 64 at a time, and stored next to each
+// other (75,000 rows of 1e6, 1.2e7 couplings, counting / filling: row by row with
+// the descriptors in each step 0.54 / 0.85 ms, RW = 1 0.55 / 0.69, RW = 4 0.44 /
+// 0.64, RW = 8 0.58 / 1.03).
+// Same order of the entries as above.
+template <bool FILL, int RW>
 __global__ __launch_bounds__(256) void k_connect_rows(ConnArgs a, int64_t *counts, const int64_t *rowptr,
                                                       int32_t *col, uint32_t *desc) {
+    constexpr uint32_t ALPHA = 0xffffffffu, BETA = 0xfffffffeu;  // info of same-spin hits
+    __shared__ RowQueue<FILL ? RW : 1> queues[FILL ? 4 : 1];
+    RowQueue<FILL ? RW : 1> &queue = queues[FILL ? threadIdx.x >> 6 : 0];
     const int lane = threadIdx.x & 63;
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (i >= a.ndet) return;
-    const uint32_t ai = a.sa[i], bi = a.sb[i];
-    const int32_t ag = a.aidx[i], bg = a.bidx[i];
-    int64_t out = FILL ? rowptr[i] : 0;
+    const int64_t t0 = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6)) * (int64_t)RW;
+    if (t0 >= a.ndet) return;
     const uint64_t below = ((uint64_t)1 << lane) - 1;
-    auto emit = [&](bool keep, int32_t j, uint32_t d) {
-        const uint64_t m = __ballot(keep);
-        if (FILL && keep) {
-            const int64_t k = out + __popcll(m & below);
-            col[k] = j;
-            desc[k] = d;
+    int64_t row[RW], out[RW];
+    uint32_t ai[RW], bi[RW];
+    int32_t ag[RW], bg[RW], held[RW], head[RW];
+    int64_t n[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const bool live = t0 + r < a.ndet;
+        row[r] = live ? (a.rows ? (int64_t)a.rows[t0 + r] : t0 + r) : -1;
+        const int64_t i = live ? row[r] : 0;
+        ai[r] = a.sa[i];
+        bi[r] = a.sb[i];
+        ag[r] = live ? a.aidx[i] : -1;
+        bg[r] = a.bidx[i];
+        out[r] = FILL ? rowptr[i] : 0;
+        n[r] = 0;
+        held[r] = head[r] = 0;
+    }
+    auto flush = [&](int r, int cnt) {  // the oldest cnt hits of row r
+        __builtin_amdgcn_wave_barrier();
+        if (lane < cnt) {
+            const int at = (head[r] + lane) & 127;
+            const int32_t j = queue.j[r][at];
+            const uint32_t s = queue.str[r][at], inf = queue.info[r][at];
+            uint32_t d;
+            if (inf == ALPHA) d = same_spin_desc(ai[r], s, HINQS_EXC_1A, HINQS_EXC_2AA);
+            else if (inf == BETA) d = same_spin_desc(bi[r], s, HINQS_EXC_1B, HINQS_EXC_2BB);
+            else d = ab_desc(inf & 31, (inf >> 5) & 31, (inf >> 10) & 1u, bi[r], s);
+            col[out[r] + lane] = inf == ALPHA ? a.bperm[j] : j;
+            desc[out[r] + lane] = d;
         }
-        out += __popcll(m);
+        __builtin_amdgcn_wave_barrier();
+        out[r] += cnt;
+        held[r] -= cnt;
+        head[r] = (head[r] + cnt) & 127;
     };
-    for (int32_t u0 = a.gb[bg], e = a.gb[bg + 1]; u0 < e; u0 += 64) {
-        const int32_t u = u0 + lane;
-        const uint32_t aj = u < e ? a.bm_alpha[u] : ai;
-        const int d = popc32(ai ^ aj);
-        const bool k = d == 2 || d == 4;
-        emit(k, FILL && k ? a.bperm[u] : 0, FILL && k ? same_spin_desc(ai, aj, HINQS_EXC_1A, HINQS_EXC_2AA) : 0u);
-    }
-    for (int32_t j0 = a.ga[ag], e = a.ga[ag + 1]; j0 < e; j0 += 64) {
-        const int32_t j = j0 + lane;
-        const uint32_t bj = j < e ? a.sb[j] : bi;
-        const int d = popc32(bi ^ bj);
-        const bool k = d == 2 || d == 4;
-        emit(k, j, FILL && k ? same_spin_desc(bi, bj, HINQS_EXC_1B, HINQS_EXC_2BB) : 0u);
-    }
-    const int64_t lbase = (int64_t)ag * a.alink_max;
-    const int32_t le = a.alink_cnt[ag];
-    for (int32_t l0 = 0; l0 < le; l0 += 64) {
-        int32_t lo = 0, hi = 0;
-        uint32_t info = 0;
-        if (l0 + lane < le) {
-            const int32_t tgt = a.alink[lbase + l0 + lane];
-            info = a.alink_info[lbase + l0 + lane];
-            lo = a.ga[tgt];
-            hi = a.ga[tgt + 1];
+    auto emit = [&](int r, bool keep, int32_t j, uint32_t s, uint32_t inf) {
+        const uint64_t m = __ballot(keep);
+        if (!FILL) {
+            n[r] += __popcll(m);
+        } else if (m) {
+            if (keep) {
+                const int at = (head[r] + held[r] + __popcll(m & below)) & 127;
+                queue.j[r][at] = j;
+                queue.str[r][at] = s;
+                queue.info[r][at] = inf;
+            }
+            held[r] += __popcll(m);
+            if (held[r] >= 64) flush(r, 64);
         }
-        const int nl = min(64, le - l0);
-        // the first 64 strings of the next group are in flight while this one's are tested
-        int32_t t0 = __shfl(lo, 0, 64), t1 = __shfl(hi, 0, 64);
-        uint32_t b0 = t0 + lane < t1 ? a.sb[t0 + lane] : bi;
-        for (int l = 0; l < nl; ++l) {
-            const int32_t s0 = t0, s1 = t1;
-            uint32_t bj = b0;
-            const uint32_t inf = __shfl(info, l, 64);
-            if (l + 1 < nl) {
-                t0 = __shfl(lo, l + 1, 64);
-                t1 = __shfl(hi, l + 1, 64);
-                b0 = t0 + lane < t1 ? a.sb[t0 + lane] : bi;
-            }
-            for (int32_t j0 = s0;;) {
-                const bool k = popc32(bi ^ bj) == 2;
-                emit(k, j0 + lane, FILL && k ? ab_desc(inf & 31, (inf >> 5) & 31, (inf >> 10) & 1u, bi, bj) : 0u);
-                j0 += 64;
-                if (j0 >= s1) break;
-                bj = j0 + lane < s1 ? a.sb[j0 + lane] : bi;
-            }
+    };
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        if (ag[r] < 0) continue;
+        for (int32_t u0 = a.gb[bg[r]], e = a.gb[bg[r] + 1]; u0 < e; u0 += 64) {
+            const int32_t u = u0 + lane;
+            const uint32_t aj = u < e ? a.bm_alpha[u] : ai[r];
+            const int d = popc32(ai[r] ^ aj);
+            emit(r, d == 2 || d == 4, u, aj, ALPHA);
         }
     }
-    if (!FILL && lane == 0) counts[i] = out;
+    // runs of rows with one alpha string
+    for (int r0 = 0; r0 < RW;) {
+        int32_t g = -1;
+        bool in[RW];
+        int next = RW;
+#pragma unroll
+        for (int r = RW - 1; r >= 0; --r)
+            if (r == r0) g = ag[r];
+        if (g < 0) break;
+#pragma unroll
+        for (int r = RW - 1; r >= 0; --r)
+            if (r > r0 && ag[r] != g) next = r;
+#pragma unroll
+        for (int r = 0; r < RW; ++r) in[r] = r >= r0 && r < next;
+        for (int32_t j0 = a.ga[g], e = a.ga[g + 1]; j0 < e; j0 += 64) {
+            const int32_t j = j0 + lane;
+            const uint32_t sj = j < e ? a.sb[j] : 0u;
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+                if (in[r]) {
+                    const int d = popc32(bi[r] ^ sj);
+                    emit(r, j < e && (d == 2 || d == 4), j, sj, BETA);
+                }
+        }
+        const int64_t lbase = (int64_t)g * a.alink_max;
+        const int32_t le = a.alink_cnt[g];
+        for (int32_t l0 = 0; l0 < le; l0 += 64) {
+            int32_t lo = 0, hi = 0;
+            uint32_t info = 0;
+            if (l0 + lane < le) {
+                const int32_t tgt = a.alink[lbase + l0 + lane];
+                info = a.alink_info[lbase + l0 + lane];
+                lo = a.ga[tgt];
+                hi = a.ga[tgt + 1];
+            }
+            const int nl = min(64, le - l0);
+            // the first 64 strings of the next group are in flight while this one's are tested
+            int32_t s0 = __builtin_amdgcn_readlane(lo, 0), s1 = __builtin_amdgcn_readlane(hi, 0);
+            uint32_t b0 = s0 + lane < s1 ? a.sb[s0 + lane] : 0u;
+            for (int l = 0; l < nl; ++l) {
+                const int32_t g0 = s0, g1 = s1;
+                uint32_t bj = b0;
+                const uint32_t inf = __builtin_amdgcn_readlane(info, l) & 0x7ffu;
+                if (l + 1 < nl) {
+                    s0 = __builtin_amdgcn_readlane(lo, l + 1);
+                    s1 = __builtin_amdgcn_readlane(hi, l + 1);
+                    b0 = s0 + lane < s1 ? a.sb[s0 + lane] : 0u;
+                }
+                for (int32_t j0 = g0;;) {
+                    const bool ok = j0 + lane < g1;
+#pragma unroll
+                    for (int r = 0; r < RW; ++r)
+                        if (in[r]) emit(r, ok && popc32(bi[r] ^ bj) == 2, j0 + lane, bj, inf);
+                    j0 += 64;
+                    if (j0 >= g1) break;
+                    bj = j0 + lane < g1 ? a.sb[j0 + lane] : 0u;
+                }
+            }
+        }
+        r0 = next;
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        if (row[r] < 0) continue;
+        if (FILL) flush(r, held[r]);
+        else if (lane == 0) counts[row[r]] = n[r];
+    }
+}
+
+// RW = 4 needs enough rows to leave several waves per SIMD (both passes of a whole
+// set, RW = 1 / 4: 20,000 rows 142 / 151 us, 60,000 rows 375 / 298 us).
+constexpr int64_t CONNECT_RW4_MIN = 32768;
+template <bool FILL>
+void launch_connect_rows(hipStream_t s, const ConnArgs &a, int64_t *counts, const int64_t *rowptr, int32_t *col,
+                         uint32_t *desc) {
+    if (a.ndet >= CONNECT_RW4_MIN)
+        hipLaunchKernelGGL((k_connect_rows<FILL, 4>), dim3(grid_for((a.ndet + 3) / 4 * 64, 256)), dim3(256), 0, s, a,
+                           counts, rowptr, col, desc);
+    else
+        hipLaunchKernelGGL((k_connect_rows<FILL, 1>), dim3(grid_for(a.ndet * 64, 256)), dim3(256), 0, s, a, counts,
+                           rowptr, col, desc);
+    HQ_LAUNCH_CHECK();
 }
 
 // bounds[x] = first row whose couplings start at or after x * total / 8 (x = 0..8).
@@ -385,10 +426,11 @@ __global__ void k_caller_copy(int64_t n, const int64_t *rowptr, const int32_t *c
     }
 }
 
-// One wave per row up to here: with one row per lane, fewer rows leave most
-// of the chip idle (both passes, one row per lane against one wave per row: 5,000 rows
-// 166 / 82 us, 20,000 558 / 185, 60,000 797 / 484; 100,000 506 / 730, 200,000
-// 909 / 1608, 1e6 5.7 / 16.3 ms).
+// One wave for a row, or four, up to here: with one row per lane, fewer rows leave
+// most of the chip idle, and past it groups of thousands of rows are looked up
+// (both passes, one row per lane against this: 5,000 rows 166 / 70 us, 20,000
+// 558 / 147, 60,000 797 / 298; 100,000 513 / 481, 200,000 907 / 899 and, with
+// longer groups, 2074 / 1673; 3 groups of 60,000 rows 8.3 / 16.7 ms).
 constexpr int64_t CONNECT_ROWS_MAX = 65536;
 
 int32_t env_i32(const char *name, int32_t dflt) {
@@ -397,6 +439,14 @@ int32_t env_i32(const char *name, int32_t dflt) {
 }
 
 }  // namespace
+
+void connect_listed_rows(Ctx &c, const int32_t *rows, int64_t nrows, int64_t *counts, bool fill) {
+    const ConnArgs a{nrows,      c.sa.p,        c.sb.p,        c.aidx.p,    c.bidx.p, c.ga.p, c.gb.p,
+                     c.bperm.p,  c.bm_alpha.p,  c.alink_ptr.p, c.alink.p,   c.alink_info.p,
+                     c.alink_max, c.norb,       0,             rows};
+    if (fill) launch_connect_rows<true>(c.stream, a, nullptr, c.rowptr.p, c.col.p, c.desc.p);
+    else launch_connect_rows<false>(c.stream, a, counts, nullptr, nullptr, nullptr);
+}
 
 void export_connectivity(Ctx &c, int64_t *rowptr_c, int32_t *col_c, uint32_t *desc_c) {
     hipStream_t s = c.stream;
@@ -445,14 +495,13 @@ void build_connectivity(Ctx &c, bool xcd_rows) {
     auto &n1 = c.bs.gidx;  // alpha-only couplings per row (free once the tables are built)
     counts.ensure(n + 1);
     n1.ensure(n);
-    // the per-lane kernel keeps the lookup of very long groups (a set of at most
-    // CONNECT_ROWS_MAX rows has one only if HINQS_CONNECT_LOOKUP_MIN asks)
+    // very long groups are scanned too where a wave takes a row (5 alpha strings with
+    // 12,870 rows each: 2.4 ms, looked up one row per lane 4.2), unless
+    // HINQS_CONNECT_LOOKUP_MIN asks for the lookup
     const bool by_rows = n <= CONNECT_ROWS_MAX && env_i32("HINQS_CONNECT_LOOKUP_MIN", 0) == 0;
-    const dim3 g(grid_for(by_rows ? 64 * n : n, 256)), b(256);
+    const dim3 g(grid_for(n, 256)), b(256);
     if (by_rows) {
-        hipLaunchKernelGGL(k_connect_rows<false>, g, b, 0, s, a, counts.p, (const int64_t *)nullptr,
-                           (int32_t *)nullptr, (uint32_t *)nullptr);
-        HQ_LAUNCH_CHECK();
+        launch_connect_rows<false>(s, a, counts.p, nullptr, nullptr, nullptr);
     } else {
         hipLaunchKernelGGL(k_connect_beta<false>, g, b, 0, s, a, n1.p, (const int64_t *)nullptr, (int32_t *)nullptr,
                            (uint32_t *)nullptr);
@@ -472,8 +521,7 @@ void build_connectivity(Ctx &c, bool xcd_rows) {
     c.col.ensure(nnz);
     c.desc.ensure(nnz);
     if (by_rows) {
-        hipLaunchKernelGGL(k_connect_rows<true>, g, b, 0, s, a, (int64_t *)nullptr, c.rowptr.p, c.col.p, c.desc.p);
-        HQ_LAUNCH_CHECK();
+        launch_connect_rows<true>(s, a, nullptr, c.rowptr.p, c.col.p, c.desc.p);
     } else {
         hipLaunchKernelGGL(k_connect_beta<true>, g, b, 0, s, a, (int32_t *)nullptr, c.rowptr.p, c.col.p, c.desc.p);
         HQ_LAUNCH_CHECK();

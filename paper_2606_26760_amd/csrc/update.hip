@@ -17,6 +17,7 @@
 #include <chrono>
 
 #include "common.hpp"
+#include "enumerate.hpp"
 
 namespace hinqs {
 
@@ -60,14 +61,18 @@ __global__ void k_new_list(const int32_t *keep, const int32_t *newidx, const int
 }
 
 // o2n[old sorted position] = new sorted position or -1; n2o the inverse (-1
-// for appended rows, filled beforehand).
-__global__ void k_maps(const int32_t *perm_old, const int32_t *keep, const int32_t *newidx, const int32_t *inv_new,
-                       int64_t n_old, int32_t *o2n, int32_t *n2o) {
+// for appended rows, filled beforehand); bit p of kept_bits: p is kept.
+__global__ __launch_bounds__(256) void k_maps(const int32_t *perm_old, const int32_t *keep, const int32_t *newidx, const int32_t *inv_new,
+                       int64_t n_old, int32_t *o2n, int32_t *n2o, uint32_t *kept_bits) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_old) return;
-    const int32_t ci = perm_old[p];
-    const int32_t r = keep[ci] ? inv_new[newidx[ci]] : -1;
-    o2n[p] = r;
+    int32_t r = -1;
+    if (p < n_old) {
+        const int32_t ci = perm_old[p];
+        if (keep[ci]) r = inv_new[newidx[ci]];
+        o2n[p] = r;
+    }
+    const uint64_t m = __ballot(r >= 0);
+    if (p < n_old && (threadIdx.x & 31) == 0) kept_bits[p >> 5] = (uint32_t)(m >> (threadIdx.x & 32));
     if (r >= 0) n2o[r] = (int32_t)p;
 }
 
@@ -128,189 +133,143 @@ struct CrossArgs {
     const int32_t *amap;          // A sorted position -> B' sorted position
 };
 
+constexpr int CROSS_W = 16;  // strings per step: A's groups are short
+
 // Counting pass (FILL = false): for each kept row, cnt[r] = kept[r] (its old
 // entries whose column survives) + its couplings to A.  Filling pass: the
-// couplings to A, written after the kept entries.
+// couplings to A, written after the kept entries through the wave's buffer
+// (1e6 rows, 1e5 appended, 1.5e7 couplings, counting / filling: 0.31 / 0.59 ms; with
+// loads per lane and every store on its own 0.35 / 0.67 ms).
 template <bool FILL>
 __global__ __launch_bounds__(256) void k_cross(CrossArgs a, int64_t *cnt, int64_t *kept, const int64_t *rowptr,
                                                int32_t *col, uint32_t *desc) {
+    __shared__ EmitBuf bufs[FILL ? 4 : 1];
+    EmitBuf &buf = bufs[FILL ? threadIdx.x >> 6 : 0];
+    const int lane = threadIdx.x & 63;
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= a.n) return;
-    const int32_t p = a.n2o[r];
-    if (p < 0) return;
-    const int64_t nk = kept[r];
-    int64_t out = FILL ? rowptr[r] + nk : 0;
-    int64_t n = 0;
+    const bool live = r < a.n && a.n2o[r] >= 0;
+    const int64_t nk = live ? kept[r] : 0;
     if (!a.has_a) {
-        if (!FILL) cnt[r] = nk;
+        if (!FILL && live) cnt[r] = nk;
         return;
     }
-    const uint32_t ai = a.sa[r], bi = a.sb[r];
-    const int32_t gbA = a.bsame[a.bidx[r]];
-    // group scans: SCAN_W candidates tested branch-free, hits emitted from the mask
-    if (gbA >= 0) {  // same beta string, alpha one or two moves away
-        for (int32_t u0 = a.gb_a[gbA], e = a.gb_a[gbA + 1]; u0 < e; u0 += SCAN_W) {
-            uint32_t m = 0;
-#pragma unroll
-            for (int v = 0; v < SCAN_W; ++v) {
-                const uint32_t aj = u0 + v < e ? a.bm_alpha_a[u0 + v] : ai;
-                const int d = popc32(ai ^ aj);
-                m |= (d == 2 || d == 4) ? 1u << v : 0u;
-            }
-            if (FILL) {
+    const int64_t at = r < a.n ? r : 0;
+    const uint32_t ai = a.sa[at], bi = a.sb[at];
+    const int32_t ag = a.aidx[at];
+    const int32_t gbA = live ? a.bsame[a.bidx[at]] : -1, gaA = live ? a.asame[ag] : -1;
+    int64_t out = FILL && live ? rowptr[r] + nk : 0;
+    int held = 0;
+    int64_t n = 0;
+    auto found = [&](uint32_t m) {
+        if (!FILL) n += popc32(m);
+        else if (__any(held + popc32(m) > EMIT_CAP)) emit_flush(buf, out, held, lane, col, desc, a.amap);
+    };
+    auto put = [&](int32_t j, uint32_t d) {  // j: sorted position in A
+        buf.col[lane * EMIT_STRIDE + held] = j;
+        buf.desc[lane * EMIT_STRIDE + held] = d;
+        ++held;
+    };
+    // same beta string, alpha one or two moves away
+    scan_strings<CROSS_W>(
+        a.bm_alpha_a, gbA >= 0 ? a.gb_a[gbA] : 0, gbA >= 0 ? a.gb_a[gbA + 1] : 0, ai,
+        [](int d) { return d == 2 || d == 4; },
+        [&](int32_t u0, uint32_t m) {
+            found(m);
+            if (FILL)
                 for (; m; m &= m - 1) {
                     const int32_t u = u0 + lowbit(m);
-                    col[out] = a.amap[a.bperm_a[u]];
-                    desc[out] = same_spin_desc(ai, a.bm_alpha_a[u], HINQS_EXC_1A, HINQS_EXC_2AA);
-                    ++out;
+                    put(a.bperm_a[u], same_spin_desc(ai, a.bm_alpha_a[u], HINQS_EXC_1A, HINQS_EXC_2AA));
                 }
-            } else {
-                n += popc32(m);
-            }
-        }
-    }
-    const int32_t ag = a.aidx[r];
-    const int32_t gaA = a.asame[ag];
-    if (gaA >= 0) {  // same alpha string, beta one or two moves away
-        for (int32_t j0 = a.ga_a[gaA], e = a.ga_a[gaA + 1]; j0 < e; j0 += SCAN_W) {
-            uint32_t m = 0;
-#pragma unroll
-            for (int v = 0; v < SCAN_W; ++v) {
-                const uint32_t bj = j0 + v < e ? a.sb_a[j0 + v] : bi;
-                const int d = popc32(bi ^ bj);
-                m |= (d == 2 || d == 4) ? 1u << v : 0u;
-            }
-            if (FILL) {
+        });
+    // same alpha string, beta one or two moves away
+    scan_strings<CROSS_W>(
+        a.sb_a, gaA >= 0 ? a.ga_a[gaA] : 0, gaA >= 0 ? a.ga_a[gaA + 1] : 0, bi,
+        [](int d) { return d == 2 || d == 4; },
+        [&](int32_t j0, uint32_t m) {
+            found(m);
+            if (FILL)
                 for (; m; m &= m - 1) {
                     const int32_t j = j0 + lowbit(m);
-                    col[out] = a.amap[j];
-                    desc[out] = same_spin_desc(bi, a.sb_a[j], HINQS_EXC_1B, HINQS_EXC_2BB);
-                    ++out;
+                    put(j, same_spin_desc(bi, a.sb_a[j], HINQS_EXC_1B, HINQS_EXC_2BB));
                 }
-            } else {
-                n += popc32(m);
-            }
+        });
+    // one move in each spin
+    const int32_t le = live ? a.xcnt[ag] : 0;
+    for (int32_t l = 0; __any(l < le); ++l) {
+        int32_t t0 = 0, t1 = 0;
+        int ha = 0, pa = 0;
+        uint32_t npar = 0;
+        if (l < le) {
+            const int32_t tg = a.xlink[(int64_t)ag * a.maxl + l];
+            const uint32_t aj = a.ua_a[tg];
+            ha = lowbit(aj & ~ai);  // the alpha move of this group
+            pa = lowbit(ai & ~aj);
+            npar = single_parity(aj, ha, pa);
+            t0 = a.ga_a[tg];
+            t1 = a.ga_a[tg + 1];
         }
+        scan_strings<CROSS_W>(
+            a.sb_a, t0, t1, bi, [](int d) { return d == 2; },
+            [&](int32_t j0, uint32_t m) {
+                found(m);
+                if (FILL)
+                    for (; m; m &= m - 1) {
+                        const int32_t j = j0 + lowbit(m);
+                        put(j, ab_desc(ha, pa, npar, bi, a.sb_a[j]));
+                    }
+            });
     }
-    for (int32_t l = 0, le = a.xcnt[ag]; l < le; ++l) {  // one move in each spin
-        const int32_t tg = a.xlink[(int64_t)ag * a.maxl + l];
-        const uint32_t aj = a.ua_a[tg];
-        const int ha = lowbit(aj & ~ai), pa = lowbit(ai & ~aj);  // the alpha move of this group
-        const uint32_t npar = single_parity(aj, ha, pa);
-        for (int32_t j0 = a.ga_a[tg], e = a.ga_a[tg + 1]; j0 < e; j0 += SCAN_W) {
-            uint32_t m = 0;
-#pragma unroll
-            for (int v = 0; v < SCAN_W; ++v) {
-                const uint32_t bj = j0 + v < e ? a.sb_a[j0 + v] : bi;
-                m |= popc32(bi ^ bj) == 2 ? 1u << v : 0u;
-            }
-            if (FILL) {
-                for (; m; m &= m - 1) {
-                    const int32_t j = j0 + lowbit(m);
-                    col[out] = a.amap[j];
-                    desc[out] = ab_desc(ha, pa, npar, bi, a.sb_a[j]);
-                    ++out;
-                }
-            } else {
-                n += popc32(m);
-            }
-        }
-    }
-    if (!FILL) cnt[r] = nk + n;
+    if (FILL) emit_flush(buf, out, held, lane, col, desc, a.amap);
+    else if (live) cnt[r] = nk + n;
 }
 
-// One wave per old row: kept[o2n[p]] = number of its entries whose column survives.
-__global__ void k_kept_count(int64_t n_old, const int32_t *o2n, const int64_t *rowptr_old, const int32_t *col_old,
-                             int64_t *kept) {
+constexpr int COPY_U = 4;  // entries of a row per lane in flight
+
+// One wave per old row: kept[o2n[p]] = number of its entries whose column
+// survives.  Bound by the look-ups, of which a CU gets about one line per 6 clk from
+// its L2: one bit per old row instead of its new position leaves most of them in
+// the CU's own cache (1.56e8 couplings: 0.45 ms, from o2n 0.67 ms; reading the
+// evicted rows only and decrementing their columns' counts took 0.45 ms for 5 to
+// 10 % evicted and more than the full pass beyond).
+__global__ __launch_bounds__(256) void k_kept_count(int64_t n_old, const int32_t *__restrict__ o2n,
+                                                    const uint32_t *__restrict__ kept_bits,
+                                                    const int64_t *__restrict__ rowptr_old,
+                                                    const int32_t *__restrict__ col_old, int64_t *__restrict__ kept) {
     const int lane = threadIdx.x & 63;
     const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     if (p >= n_old) return;
     const int32_t r = o2n[p];
     if (r < 0) return;
+    const int64_t e = rowptr_old[p + 1];
     int64_t n = 0;
-    for (int64_t q = rowptr_old[p] + lane, e = rowptr_old[p + 1]; q < e; q += 64) n += o2n[col_old[q]] >= 0;
-    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
+    for (int64_t q0 = rowptr_old[p]; q0 < e; q0 += 64 * COPY_U) {
+        int32_t c[COPY_U];
+        uint32_t w[COPY_U];
+#pragma unroll
+        for (int u = 0; u < COPY_U; ++u) c[u] = q0 + 64 * u + lane < e ? col_old[q0 + 64 * u + lane] : -1;
+#pragma unroll
+        for (int u = 0; u < COPY_U; ++u) w[u] = c[u] >= 0 ? kept_bits[c[u] >> 5] >> (c[u] & 31) : 0u;
+#pragma unroll
+        for (int u = 0; u < COPY_U; ++u) n += __popcll(__ballot(w[u] & 1u));
+    }
     if (lane == 0) kept[r] = n;
 }
 
-struct RowArgs {
-    const int32_t *rows;  // rows to enumerate (sorted positions, ascending)
-    int64_t nrows;
-    const uint32_t *sa, *sb, *bm_alpha, *alink_info;
-    const int32_t *aidx, *bidx, *ga, *gb, *bperm, *alink_cnt, *alink;
-    int alink_max;
-};
-
-// Ballot-compacted append of the lanes with `keep` set, in lane order.
-struct WaveOut {
-    int64_t pos;  // next output slot (uniform)
-    int64_t n;    // entries so far (uniform)
-};
-
-template <bool FILL>
-__device__ inline void wave_emit(bool keep, int32_t colv, uint32_t descv, int lane, WaveOut &o, int32_t *col,
-                                 uint32_t *desc) {
-    const uint64_t m = __ballot(keep);
-    if (FILL && keep) {
-        const int64_t k = o.pos + __popcll(m & ((1ull << lane) - 1ull));
-        col[k] = colv;
-        desc[k] = descv;
-    }
-    o.pos += __popcll(m);
-    o.n += __popcll(m);
-}
-
-// Couplings of the listed rows against the whole set, one wave per row
-// (lanes stride each group), in the same order as the one-thread-per-row
-// enumerator: beta group, alpha group, then the linked alpha groups.  Used
-// for appended rows, which are too scattered for rows sharing alpha strings
-// in one wave.
-template <bool FILL>
-__global__ __launch_bounds__(256) void k_rows_wave(RowArgs a, int64_t *counts, const int64_t *rowptr, int32_t *col,
-                                                   uint32_t *desc) {
-    const int lane = threadIdx.x & 63;
-    const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (t >= a.nrows) return;
-    const int64_t i = a.rows[t];
-    const uint32_t ai = a.sa[i], bi = a.sb[i];
-    const int32_t ag = a.aidx[i], bg = a.bidx[i];
-    WaveOut o{FILL ? rowptr[i] : 0, 0};
-    for (int32_t u0 = a.gb[bg], e = a.gb[bg + 1]; u0 < e; u0 += 64) {
-        const int32_t u = u0 + lane;
-        const uint32_t aj = u < e ? a.bm_alpha[u] : ai;
-        const int d = popc32(ai ^ aj);
-        const bool k = d == 2 || d == 4;
-        wave_emit<FILL>(k, k ? a.bperm[u] : 0, k ? same_spin_desc(ai, aj, HINQS_EXC_1A, HINQS_EXC_2AA) : 0u, lane, o,
-                        col, desc);
-    }
-    for (int32_t j0 = a.ga[ag], e = a.ga[ag + 1]; j0 < e; j0 += 64) {
-        const int32_t j = j0 + lane;
-        const uint32_t bj = j < e ? a.sb[j] : bi;
-        const int d = popc32(bi ^ bj);
-        const bool k = d == 2 || d == 4;
-        wave_emit<FILL>(k, j, k ? same_spin_desc(bi, bj, HINQS_EXC_1B, HINQS_EXC_2BB) : 0u, lane, o, col, desc);
-    }
-    const int64_t lbase = (int64_t)ag * a.alink_max;
-    for (int32_t l = 0, le = a.alink_cnt[ag]; l < le; ++l) {
-        const int32_t tgt = a.alink[lbase + l];
-        const uint32_t info = a.alink_info[lbase + l];
-        const int ha = info & 31, pa = (info >> 5) & 31;
-        const uint32_t npar = (info >> 10) & 1u;
-        for (int32_t j0 = a.ga[tgt], e = a.ga[tgt + 1]; j0 < e; j0 += 64) {
-            const int32_t j = j0 + lane;
-            const uint32_t bj = j < e ? a.sb[j] : bi;
-            const bool k = popc32(bi ^ bj) == 2;
-            wave_emit<FILL>(k, j, k ? ab_desc(ha, pa, npar, bi, bj) : 0u, lane, o, col, desc);
-        }
-    }
-    if (!FILL && lane == 0) counts[i] = o.n;
-}
-
 // One wave per old row: copy its entries whose column survives (order kept)
-// into the B' row, with remapped columns and their values.
-__global__ void k_copy_kept(int64_t n_old, const int32_t *o2n, const int64_t *rowptr_old, const int32_t *col_old,
-                            const uint32_t *desc_old, const double *val_old, const float *val32_old,
-                            const int64_t *rowptr, int32_t *col, uint32_t *desc, double *val, float *val32) {
+// into the B' row, with remapped columns and their values.  Bound by memory, 36
+// bytes per entry, and by the look-ups of o2n: COPY_U entries per lane are read
+// before the first is written, values along with the columns, so a row of up to
+// 64 COPY_U entries waits for memory twice (1.56e8 couplings, 95 % kept: 1.77 ms;
+// one entry per lane at a time, with the FP32 values read as well, 2.0 ms; several
+// rows per wave with the next one's entries on their way 2.0 ms).
+__global__ __launch_bounds__(256) void k_copy_kept(int64_t n_old, const int32_t *__restrict__ o2n,
+                                                   const int64_t *__restrict__ rowptr_old,
+                                                   const int32_t *__restrict__ col_old,
+                                                   const uint32_t *__restrict__ desc_old,
+                                                   const double *__restrict__ val_old,
+                                                   const int64_t *__restrict__ rowptr, int32_t *__restrict__ col,
+                                                   uint32_t *__restrict__ desc, double *__restrict__ val,
+                                                   float *__restrict__ val32) {
     const int lane = threadIdx.x & 63;
     const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     if (p >= n_old) return;
@@ -318,18 +277,32 @@ __global__ void k_copy_kept(int64_t n_old, const int32_t *o2n, const int64_t *ro
     if (r < 0) return;
     int64_t dst = rowptr[r];
     const int64_t b = rowptr_old[p], e = rowptr_old[p + 1];
-    for (int64_t q0 = b; q0 < e; q0 += 64) {
-        const int64_t q = q0 + lane;
-        const int32_t nc = q < e ? o2n[col_old[q]] : -1;
-        const uint64_t m = __ballot(nc >= 0);
-        if (nc >= 0) {
-            const int64_t k = dst + __popcll(m & ((1ull << lane) - 1ull));
-            col[k] = nc;
-            desc[k] = desc_old[q];
-            val[k] = val_old[q];
-            val32[k] = val32_old[q];
+    for (int64_t q0 = b; q0 < e; q0 += 64 * COPY_U) {
+        int32_t c[COPY_U];
+        uint32_t d[COPY_U];
+        double v[COPY_U];
+#pragma unroll
+        for (int u = 0; u < COPY_U; ++u) {
+            const int64_t q = q0 + 64 * u + lane;
+            const bool ok = q < e;
+            c[u] = ok ? col_old[q] : -1;
+            d[u] = ok ? desc_old[q] : 0u;
+            v[u] = ok ? val_old[q] : 0.0;
         }
-        dst += __popcll(m);
+#pragma unroll
+        for (int u = 0; u < COPY_U; ++u) c[u] = c[u] >= 0 ? o2n[c[u]] : -1;
+#pragma unroll
+        for (int u = 0; u < COPY_U; ++u) {
+            const uint64_t m = __ballot(c[u] >= 0);
+            if (c[u] >= 0) {
+                const int64_t k = dst + __popcll(m & ((1ull << lane) - 1ull));
+                col[k] = c[u];
+                desc[k] = d[u];
+                val[k] = v[u];
+                val32[k] = (float)v[u];
+            }
+            dst += __popcll(m);
+        }
     }
 }
 
@@ -500,28 +473,27 @@ void update_determinants(Ctx &c, int64_t n_evict, const int32_t *evict, int64_t 
     DBuf<int32_t> col_old;
     DBuf<uint32_t> desc_old;
     DBuf<double> val_old;
-    DBuf<float> val32_old;
     rowptr_old.swap(c.rowptr);
     col_old.swap(c.col);
     desc_old.swap(c.desc);
     val_old.swap(c.val);
-    val32_old.swap(c.val32);
 
     DBuf<int32_t> o2n, n2o;
+    DBuf<uint32_t> kept_bits;
     o2n.ensure(n_old);
+    kept_bits.ensure((n_old + 31) / 32);
     n2o.ensure(n_new);
     hipLaunchKernelGGL(k_fill_i32v, dim3(grid_for(n_new, 256)), dim3(256), 0, s, n2o.p, n_new, -1);
     HQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_maps, dim3(grid_for(n_old, 256)), dim3(256), 0, s, t.perm.p, keep.p, newidx.p, c.inv.p,
-                       n_old, o2n.p, n2o.p);
-    HQ_LAUNCH_CHECK();
-
     // ---- counts: kept rows (old entries + couplings to A), appended rows (full)
     DBuf<int64_t> cnt, kept, rowptr;
     cnt.ensure(n_new + 1);
     kept.ensure(n_new);
     HQ_CHECK(hipMemsetAsync(kept.p, 0, sizeof(int64_t) * n_new, s));
     HQ_CHECK(hipMemsetAsync(cnt.p + n_new, 0, sizeof(int64_t), s));
+    hipLaunchKernelGGL(k_maps, dim3(grid_for(n_old, 256)), dim3(256), 0, s, t.perm.p, keep.p, newidx.p, c.inv.p,
+                       n_old, o2n.p, n2o.p, kept_bits.p);
+    HQ_LAUNCH_CHECK();
     DBuf<int32_t> asame, bsame, xcnt, xlink, amap;
     const int maxl = std::max(1, c.na * (norb - c.na));
     CrossArgs ca{};
@@ -560,20 +532,14 @@ void update_determinants(Ctx &c, int64_t n_evict, const int32_t *evict, int64_t 
         ca.bperm_a = ta.bperm.p;
         ca.amap = amap.p;
     }
-    hipLaunchKernelGGL(k_kept_count, dim3(grid_for(n_old * 64, 256)), dim3(256), 0, s, n_old, o2n.p, rowptr_old.p,
-                       col_old.p, kept.p);
+    hipLaunchKernelGGL(k_kept_count, dim3(grid_for(n_old * 64, 256)), dim3(256), 0, s, n_old, o2n.p, kept_bits.p,
+                       rowptr_old.p, col_old.p, kept.p);
     HQ_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_cross<false>, dim3(grid_for(n_new, 256)), dim3(256), 0, s, ca, cnt.p, kept.p,
                        (const int64_t *)nullptr, (int32_t *)nullptr, (uint32_t *)nullptr);
     HQ_LAUNCH_CHECK();
     // appended rows in ascending sorted position (amap is ascending: A and B' share the key order)
-    const RowArgs ra{amap.p,    n_add,     c.sa.p,    c.sb.p,   c.bm_alpha.p, c.alink_info.p, c.aidx.p,
-                     c.bidx.p,  c.ga.p,    c.gb.p,    c.bperm.p, c.alink_ptr.p, c.alink.p,    c.alink_max};
-    if (n_add > 0) {
-        hipLaunchKernelGGL(k_rows_wave<false>, dim3(grid_for(n_add * 64, 256)), dim3(256), 0, s, ra, cnt.p,
-                           (const int64_t *)nullptr, (int32_t *)nullptr, (uint32_t *)nullptr);
-        HQ_LAUNCH_CHECK();
-    }
+    if (n_add > 0) connect_listed_rows(c, amap.p, n_add, cnt.p, false);
     rowptr.ensure(n_new + 1);
     exclusive_scan_i64(s, cnt.p, rowptr.p, n_new + 1, c.work);
     int64_t nnz = 0;
@@ -589,16 +555,14 @@ void update_determinants(Ctx &c, int64_t n_evict, const int32_t *evict, int64_t 
     c.val.ensure(nnz);
     c.val32.ensure(nnz);
     hipLaunchKernelGGL(k_copy_kept, dim3(grid_for(n_old * 64, 256)), dim3(256), 0, s, n_old, o2n.p, rowptr_old.p,
-                       col_old.p, desc_old.p, val_old.p, val32_old.p, c.rowptr.p, c.col.p, c.desc.p, c.val.p,
+                       col_old.p, desc_old.p, val_old.p, c.rowptr.p, c.col.p, c.desc.p, c.val.p,
                        c.val32.p);
     HQ_LAUNCH_CHECK();
     if (n_add > 0) {
         hipLaunchKernelGGL(k_cross<true>, dim3(grid_for(n_new, 256)), dim3(256), 0, s, ca, (int64_t *)nullptr,
                            kept.p, c.rowptr.p, c.col.p, c.desc.p);
         HQ_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_rows_wave<true>, dim3(grid_for(n_add * 64, 256)), dim3(256), 0, s, ra,
-                           (int64_t *)nullptr, c.rowptr.p, c.col.p, c.desc.p);
-        HQ_LAUNCH_CHECK();
+        connect_listed_rows(c, amap.p, n_add, nullptr, true);
     }
     build_elements_after(c, kept.p);  // new entries' values, every diagonal element
     compute_xcd_rows(c);

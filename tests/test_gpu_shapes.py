@@ -221,3 +221,43 @@ def test_solver_subspaces_and_row_tiles(ndet, block, max_space):
     assert np.abs(w - e).min() <= 1e-9 + slack and e <= o.diag().min() + slack
     assert abs(np.linalg.norm(c) - 1.0) <= 1e-12
     assert np.linalg.norm(o.dense() @ c - e * c) <= 1e-9 + 100 * slack
+
+
+@pytest.mark.parametrize("evict", ["none", "first", "last", "every other"])
+@pytest.mark.parametrize("n_old", [31, 32, 33, 64, 65, 1027])
+def test_update_at_word_and_wave_edges(n_old, evict):
+    """Kept-row bits around a word and a wave, rows shorter and longer than the
+    entries in flight, appended rows that fill the last wave and that do not:
+    the couplings, their values and the products of a fresh build."""
+    log(f"update of {n_old} rows, evict {evict}")
+    ints = W.gen_integrals(9, 3, -2.0, -0.5, 51)
+    a, b = W.sample_determinants(9, 4, 5, n_old + 38, 0.6, 0.2, 52 + n_old)
+    ev = {"none": [], "first": [0], "last": [n_old - 1], "every other": list(range(0, n_old, 2))}[evict]
+    s = solver_for(ints, a[:n_old], b[:n_old], 4, 5)
+    s.update_determinants(a[n_old:], b[n_old:], evict=np.array(ev, np.int32) if ev else None)
+    keep = np.setdiff1d(np.arange(n_old), ev)
+    na, nb = np.concatenate([a[keep], a[n_old:]]), np.concatenate([b[keep], b[n_old:]])
+    f = solver_for(ints, na, nb, 4, 5)
+    rows = np.arange(len(na))
+    assert gpu_rows_as_tuples(s, rows) == gpu_rows_as_tuples(f, rows)
+    X = W.random_block(len(na), 3, 53)
+    o = oracle_for(ints, na, nb, 4, 5)
+    bound = row_bound(oracle_rows_as_tuples(o, rows)[1], X, 3)
+    for dtype, tol in ((torch.float64, 1e-12), (torch.float32, 2e-6)):
+        Xd = torch.from_numpy(X).to(dtype).cuda()
+        ref = o.sigma_rows(Xd.double().cpu().numpy(), rows)
+        assert np.all(np.abs(s.sigma(Xd).double().cpu().numpy() - ref) <= tol * bound + 1e-300)
+
+
+@pytest.mark.parametrize("ndet", [32_767, 32_768, 32_771])
+def test_couplings_either_side_of_the_rows_per_wave_rule(ndet):
+    """One row or four per wave: runs of rows with one alpha string that begin
+    and end inside a wave, and a last wave with fewer rows."""
+    ints, a, b, cfg = W.config_inputs(3, ndet=ndet)
+    log(f"couplings at {ndet} rows")
+    s = solver_for(ints, a, b, cfg.na, cfg.nb)
+    o = oracle_for(ints, a, b, cfg.na, cfg.nb)
+    last = s.permutation().cpu().numpy()[-5:].astype(np.int64)
+    rows = np.unique(np.concatenate([np.random.default_rng(5).choice(ndet, 300, replace=False), last]))
+    ref, _ = oracle_rows_as_tuples(o, rows)
+    assert gpu_rows_as_tuples(s, rows) == ref
