@@ -178,9 +178,9 @@ int hinqs_sigma(hinqs_ctx *ctx, int k, const void *X, void *S, int precision, in
             sigma_sorted(c, K, X, K, S, K, precision, s);
             return HINQS_OK;
         }
-        // stage through sorted-order buffers (gather X, scatter S); pad k up to K
+        // X gathered into a sorted-order buffer and padded to K columns
         const size_t bytes = (size_t)c.ndet * K * esz;
-        sigma_staged(c, k, X, S, precision, sorted, c.cs.get<char>(0, bytes), c.cs.get<char>(1, bytes), nullptr);
+        sigma_staged(c, k, X, S, precision, sorted, c.cs.get<char>(0, bytes), nullptr);
         return HINQS_OK;
     });
 }

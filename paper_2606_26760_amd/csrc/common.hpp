@@ -420,11 +420,18 @@ void radix_sort_u64(hipStream_t s, uint64_t *keys, int32_t *vals, int64_t n, int
 void radix_sort_u64(hipStream_t s, uint64_t *keys, int32_t *vals, int64_t n, int nbits, DBuf<char> &tmp,
                     DBuf<char> &own);
 
+// Where a product goes: row r to row[r] (nullptr: r), the first `cols` columns
+// of it element by element (0: all of them, in 16-byte vectors).
+struct SigmaOut {
+    const int32_t *row = nullptr;
+    int cols = 0;
+};
+
 // Sigma (sigma.hip): S = H X in sorted order with leading dimensions.
 // ctr: the kernel's row counters (SIGMA_CTR_WORDS, zero on entry, left at
 // zero); nullptr = the context's own.
 void sigma_sorted(Ctx &c, int k, const void *X, int ldx, void *S, int lds, int precision,
-                  hipStream_t s, unsigned long long *ctr = nullptr);
+                  hipStream_t s, unsigned long long *ctr = nullptr, const SigmaOut &out = SigmaOut{});
 
 // S = H X in one launch for a small set: X, S in caller order or sorted, any k
 // in [1, 16], any alignment.  False (nothing done) when the set or its tuned
@@ -438,10 +445,10 @@ bool sigma_small(const Ctx &c, int k, const void *X, void *S, int precision, boo
 void noalloc_setup(int device);
 void sigma_noalloc(Ctx &c, int k, const void *X, void *S, int precision, bool sorted);
 // S = H X for X, S in caller order (sorted = false) or sorted order, any k in
-// [1, 16]: X gathered and padded to K columns into xs, the sorted product into
-// ss (both ndet x K of the precision's type), S scattered back.  ctr: as for
-// sigma_sorted.
-void sigma_staged(Ctx &c, int k, const void *X, void *S, int precision, bool sorted, void *xs, void *ss,
+// [1, 16] and any alignment: X gathered and padded to K columns into xs (ndet x K
+// of the precision's type, 16-byte aligned), the product written to S's rows and
+// columns by the kernel itself.  ctr: as for sigma_sorted.
+void sigma_staged(Ctx &c, int k, const void *X, void *S, int precision, bool sorted, void *xs,
                   unsigned long long *ctr);
 // Time the candidate launch shapes on c's couplings, keep the fastest in c
 // (and in a process-wide cache keyed by problem shape).  Returns it.

@@ -76,6 +76,20 @@ __device__ inline void store_vec(T *p, const T (&x)[N]) {
     }
 }
 
+// The entries of a row of S that one lane holds, columns c0 .. c0 + N - 1, to the
+// caller's row: whole vectors, or the columns that there are, one by one.
+template <typename T, int N>
+__device__ inline void store_row(T *S, int64_t row, int lds, int c0, const SigmaOut &out, const T (&x)[N]) {
+    T *p = S + row * lds + c0;
+    if (out.cols == 0) {
+        store_vec<T, N>(p, x);
+    } else {
+#pragma unroll
+        for (int c = 0; c < N; ++c)
+            if (c0 + c < out.cols) p[c] = x[c];
+    }
+}
+
 // Persistent teams: TEAM lanes own one row at a time and walk a strided list
 // of rows.  Rows are split into 8 contiguous ranges holding equal numbers of
 // couplings, one per XCD (hardware block b runs on XCD b % 8; the coupling
@@ -119,7 +133,7 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma(XcdRows ranges, SigmaMask
                                                        const T *__restrict__ val,
                                                        const T *__restrict__ diag,
                                                        const T *__restrict__ X, int ldx,
-                                                       T *__restrict__ S, int lds,
+                                                       T *__restrict__ S, int lds, SigmaOut out,
                                                        unsigned long long *ctr, int run) {
     constexpr int VW = Vec16<T>::n;
     constexpr int LPN = (K >= VW) ? K / VW : 1;   // lanes per coupling
@@ -187,6 +201,7 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma(XcdRows ranges, SigmaMask
         return;
     }
     int64_t beg = uniform_if<TEAM == 64>(rowptr[row]), end = uniform_if<TEAM == 64>(rowptr[row + 1]);
+    int32_t srow = !MASK && out.row ? out.row[row] : (int32_t)row;
     for (;;) {
         int64_t nrow;
         if (dyn) {
@@ -203,6 +218,7 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma(XcdRows ranges, SigmaMask
         // next row's bounds, in flight during this row (clamped, not predicated)
         const int64_t nrc = nrow < r1 ? nrow : row;
         const int64_t nbeg = rowptr[nrc], nend = rowptr[nrc + 1];
+        const int32_t nsrow = !MASK && out.row ? out.row[nrc] : (int32_t)nrc;
         T acc[EPL];
 #pragma unroll
         for (int c = 0; c < EPL; ++c) acc[c] = T(0);
@@ -263,10 +279,11 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma(XcdRows ranges, SigmaMask
 #pragma unroll
                 for (int c = 0; c < EPL; ++c) acc[c] += d * xr[c];
             }
-            store_vec<T, EPL>(S + row * lds + q * EPL, acc);
+            store_row<T, EPL>(S, srow, lds, q * EPL, out, acc);
         }
         if (nrow >= r1) break;
         row = nrow;
+        srow = nsrow;
         beg = uniform_if<TEAM == 64>(nbeg);
         end = uniform_if<TEAM == 64>(nend);
     }
@@ -290,7 +307,7 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma_xr(XcdRows ranges, SigmaM
                                                           const T *__restrict__ val,
                                                           const T *__restrict__ diag,
                                                           const T *__restrict__ X, int ldx,
-                                                          T *__restrict__ S, int lds) {
+                                                          T *__restrict__ S, int lds, SigmaOut out) {
     constexpr int VW = Vec16<T>::n;
     constexpr int LPN = (K >= VW) ? K / VW : 1;   // lanes per coupling
     constexpr int EPL = K / LPN;                   // entries of X per lane
@@ -403,7 +420,7 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma_xr(XcdRows ranges, SigmaM
                 T o[EPL];
 #pragma unroll
                 for (int c = 0; c < EPL; ++c) o[c] = acc[c] + sl.dd * sl.dx[c];
-                store_vec<T, EPL>(S + sl.row * lds + q * EPL, o);
+                store_row<T, EPL>(S, !MASK && out.row ? out.row[sl.row] : sl.row, lds, q * EPL, out, o);
             }
 #pragma unroll
             for (int c = 0; c < EPL; ++c) acc[c] = T(0);
@@ -563,7 +580,7 @@ int row_run(const Ctx &c, const SigmaCfg &cfg) {
 
 template <typename T, int K, int TEAM, int UNR, bool MASK>
 void launch_sigma_u(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, const T *val, const T *diag,
-                    const T *X, int ldx, T *S, int lds, hipStream_t s, unsigned long long *ctr) {
+                    const T *X, int ldx, T *S, int lds, const SigmaOut &out, hipStream_t s, unsigned long long *ctr) {
     static int cus = 0;
     if (!cus) {
         cus = 256;
@@ -580,28 +597,28 @@ void launch_sigma_u(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, cons
     const int run = MASK ? 0 : row_run(c, cfg);
     if (cfg.pipe == 1)
         hipLaunchKernelGGL((k_sigma_xr<T, K, TEAM, UNR, MASK>), dim3((unsigned)nblk), dim3(SIGMA_BLOCK), 0, s,
-                           ranges, mk, xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds);
+                           ranges, mk, xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds, out);
     else
         hipLaunchKernelGGL((k_sigma<T, K, TEAM, UNR, MASK>), dim3((unsigned)nblk), dim3(SIGMA_BLOCK), 0, s,
-                           ranges, mk, xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds,
+                           ranges, mk, xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds, out,
                            run > 0 ? (ctr ? ctr : c.sigma_ctr.p) : (unsigned long long *)nullptr, std::max(1, run));
     HQ_LAUNCH_CHECK();
 }
 
 template <typename T, int K, int TEAM, bool MASK>
 void launch_sigma(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, const T *val, const T *diag,
-                  const T *X, int ldx, T *S, int lds, hipStream_t s, unsigned long long *ctr) {
-    if (cfg.unr <= 2) launch_sigma_u<T, K, TEAM, 2, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr);
-    else if (cfg.unr <= 4) launch_sigma_u<T, K, TEAM, 4, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr);
-    else launch_sigma_u<T, K, TEAM, 8, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr);
+                  const T *X, int ldx, T *S, int lds, const SigmaOut &out, hipStream_t s, unsigned long long *ctr) {
+    if (cfg.unr <= 2) launch_sigma_u<T, K, TEAM, 2, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr);
+    else if (cfg.unr <= 4) launch_sigma_u<T, K, TEAM, 4, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr);
+    else launch_sigma_u<T, K, TEAM, 8, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr);
 }
 
 template <typename T, int K, bool MASK>
 void dispatch_team(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, const T *val, const T *diag,
-                   const T *X, int ldx, T *S, int lds, hipStream_t s, unsigned long long *ctr) {
+                   const T *X, int ldx, T *S, int lds, const SigmaOut &out, hipStream_t s, unsigned long long *ctr) {
     constexpr int LPN = lanes_per_coupling<T, K>();
     const int team = std::max(cfg.team, LPN);
-#define HQ_TEAM(n) launch_sigma<T, K, n, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr)
+#define HQ_TEAM(n) launch_sigma<T, K, n, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr)
     switch (team) {
         case 1: if constexpr (LPN <= 1) { HQ_TEAM(1); break; } [[fallthrough]];
         case 2: if constexpr (LPN <= 2) { HQ_TEAM(2); break; } [[fallthrough]];
@@ -617,13 +634,13 @@ void dispatch_team(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, const
 template <typename T, bool MASK = false>
 void dispatch_k(const Ctx &c, int k, const SigmaCfg &cfg, const T *val, const T *diag, const T *X, int ldx,
                 T *S, int lds, hipStream_t s, const SigmaMask &mk = SigmaMask{},
-                unsigned long long *ctr = nullptr) {
+                unsigned long long *ctr = nullptr, const SigmaOut &out = SigmaOut{}) {
     switch (k) {
-        case 1: dispatch_team<T, 1, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr); break;
-        case 2: dispatch_team<T, 2, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr); break;
-        case 4: dispatch_team<T, 4, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr); break;
-        case 8: dispatch_team<T, 8, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr); break;
-        case 16: dispatch_team<T, 16, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, s, ctr); break;
+        case 1: dispatch_team<T, 1, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr); break;
+        case 2: dispatch_team<T, 2, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr); break;
+        case 4: dispatch_team<T, 4, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr); break;
+        case 8: dispatch_team<T, 8, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr); break;
+        case 16: dispatch_team<T, 16, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr); break;
         default: throw Error(HINQS_E_UNSUPPORTED, "sigma block size must be 1, 2, 4, 8 or 16");
     }
 }
@@ -676,16 +693,16 @@ SigmaCfg sigma_config(const Ctx &c, int k, int precision) {
 namespace {
 
 void launch_shape(const Ctx &c, int k, int precision, const SigmaCfg &cfg, const void *X, int ldx, void *S, int lds,
-                  hipStream_t s, unsigned long long *ctr) {
-    const bool small = cfg.pipe == 2 && ldx == k && lds == k;
+                  hipStream_t s, unsigned long long *ctr, const SigmaOut &out = SigmaOut{}) {
+    const bool small = cfg.pipe == 2 && ldx == k && lds == k && !out.row && !out.cols;
     if (precision == HINQS_FP64) {
         if (small) dispatch_small<double>(c, c.val.p, c.diag.p, (const double *)X, k, (double *)S, true, s);
         else dispatch_k<double>(c, k, cfg, c.val.p, c.diag.p, (const double *)X, ldx, (double *)S, lds, s,
-                                SigmaMask{}, ctr);
+                                SigmaMask{}, ctr, out);
     } else if (precision == HINQS_FP32) {
         if (small) dispatch_small<float>(c, c.val32.p, c.diag32.p, (const float *)X, k, (float *)S, true, s);
         else dispatch_k<float>(c, k, cfg, c.val32.p, c.diag32.p, (const float *)X, ldx, (float *)S, lds, s,
-                               SigmaMask{}, ctr);
+                               SigmaMask{}, ctr, out);
     } else {
         throw Error(HINQS_E_INVALID_ARG, "precision must be HINQS_FP64 or HINQS_FP32");
     }
@@ -693,12 +710,13 @@ void launch_shape(const Ctx &c, int k, int precision, const SigmaCfg &cfg, const
 
 }  // namespace
 
-// X, S in sorted order; k in {1,2,4,8,16}; leading dimensions keep 16-byte
+// X in sorted order; k in {1,2,4,8,16}; leading dimensions keep 16-byte
 // alignment of every row (ldx, lds multiples of 16 / sizeof(T) when k >= that).
+// S in sorted order as well, or where out says.
 void sigma_sorted(Ctx &c, int k, const void *X, int ldx, void *S, int lds, int precision,
-                  hipStream_t s, unsigned long long *ctr) {
+                  hipStream_t s, unsigned long long *ctr, const SigmaOut &out) {
     if (!c.have_elements) throw Error(HINQS_E_NOT_READY, "matrix elements are not built");
-    launch_shape(c, k, precision, sigma_config(c, k, precision), X, ldx, S, lds, s, ctr);
+    launch_shape(c, k, precision, sigma_config(c, k, precision), X, ldx, S, lds, s, ctr, out);
 }
 
 bool sigma_small(const Ctx &c, int k, const void *X, void *S, int precision, bool sorted, hipStream_t s) {
