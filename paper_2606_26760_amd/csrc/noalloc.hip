@@ -44,7 +44,7 @@ __global__ void k_clear_words(unsigned long long *p, int n) {
 
 // xs (sorted order, K wide) from X (k wide; caller order through perm, or
 // sorted when perm is null); columns k..K-1 are zero.  Bound by memory; VEC: X is
-// K wide and aligned, 16 bytes per thread (1e6 rows of 8 doubles: @SV@ us, element
+// K wide and aligned, 16 bytes per thread (1e6 rows of 8 doubles: 30 us, element
 // by element with the row divided out 40 us).
 template <typename T, int K, bool VEC>
 __global__ __launch_bounds__(256) void k_stage_in(const T *__restrict__ X, int k, const int32_t *__restrict__ perm,
