@@ -1,7 +1,6 @@
 // Launch-shape autotuner of the block-sigma kernel: times the candidate
-// shapes (team width, software-pipeline depth, workgroups per CU, cross-row
-// pipelined variant) on the problem at hand with HIP events and keeps the
-// fastest.  Results are cached per process, keyed by device architecture,
+// shapes (team width, software-pipeline depth, workgroups per CU) on the
+// problem at hand with HIP events and keeps the fastest.  Results are cached per process, keyed by device architecture,
 // precision, block size and problem-size class, and optionally in a text
 // file named by HINQS_TUNE_CACHE.
 #include <algorithm>
@@ -118,20 +117,20 @@ SigmaCfg autotune_sigma(Ctx &c, int k, int precision) {
     const int teams[] = {16, 32, 64};
     const int unrs[] = {2, 4};
     const int occs[] = {2, 4, 8};
-    for (int pipe = 0; pipe < 2; ++pipe)
-        for (int team : teams) {
-            if (team < 4 * lpn) continue;
-            for (int unr : unrs)
-                for (int occ : occs) {
-                    SigmaCfg g;
-                    g.team = team;
-                    g.unr = unr;
-                    g.occ = occ;
-                    g.pipe = pipe;
-                    time_cfg(g);
-                    if (g.ms < 0.97 * best.ms) best = g;
-                }
+    for (int team : teams) {
+        if (team < 4 * lpn) continue;
+        for (int unr : unrs) {
+            if (unr == 2 && lpn >= 8) continue;  // the same kernel as 4
+            for (int occ : occs) {
+                SigmaCfg g;
+                g.team = team;
+                g.unr = unr;
+                g.occ = occ;
+                time_cfg(g);
+                if (g.ms < 0.97 * best.ms) best = g;
+            }
         }
+    }
     slot = best;
     {
         std::lock_guard<std::mutex> lk(g_tune_mutex);

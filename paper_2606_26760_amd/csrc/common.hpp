@@ -237,12 +237,11 @@ inline int neri_packed(int norb) { int m = npair(norb); return m * (m + 1) / 2; 
 // Words of the sigma kernel's row counters: 32 per XCD (8 XCDs).
 constexpr int SIGMA_CTR_WORDS = 8 * 32;
 
-// Launch shape of the sigma kernel: lanes per row team, couplings in flight per
-// lane, resident workgroups per CU.
+// Launch shape of the sigma kernel: lanes per row team, pairs of gathers in
+// flight per lane, workgroups per CU.
 struct SigmaCfg {
     int team = 0, unr = 0, occ = 0;
-    int pipe = 0;     // 0: one step of gathers in flight per team; 1: cross-row four-stage pipeline;
-                      // 2: small sets, one wave per row
+    int pipe = 0;     // 2: small sets, one wave per row; 0 (or 1, in saved plans): teams
     int run = -1;     // rows a team takes from its XCD's row counter at a time, 0: fixed strides,
                       // -1: by the size of the set (pipe 0)
     double ms = 0.0;  // measured time of one launch when chosen by the tuner

@@ -18,6 +18,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <utility>
 
 #include "common.hpp"
 
@@ -90,6 +91,35 @@ __device__ inline void store_row(T *S, int64_t row, int lds, int c0, const Sigma
     }
 }
 
+// The 32 bits that lane U of each group of LPN neighbouring lanes holds, on every
+// lane of the group (DPP moves; LPN in {1, 2, 4, 8}).
+template <int LPN, int U>
+__device__ inline int group_bcast(int x) {
+    if constexpr (LPN == 1) return x;
+    else if constexpr (LPN == 2) return __builtin_amdgcn_update_dpp(x, x, U == 0 ? 0xa0 : 0xf5, 0xf, 0xf, false);
+    else if constexpr (LPN == 4) return __builtin_amdgcn_update_dpp(x, x, U * 0x55, 0xf, 0xf, false);
+    else {  // lane U of a row of 16 to its first half, lane 8 + U to its second
+        const int lo = __builtin_amdgcn_update_dpp(x, x, 0x150 + U, 0xf, 0x3, false);
+        return __builtin_amdgcn_update_dpp(lo, x, 0x158 + U, 0xf, 0xc, false);
+    }
+}
+template <int LPN, int U>
+__device__ inline float group_bcast(float x) {
+    return __int_as_float(group_bcast<LPN, U>(__float_as_int(x)));
+}
+template <int LPN, int U>
+__device__ inline double group_bcast(double x) {
+    return __hiloint2double(group_bcast<LPN, U>(__double2hiint(x)), group_bcast<LPN, U>(__double2loint(x)));
+}
+template <int... I, typename F>
+__device__ inline void static_for_seq(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ inline void static_for(F &&f) {
+    static_for_seq(std::make_integer_sequence<int, N>{}, f);
+}
+
 // Persistent teams: TEAM lanes own one row at a time and walk a strided list
 // of rows.  Rows are split into 8 contiguous ranges holding equal numbers of
 // couplings, one per XCD (hardware block b runs on XCD b % 8; the coupling
@@ -101,7 +131,17 @@ __device__ inline void store_row(T *S, int64_t row, int lds, int c0, const Sigma
 // share one coupling: each loads EPL consecutive entries (16 bytes) of the
 // gathered X row, so one load instruction touches 64 / LPN distinct rows and
 // every row is read as one contiguous segment.
-// The CSR stream is software-pipelined: while the X rows of one step (UNR
+// What bounds the product is the return path of a CU's loads: about 20 clk per
+// load instruction whatever it brings, 75 % busy when the LPN lanes of a coupling
+// each fetched its column and value.  So every lane fetches the column and value
+// of a coupling of its own, and the group takes its LPN couplings in turn, handing
+// each around by DPP: half the load instructions per coupling for k = 8 (FP64,
+// 20,000 rows, 7.1e6 couplings 69 -> 53 us, 1e6 rows, 1.56e8 1750 -> 1500).  Past
+// that it is the lines that miss L1, 0.8 per coupling at 2.4 clk from L2 and 10 from
+// beyond it (1e6 rows: 40 % of them).  Larger workgroups, the first fetch of the
+// next row ahead of a row's end and its diagonal element ahead were within 8 %
+// either way.
+// The CSR stream is software-pipelined: while the X rows of one step (CH
 // couplings per lane) are in flight, the (col, val) of the next step and the
 // bounds of the team's next row are already being fetched, so the dependent
 // load chain rowptr -> col -> X costs one memory latency per step, not three.
@@ -138,8 +178,8 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma(XcdRows ranges, SigmaMask
     constexpr int VW = Vec16<T>::n;
     constexpr int LPN = (K >= VW) ? K / VW : 1;   // lanes per coupling
     constexpr int EPL = K / LPN;                   // entries of X per lane
-    constexpr int NPT = TEAM / LPN;                // couplings per team per unrolled slot
-    constexpr int STEP = UNR * NPT;                // couplings per team step
+    constexpr int CH = (UNR + LPN - 1) / LPN;      // couplings that a lane fetches per step
+    constexpr int STEP = CH * TEAM;                // couplings per team step
     constexpr int TPB = SIGMA_BLOCK / TEAM;        // teams per block
     static_assert(TEAM % LPN == 0 && TEAM <= 64, "team shape");
     const int64_t blocks_per_xcd = gridDim.x / NUM_XCD;
@@ -228,34 +268,38 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma(XcdRows ranges, SigmaMask
         // Loads are never predicated: indices past the row are clamped to a
         // valid entry and their value is replaced by 0 at the point of use.
         const int64_t last = end > 0 ? end - 1 : 0;
-        int32_t ja[UNR], jb[UNR];
-        T va[UNR], vb[UNR];
-        bool oka[UNR], okb[UNR];
-        auto fetch = [&](int64_t eb, int32_t (&jj)[UNR], T (&vv)[UNR], bool (&ok)[UNR]) {
+        int32_t ja[CH], jb[CH];
+        T va[CH], vb[CH];
+        bool oka[CH], okb[CH];
+        auto fetch = [&](int64_t eb, int32_t (&jj)[CH], T (&vv)[CH], bool (&ok)[CH]) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const int64_t idx = eb + g + u * NPT;
-                ok[u] = idx < end;
-                const int64_t idc = ok[u] ? idx : last;
-                jj[u] = __builtin_nontemporal_load(col + idc);
-                vv[u] = __builtin_nontemporal_load(val + idc);
+            for (int v = 0; v < CH; ++v) {
+                const int64_t idx = eb + v * TEAM + sub;
+                ok[v] = idx < end;
+                const int64_t idc = ok[v] ? idx : last;
+                jj[v] = __builtin_nontemporal_load(col + idc);
+                vv[v] = __builtin_nontemporal_load(val + idc);
             }
         };
-        auto step = [&](const int32_t (&jj)[UNR], const T (&vv)[UNR], const bool (&ok)[UNR],
-                        int64_t eb_next, int32_t (&jn)[UNR], T (&vn)[UNR], bool (&okn)[UNR]) {
-            T x[UNR][EPL];
+        auto step = [&](const int32_t (&jj)[CH], const T (&vv)[CH], const bool (&ok)[CH],
+                        int64_t eb_next, int32_t (&jn)[CH], T (&vn)[CH], bool (&okn)[CH]) {
+            T x[CH][LPN][EPL], w[CH];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const int32_t jr = ok[u] ? jj[u] : (int32_t)row;
-                load_vec<T, EPL>(Xq + (int64_t)jr * ldx, x[u]);
+            for (int v = 0; v < CH; ++v) {
+                const int32_t jr = ok[v] ? jj[v] : (int32_t)row;
+                w[v] = ok[v] ? vv[v] : T(0);
+                static_for<LPN>([&](auto u) {
+                    load_vec<T, EPL>(Xq + (int64_t)group_bcast<LPN, u>(jr) * ldx, x[v][u]);
+                });
             }
             fetch(eb_next, jn, vn, okn);
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const T w = ok[u] ? vv[u] : T(0);
+            for (int v = 0; v < CH; ++v)
+                static_for<LPN>([&](auto u) {
+                    const T wu = group_bcast<LPN, u>(w[v]);
 #pragma unroll
-                for (int c = 0; c < EPL; ++c) acc[c] += w * x[u][c];
-            }
+                    for (int c = 0; c < EPL; ++c) acc[c] += wu * x[v][u][c];
+                });
         };
         int64_t eb = beg;
         fetch(eb, ja, va, oka);
@@ -288,167 +332,6 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma(XcdRows ranges, SigmaMask
         end = uniform_if<TEAM == 64>(nend);
     }
     finish();
-}
-
-// Cross-row pipelined variant.  A team walks its rows as one stream of steps
-// (UNR * TEAM / LPN couplings of one row per step; an empty row is one step
-// with none), and four register sets rotate through the stages of a step:
-//   stage t:  fetch (col, val) of step t+2;  gather the X rows of step t+1;
-//             accumulate step t-1 (and finish its row if it is the row's last)
-// so two steps of X gathers are in flight while a third is accumulated, with
-// no bubble at row boundaries.  Every step also fetches its row's diagonal
-// element and X row (used by the row's last step), so each stage issues the
-// same loads in the same order and the hardware's in-order load counter never
-// forces a wait on younger gathers.
-template <typename T, int K, int TEAM, int UNR, bool MASK>
-__global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma_xr(XcdRows ranges, SigmaMask mk, int xcd_map,
-                                                          const int64_t *__restrict__ rowptr,
-                                                          const int32_t *__restrict__ col,
-                                                          const T *__restrict__ val,
-                                                          const T *__restrict__ diag,
-                                                          const T *__restrict__ X, int ldx,
-                                                          T *__restrict__ S, int lds, SigmaOut out) {
-    constexpr int VW = Vec16<T>::n;
-    constexpr int LPN = (K >= VW) ? K / VW : 1;   // lanes per coupling
-    constexpr int EPL = K / LPN;                   // entries of X per lane
-    constexpr int NPT = TEAM / LPN;                // couplings per team per unrolled slot
-    constexpr int STEP = UNR * NPT;                // couplings per team step
-    constexpr int TPB = SIGMA_BLOCK / TEAM;        // teams per block
-    constexpr bool UNI = TEAM == 64;
-    static_assert(TEAM % LPN == 0 && TEAM <= 64, "team shape");
-    const int64_t blocks_per_xcd = gridDim.x / NUM_XCD;
-    const int xcd = xcd_map ? blockIdx.x % NUM_XCD : blockIdx.x / blocks_per_xcd;
-    const int64_t bix = xcd_map ? blockIdx.x / NUM_XCD : blockIdx.x % blocks_per_xcd;
-    const int64_t team0 = bix * TPB + threadIdx.x / TEAM;
-    const int64_t nteams = blocks_per_xcd * TPB;
-    const int64_t r0 = MASK ? mk.ranges[xcd] : ranges.b[xcd];
-    const int64_t r1 = MASK ? mk.ranges[xcd + 1] : ranges.b[xcd + 1];
-    const int sub = threadIdx.x % TEAM;
-    const int q = sub % LPN, g = sub / LPN;
-    const T *Xq = X + q * EPL;
-    int64_t inst_end = -1;
-    bool inst_done = false;
-    auto live_row = [&](int64_t rw) -> int64_t {
-        if constexpr (MASK) {
-            while (rw < r1) {
-                if (rw >= inst_end) {
-                    const int32_t b = mk.row_inst[rw];
-                    inst_end = mk.inst_row[b + 1];
-                    inst_done = mk.done[b] != 0;
-                }
-                if (!inst_done) break;
-                rw += (inst_end - rw + nteams - 1) / nteams * nteams;
-            }
-        }
-        return rw;
-    };
-    // step generator (the same on every lane of a team)
-    int64_t g_row = live_row(r0 + team0);
-    if (g_row >= r1) return;
-    const int64_t safe_row = g_row;  // an in-range row for clamped loads
-    int64_t g_eb = uniform_if<UNI>(rowptr[g_row]), g_end = uniform_if<UNI>(rowptr[g_row + 1]);
-    int64_t n_row = live_row(g_row + nteams);
-    int64_t n_beg, n_end;
-    {
-        const int64_t c = n_row < r1 ? n_row : safe_row;
-        n_beg = rowptr[c];
-        n_end = rowptr[c + 1];
-    }
-    struct Slot {
-        int32_t j[UNR];
-        T v[UNR];
-        bool ok[UNR];
-        T x[UNR][EPL];
-        T dx[EPL];
-        T dd;
-        int64_t row;
-        bool last, valid;
-    };
-    Slot s0, s1, s2, s3;
-    auto emit = [&](Slot &sl) {
-        sl.valid = g_row < r1;
-        sl.row = sl.valid ? g_row : safe_row;
-        sl.last = g_eb + STEP >= g_end;
-        const int64_t lastidx = g_end > 0 ? g_end - 1 : 0;
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int64_t idx = g_eb + g + u * NPT;
-            sl.ok[u] = sl.valid && idx < g_end;
-            const int64_t idc = sl.ok[u] ? idx : lastidx;
-            sl.j[u] = __builtin_nontemporal_load(col + idc);
-            sl.v[u] = __builtin_nontemporal_load(val + idc);
-        }
-        if (sl.valid) {
-            g_eb += STEP;
-            if (g_eb >= g_end) {
-                g_row = n_row;
-                g_eb = uniform_if<UNI>(n_beg);
-                g_end = uniform_if<UNI>(n_end);
-                n_row = live_row(g_row + nteams);
-                const int64_t c = n_row < r1 ? n_row : safe_row;
-                n_beg = rowptr[c];
-                n_end = rowptr[c + 1];
-            }
-        }
-    };
-    auto gather = [&](Slot &sl) {
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int32_t jr = sl.ok[u] ? sl.j[u] : (int32_t)safe_row;
-            load_vec<T, EPL>(Xq + (int64_t)jr * ldx, sl.x[u]);
-        }
-        sl.dd = diag ? diag[sl.row] : T(0);
-        load_vec<T, EPL>(Xq + sl.row * ldx, sl.dx);
-    };
-    T acc[EPL];
-#pragma unroll
-    for (int c = 0; c < EPL; ++c) acc[c] = T(0);
-    auto accumulate = [&](Slot &sl) {
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const T w = sl.ok[u] ? sl.v[u] : T(0);
-#pragma unroll
-            for (int c = 0; c < EPL; ++c) acc[c] += w * sl.x[u][c];
-        }
-        if (sl.last) {
-#pragma unroll
-            for (int off = LPN; off < TEAM; off <<= 1) {
-#pragma unroll
-                for (int c = 0; c < EPL; ++c) acc[c] += __shfl_xor(acc[c], off, TEAM);
-            }
-            if (g == 0) {
-                T o[EPL];
-#pragma unroll
-                for (int c = 0; c < EPL; ++c) o[c] = acc[c] + sl.dd * sl.dx[c];
-                store_row<T, EPL>(S, !MASK && out.row ? out.row[sl.row] : sl.row, lds, q * EPL, out, o);
-            }
-#pragma unroll
-            for (int c = 0; c < EPL; ++c) acc[c] = T(0);
-        }
-    };
-    emit(s0);
-    emit(s1);
-    gather(s0);
-    emit(s2);
-    gather(s1);
-    for (;;) {
-        emit(s3);
-        gather(s2);
-        accumulate(s0);
-        if (!s1.valid) break;
-        emit(s0);
-        gather(s3);
-        accumulate(s1);
-        if (!s2.valid) break;
-        emit(s1);
-        gather(s0);
-        accumulate(s2);
-        if (!s3.valid) break;
-        emit(s2);
-        gather(s1);
-        accumulate(s3);
-        if (!s0.valid) break;
-    }
 }
 
 // Small sets (at most SIGMA_SMALL_ROWS rows): one wave per row, in whatever
@@ -565,11 +448,11 @@ constexpr int lanes_per_coupling() {
 
 // Rows a team takes from its XCD's counter at a time; 0: fixed strides.  The
 // atomics on one counter come through at about 24 ns each (1e6 rows, runs of
-// one row: 3.0 ms, all of it the counters), so below SIGMA_STATIC_NNZ couplings
-// they cost more than the shared L2 gives: 3,000 rows k = 8 18.9 us with
-// counters, 5.1 with strides; 20,000 rows 118 / 69; 100,000 short rows 99 / 42;
-// equal at 3.5e7 couplings (353 / 336 us), and 1749 / 1842 us at 1.6e8.
-constexpr int64_t SIGMA_STATIC_NNZ = 32000000;
+// one row: 3.0 ms, all of it the counters), so they pay only where X is many
+// times the L2s: strides / counters in us, k = 1 and 8, 20,000 rows with 356
+// couplings 33 / 170 and 54 / 140, 5e5 with 85 333 / 350 and 457 / 463, 2e5 with
+// 615 565 / 601 and 962 / 938, 1e6 with 156 1098 / 1086 and 1550 / 1505.
+constexpr int64_t SIGMA_STATIC_NNZ = 130000000;
 constexpr double SIGMA_LONG_ROW = 256.0;  // mean couplings from which two rows make a run
 
 int row_run(const Ctx &c, const SigmaCfg &cfg) {
@@ -595,21 +478,19 @@ void launch_sigma_u(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, cons
     for (int x = 0; x <= NUM_XCD; ++x) ranges.b[x] = c.xcd_rows[x];
     const int xmap = env_int("HINQS_SIGMA_XCDMAP", 1);
     const int run = MASK ? 0 : row_run(c, cfg);
-    if (cfg.pipe == 1)
-        hipLaunchKernelGGL((k_sigma_xr<T, K, TEAM, UNR, MASK>), dim3((unsigned)nblk), dim3(SIGMA_BLOCK), 0, s,
-                           ranges, mk, xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds, out);
-    else
-        hipLaunchKernelGGL((k_sigma<T, K, TEAM, UNR, MASK>), dim3((unsigned)nblk), dim3(SIGMA_BLOCK), 0, s,
-                           ranges, mk, xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds, out,
-                           run > 0 ? (ctr ? ctr : c.sigma_ctr.p) : (unsigned long long *)nullptr, std::max(1, run));
+    hipLaunchKernelGGL((k_sigma<T, K, TEAM, UNR, MASK>), dim3((unsigned)nblk), dim3(SIGMA_BLOCK), 0, s, ranges, mk,
+                       xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds, out,
+                       run > 0 ? (ctr ? ctr : c.sigma_ctr.p) : (unsigned long long *)nullptr, std::max(1, run));
     HQ_LAUNCH_CHECK();
 }
 
 template <typename T, int K, int TEAM, bool MASK>
 void launch_sigma(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, const T *val, const T *diag,
                   const T *X, int ldx, T *S, int lds, const SigmaOut &out, hipStream_t s, unsigned long long *ctr) {
-    if (cfg.unr <= 2) launch_sigma_u<T, K, TEAM, 2, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr);
-    else if (cfg.unr <= 4) launch_sigma_u<T, K, TEAM, 4, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr);
+    // cfg.unr pairs of gathers in flight per lane; a step has at least the couplings
+    // that the lanes of one fetch
+    constexpr int U4 = lanes_per_coupling<T, K>() < 8 ? 4 : 8;
+    if (cfg.unr <= 2) launch_sigma_u<T, K, TEAM, U4, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr);
     else launch_sigma_u<T, K, TEAM, 8, MASK>(c, cfg, mk, val, diag, X, ldx, S, lds, out, s, ctr);
 }
 
@@ -648,31 +529,35 @@ void dispatch_k(const Ctx &c, int k, const SigmaCfg &cfg, const T *val, const T 
 
 }  // namespace
 
-// Default shape before tuning.  Row by row from counters: a team of about four
-// unrolled steps per mean row.  Fixed strides: fewer lanes per row (more rows
-// in flight; 4e5 rows of 70 couplings, k = 8: 32 lanes 394 us, 64 lanes 441),
-// doubled while the rows' teams do not fill the chip (5,000 rows of 13: 16
-// lanes 5.9 us, 8 lanes 7.2), four couplings in flight per lane (1e5 rows of
-// 19: 41.8 against 46.4 us with two).
+// Default shape before tuning, from the mean row and the lanes that share a
+// coupling (times in us, FP64).  Lanes: a step takes one or two couplings per
+// lane, and a row should be a few steps (k = 1: rows of 19 couplings 8 lanes 21.3,
+// of 73 16 lanes 16.1, of 356 32 lanes 31.3 and 64 lanes 32.4; k = 8: 36 couplings 16
+// lanes 94, 230 and 356 32 lanes 113 and 54, 64 lanes 117 and 53; k = 16, eight
+// lanes per coupling: 19 couplings 16 lanes 43 and 32 lanes 55, 356 64 lanes 67 and
+// 32 lanes 75), and the rows' teams fill the chip (5,000 rows of 13: 16 lanes
+// 5.9, 8 lanes 7.2).  Gathers in flight: eight per lane where the row has them
+// (k = 8, 356 couplings 52 against 59 with four).  Workgroups per CU: more than are
+// resident even out rows of different length (60,000 rows, k = 8, 8 / 4: 114 / 117)
+// until the rows per team are many (4.9e7 couplings: 4 386, 8 400).
+constexpr int64_t SIGMA_EVEN_NNZ = 32000000;
+constexpr double SIGMA_WIDE_ROW = 240.0;  // mean couplings times lanes per coupling
 SigmaCfg default_cfg(const Ctx &c, int k, int precision) {
     const int vw = precision == HINQS_FP64 ? 2 : 4;
     const int lpn = k >= vw ? k / vw : 1;
     const double avg = c.ndet > 0 ? (double)c.nnz / (double)c.ndet : 0.0;
     const double want = avg / 8.0 * lpn;
     SigmaCfg g;
+    g.unr = avg * lpn >= SIGMA_WIDE_ROW ? 4 : 2;
     g.occ = 4;
     if (c.nnz <= SIGMA_STATIC_NNZ) {
-        g.team = want <= 3 ? 8 : want <= 12 ? 16 : want <= 72 ? 32 : 64;
+        if (lpn >= 8) g.team = avg < 32 ? 16 : avg < 100 ? 32 : 64;
+        else g.team = want <= 3 ? 8 : want <= 16 ? 16 : 32;
         while (g.team < 64 && c.ndet * g.team < (int64_t)256 * 1024) g.team *= 2;
-        g.unr = 4;
+        if (c.nnz <= SIGMA_EVEN_NNZ) g.occ = 8;
         if (c.ndet <= SIGMA_SMALL_ROWS) g.pipe = 2;
     } else {
-        // long rows, and the eight lanes of a 128-byte row of X, take four
-        // couplings in flight per lane (615 couplings per row: 1116 against
-        // 1163 us; k = 16 at 1e6 rows: 2352 against 2494; k = 8 there: 1789
-        // against 1749)
-        g.team = want <= 8 ? 8 : want <= 16 ? 16 : want <= (lpn == 1 ? 96 : 32) ? 32 : 64;
-        g.unr = lpn >= 8 || avg >= SIGMA_LONG_ROW ? 4 : 2;
+        g.team = lpn >= 4 ? 64 : 32;  // 1e6 rows of 156: k = 8 1509 / 1525, k = 1 1240 / 1086
     }
     return g;
 }

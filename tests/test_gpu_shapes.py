@@ -261,3 +261,35 @@ def test_couplings_either_side_of_the_rows_per_wave_rule(ndet):
     rows = np.unique(np.concatenate([np.random.default_rng(5).choice(ndet, 300, replace=False), last]))
     ref, _ = oracle_rows_as_tuples(o, rows)
     assert gpu_rows_as_tuples(s, rows) == ref
+
+
+@pytest.mark.parametrize("team,unr", [(8, 2), (8, 8), (16, 4), (32, 2), (32, 8), (64, 4), (64, 8)])
+@pytest.mark.parametrize("ndet", [8193, 9001])
+def test_sigma_lanes_and_steps(ndet, team, unr, monkeypatch):
+    """Lanes that fetch their own coupling and hand it to their group: every
+    width, one to eight lanes per coupling, rows that end anywhere in a step,
+    rows written in sorted and in caller order, padded and not, with fixed
+    strides and with counters."""
+    ints, a, b, cfg = W.config_inputs(1, ndet=ndet)
+    log(f"sigma at {ndet} rows, team {team}, {unr} gathers in flight")
+    for name, v in (("TEAM", team), ("UNR", unr), ("OCC", 4)):
+        monkeypatch.setenv("HINQS_SIGMA_" + name, str(v))
+    s = solver_for(ints, a, b, cfg.na, cfg.nb)
+    o = oracle_for(ints, a, b, cfg.na, cfg.nb)
+    rows = np.unique(np.linspace(0, ndet - 1, 250).astype(np.int64))
+    perm = torch.from_numpy(s.permutation().cpu().numpy()).long().cuda()
+    _, r = oracle_rows_as_tuples(o, rows)
+    for k in (1, 2, 3, 4, 8, 11, 16):
+        X = W.random_block(ndet, k, 950 + k)
+        for dtype, tol in ((torch.float64, 1e-12), (torch.float32, 2e-6)):
+            Xd = torch.from_numpy(X).to(dtype).cuda()
+            Xr = Xd.double().cpu().numpy()
+            ref, bound = o.sigma_rows(Xr, rows), row_bound(r, Xr, k)
+            for run in ("0", "3"):
+                monkeypatch.setenv("HINQS_SIGMA_RUN", run)
+                S = s.sigma(Xd)
+                back = torch.empty_like(S)
+                back[perm] = s.sigma(Xd[perm].contiguous(), sorted_order=True)
+                for P in (S, back):
+                    err = np.abs(P.double().cpu().numpy()[rows] - ref)
+                    assert np.all(err <= tol * bound + 1e-300), (k, dtype, run)
