@@ -153,8 +153,9 @@ struct XcdRows {
 // rows of finished instances are skipped; a team jumps over a finished
 // instance in one step, so the cost does not grow with its size.
 // Row counters (ctr, not for MASK; sets above SIGMA_STATIC_NNZ couplings, see
-// row_run): instead of a fixed stride, the team leader takes the XCD's next run of `run` rows from a counter, so the teams of an XCD stay
-// on neighbouring rows however unequal the rows are; with fixed strides the
+// row_run): instead of a fixed stride, the team leader takes the XCD's next run
+// of `run` rows from a counter, so the teams of an XCD stay on neighbouring rows
+// however unequal the rows are; with fixed strides the
 // teams drift apart and the X rows in flight no longer share the XCD's L2
 // (a trace-driven model of the gathers gives 53 % L2 hits for strides and
 // 80 % for a shared counter).  The next run is requested when a run starts,
