@@ -341,6 +341,9 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma(XcdRows ranges, SigmaMask
 // rows).  Such a product is bound by launches, not by its gathers: staging
 // caller-order vectors took two more kernels (400 rows, k = 1: 12.8 us per call
 // with them, 5 us for this kernel alone), and the lookup perm[col] stays in L1.
+// Couplings are fetched one per lane and handed around as in k_sigma (8,192 rows of
+// 165 couplings, caller order, k = 8 / 16: 14.6 / 24.3 us with a fetch on every lane
+// of a coupling, 10.4 / 12.9 us).
 template <typename T, int K, bool VEC>
 __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma_small(int64_t ndet, const int64_t *__restrict__ rowptr,
                                                              const int32_t *__restrict__ col,
@@ -350,8 +353,7 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma_small(int64_t ndet, const
     constexpr int VW = Vec16<T>::n;
     constexpr int LPN = (K >= VW) ? K / VW : 1;
     constexpr int EPL = K / LPN;
-    constexpr int NPT = 64 / LPN;  // couplings per wave and step
-    constexpr int UNR = 4;
+    constexpr int CH = LPN >= 4 ? 1 : 4 / LPN;  // couplings that a lane fetches per step
     const int lane = threadIdx.x & 63, q = lane % LPN, g = lane / LPN;
     const int64_t row = uniform_if<true>((int64_t)blockIdx.x * (SIGMA_BLOCK / 64) + (threadIdx.x >> 6));
     if (row >= ndet) return;
@@ -364,34 +366,41 @@ __global__ __launch_bounds__(SIGMA_BLOCK) void k_sigma_small(int64_t ndet, const
             for (int c = 0; c < EPL; ++c) x[c] = c0 + c < k ? X[r * k + c0 + c] : T(0);
         }
     };
-    const int64_t beg = rowptr[row], end = rowptr[row + 1];
+    const int64_t beg = uniform_if<true>(rowptr[row]), end = uniform_if<true>(rowptr[row + 1]);
     const int64_t orow = perm ? perm[row] : row;
     T acc[EPL], own[EPL];
 #pragma unroll
     for (int c = 0; c < EPL; ++c) acc[c] = T(0);
     load(orow, own);
     const T d = diag ? diag[row] : T(0);
-    for (int64_t e = beg + g; e < end; e += UNR * NPT) {
-        int64_t j[UNR];
-        T w[UNR], x[UNR][EPL];
+    for (int64_t e0 = beg; e0 + g * LPN < end; e0 += CH * 64) {  // a group with a coupling stays whole
+        int32_t j[CH];
+        T w[CH], x[CH][LPN][EPL];
         // past the row's end: the row itself with value 0
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const bool ok = e + u * NPT < end;
-            const int64_t i = ok ? e + u * NPT : e;
-            j[u] = ok ? (int64_t)col[i] : row;
-            w[u] = ok ? val[i] : T(0);
+        for (int v = 0; v < CH; ++v) {
+            const int64_t e = e0 + v * 64 + lane;
+            const bool ok = e < end;
+            const int64_t i = ok ? e : beg;
+            const int32_t ji = col[i];
+            const T wi = val[i];
+            j[v] = ok ? ji : (int32_t)row;
+            w[v] = ok ? wi : T(0);
         }
         if (perm) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) j[u] = perm[j[u]];
+            for (int v = 0; v < CH; ++v) j[v] = perm[j[v]];
         }
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) load(j[u], x[u]);
+        for (int v = 0; v < CH; ++v)
+            static_for<LPN>([&](auto u) { load(group_bcast<LPN, u>(j[v]), x[v][u]); });
 #pragma unroll
-        for (int u = 0; u < UNR; ++u)
+        for (int v = 0; v < CH; ++v)
+            static_for<LPN>([&](auto u) {
+                const T wu = group_bcast<LPN, u>(w[v]);
 #pragma unroll
-            for (int c = 0; c < EPL; ++c) acc[c] += w[u] * x[u][c];
+                for (int c = 0; c < EPL; ++c) acc[c] += wu * x[v][u][c];
+            });
     }
 #pragma unroll
     for (int off = LPN; off < 64; off <<= 1) {
