@@ -330,6 +330,8 @@ class Hinqs:
 
     # ------------------------------------------------------------- products
     def sigma(self, X, out=None, sorted_order: bool = False):
+        """H X (ndet x k, k <= 16, FP64 or FP32) into ``out`` or a new tensor; a
+        sorted-order product must not write over X."""
         torch = _torch()
         squeeze = X.dim() == 1
         if squeeze:

@@ -617,6 +617,11 @@ void sigma_sorted(Ctx &c, int k, const void *X, int ldx, void *S, int lds, int p
 bool sigma_small(const Ctx &c, int k, const void *X, void *S, int precision, bool sorted, hipStream_t s) {
     const int K = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
     if (sigma_config(c, K, precision).pipe != 2) return false;
+    // the launch reads X while others of its waves write S: arrays that share
+    // memory take the path that copies X first
+    const size_t bytes = (size_t)c.ndet * k * (precision == HINQS_FP64 ? 8 : 4);
+    const uintptr_t x = (uintptr_t)X, y = (uintptr_t)S;
+    if (x < y + bytes && y < x + bytes) return false;
     if (precision == HINQS_FP64)
         dispatch_small<double>(c, c.val.p, c.diag.p, (const double *)X, k, (double *)S, sorted, s);
     else

@@ -46,6 +46,32 @@ def test_sigma_either_side_of_the_small_set_rule(ndet):
             assert torch.equal(products[2], S)
 
 
+@pytest.mark.parametrize("ndet", [5, 400, 8192, 8193])
+def test_caller_order_sigma_into_its_own_input(ndet):
+    """A caller-order product written over X, or over rows shifted against it, is
+    the product of X as it was: the rows come through a copy at every size."""
+    ints, a, b, cfg = W.config_inputs(1, ndet=ndet)
+    log(f"sigma over its own input at {ndet} rows")
+    s = solver_for(ints, a, b, cfg.na, cfg.nb)
+    o = oracle_for(ints, a, b, cfg.na, cfg.nb)
+    rows = np.unique(np.linspace(0, ndet - 1, 300).astype(np.int64))
+    _, r = oracle_rows_as_tuples(o, rows)
+    for k in (1, 3, 8, 16):
+        X = W.random_block(ndet, k, 700 + k)
+        for dtype, tol in ((torch.float64, 1e-12), (torch.float32, 2e-6)):
+            Xd = torch.from_numpy(X).to(dtype).cuda()
+            Xr = Xd.double().cpu().numpy()
+            ref, bound = o.sigma_rows(Xr, rows), row_bound(r, Xr, k)
+            for product in (s.sigma, s.sigma_noalloc):
+                for shift in (0, 4):
+                    buf = torch.zeros((ndet + shift) * k, dtype=dtype, device="cuda")
+                    src, dst = buf[:ndet * k].view(ndet, k), buf[shift * k:].view(ndet, k)
+                    src.copy_(Xd)
+                    product(src, out=dst)
+                    err = np.abs(dst.double().cpu().numpy()[rows] - ref)
+                    assert np.all(err <= tol * bound + 1e-300), (k, dtype, shift)
+
+
 @pytest.mark.parametrize("norb,na,nb,ndet", [(1, 1, 0, 1), (2, 1, 1, 4), (9, 4, 5, 63), (16, 8, 8, 65), (16, 7, 5, 3001),
                                              (17, 6, 5, 2500)])
 def test_rdm12_either_side_of_the_table_rule(norb, na, nb, ndet):
