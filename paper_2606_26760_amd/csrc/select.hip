@@ -15,6 +15,7 @@
 // packed integrals in LDS when they fit.
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <type_traits>
 
 #include "common.hpp"
@@ -868,6 +869,29 @@ int64_t expand(Ctx &c, const double *coeffs, bool sorted, int64_t ntop, int64_t 
     return (int64_t)last[0] + last[1];
 }
 
+namespace {
+
+// Times (us) of the linked class alone: scanning the groups, and through the
+// tables.  The scan's waves take PT2_RUN candidates one after another, 8,192 of
+// them at a time, and wait for each group in turn: about 0.4 us for a few
+// members, 0.95 from about 64 on.  The tables cost their building, then 1.4 us
+// per group and 512 tiles at a time, whatever a tile holds.
+// Whole calls, scan / tables in us: 1e6 rows, groups of 87, 1 candidate 135 / 260,
+// 100 candidates 1028 / 409, 8,000 in as many tiles 1287 / 1685, 1e5 in 11,000
+// 2410 / 2780, 5.4e5 in 18,000 6536 / 5124; 1e5 rows, groups of 9, 2,000 in as
+// many 538 / 569, 30,000 in 8,600 823 / 1810, 5.3e6 in 88,000 25,900 / 23,250;
+// 1,000 rows, 1 candidate 82 / 127, 3,000 in 250 tiles 411 / 250.
+double link_scan_us(const Ctx &c, int moves, int64_t ncand) {
+    const double group = (double)c.ndet / c.nua;
+    const double per_wave = ncand <= 8192 * PT2_RUN ? (double)std::min<int64_t>(ncand, PT2_RUN) : ncand / 8192.0;
+    return per_wave * moves * (0.4 + 0.55 * std::min(1.0, group / 64.0));
+}
+double link_table_us(size_t bytes, int moves, int64_t tiles) {
+    return 40.0 + 0.5e-6 * bytes + moves * 1.4 * std::max(1.0, tiles / 512.0);
+}
+
+}  // namespace
+
 void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, const uint64_t *ca,
          const uint64_t *cb, double *numer, double *hxx, double *score) {
     hipStream_t s = c.stream;
@@ -909,12 +933,38 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
         hipLaunchKernelGGL(k_pt2_diag<false>, dim3(dgrid), dim3(256), 0, s, pa, order);
     }
     HQ_LAUNCH_CHECK();
-    // lookups by the candidates' own moves while the tables stay small; sets of
-    // very many distinct strings keep the scan
+    // lookups by the candidates' own moves while the tables stay small (sets of very
+    // many distinct strings keep the scan) and the candidates share alpha strings
     const int nwords = (c.nub + 31) / 32;
     const int moves = c.na * (c.norb - c.na), moves_b = c.nb * (c.norb - c.nb);
-    const bool lookup = nwords <= PT2_MAX_WORDS && (int64_t)c.nua * nwords * (int64_t)sizeof(uint2) <= PT2_MAX_TABLE &&
-                        moves <= PT2_MAX_MOVES && moves_b <= PT2_MAX_MOVES;
+    const bool fits = nwords <= PT2_MAX_WORDS && (int64_t)c.nua * nwords * (int64_t)sizeof(uint2) <= PT2_MAX_TABLE &&
+                      moves <= PT2_MAX_MOVES && moves_b <= PT2_MAX_MOVES;
+    const size_t table = sizeof(uint2) * (size_t)c.nua * nwords;
+    const double scan = link_scan_us(c, moves, ncand);
+    const char *env = std::getenv("HINQS_PT2_TABLES");  // 0: scan, 1: tables wherever they fit
+    const int asked = env && *env ? std::atoi(env) : -1;
+    const int64_t fewest = (ncand + PT2_TILE - 1) / PT2_TILE;
+    bool lookup = fits && (asked >= 0 ? asked != 0 : link_table_us(table, moves, fewest) <= scan);
+    int32_t *tiles = nullptr, *ntiles = nullptr;
+    if (lookup) {
+        int32_t *flag = c.cs.get<int32_t>(7, 3 * ncand + 1);
+        int32_t *fpos = flag + ncand;
+        tiles = fpos + ncand;
+        ntiles = tiles + ncand;
+        hipLaunchKernelGGL(k_pt2_tile_flags, dim3(grid_for(ncand, 256)), dim3(256), 0, s, keys, ncand, c.norb, flag);
+        HQ_LAUNCH_CHECK();
+        exclusive_scan_i32(s, flag, fpos, ncand, c.work);
+        hipLaunchKernelGGL(k_pt2_tile_list, dim3(grid_for(ncand, 256)), dim3(256), 0, s, flag, fpos, ncand, tiles,
+                           ntiles);
+        HQ_LAUNCH_CHECK();
+        // the number of tiles is read back where it decides
+        if (asked < 0 && link_table_us(table, moves, ncand) > scan) {
+            int32_t nt = 0;
+            HQ_CHECK(hipMemcpyAsync(&nt, ntiles, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            HQ_CHECK(hipStreamSynchronize(s));
+            lookup = link_table_us(table, moves, nt) <= scan;
+        }
+    }
     // resident workgroups only (two per CU); they share the candidates through a counter
     const int64_t runs = (ncand + PT2_RUN - 1) / PT2_RUN;
     const unsigned grid =
@@ -937,19 +987,11 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
     using S4 = std::integral_constant<int, 4>;
     if (lookup) {
         uint2 *tab = c.cs.get<uint2>(6, (size_t)c.nua * nwords);
-        int32_t *flag = c.cs.get<int32_t>(7, 3 * ncand + 1);
-        int32_t *fpos = flag + ncand, *tiles = fpos + ncand, *ntiles = tiles + ncand;
-        HQ_CHECK(hipMemsetAsync(tab, 0, sizeof(uint2) * (size_t)c.nua * nwords, s));
+        HQ_CHECK(hipMemsetAsync(tab, 0, table, s));
         hipLaunchKernelGGL(k_pt2_bits, dim3(grid_for(c.ndet, 256)), dim3(256), 0, s, c.ndet, c.aidx.p, c.bidx.p,
                            nwords, tab);
         HQ_LAUNCH_CHECK();
         hipLaunchKernelGGL(k_pt2_ranks, dim3(grid_for((int64_t)c.nua * 64, 256)), dim3(256), 0, s, c.nua, nwords, tab);
-        HQ_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_pt2_tile_flags, dim3(grid_for(ncand, 256)), dim3(256), 0, s, keys, ncand, c.norb, flag);
-        HQ_LAUNCH_CHECK();
-        exclusive_scan_i32(s, flag, fpos, ncand, c.work);
-        hipLaunchKernelGGL(k_pt2_tile_list, dim3(grid_for(ncand, 256)), dim3(256), 0, s, flag, fpos, ncand, tiles,
-                           ntiles);
         HQ_LAUNCH_CHECK();
         if (use_lds) launch(T{}, S1{}, F{});
         else launch(F{}, S1{}, F{});

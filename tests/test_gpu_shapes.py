@@ -155,6 +155,52 @@ def test_pt2_table_and_scan_paths(kind):
     assert ei.value.name == "BAD_OCCUPATION"
 
 
+def _elapsed(f, repeats=9):
+    """Median time of f in ms."""
+    f()
+    times = []
+    for _ in range(repeats):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        f()
+        t1.record()
+        t1.synchronize()
+        times.append(t0.elapsed_time(t1))
+    return sorted(times)[repeats // 2]
+
+
+def test_pt2_path_follows_the_candidates(monkeypatch):
+    """One candidate, lists spread over thousands of alpha strings and lists that share a
+    few: both paths against the oracle, and the path taken is the faster of the two
+    where they are far apart (measured apart by 2 or more, bound halfway)."""
+    ints, a, b, cfg = W.config_inputs(2, ndet=100_000)
+    log("pt2 of sparse and dense lists, 1e5 determinants")
+    s = solver_for(ints, a, b, cfg.na, cfg.nb)
+    o = oracle_for(ints, a, b, cfg.na, cfg.nb)
+    rng = np.random.default_rng(61)
+    c = rng.standard_normal(len(a))
+    c /= np.linalg.norm(c)
+    cd = torch.from_numpy(c).cuda()
+    sa, sb = W.fci_strings(cfg.norb, cfg.na), W.fci_strings(cfg.norb, cfg.nb)
+    e0 = -1000.0
+    for nalpha, n in ((1, 1), (len(sa), 300), (len(sa), 30_000), (40, 12_000)):
+        pick = sa[rng.permutation(len(sa))[:nalpha]]
+        ca, cb = pick[rng.integers(0, nalpha, n)], sb[rng.integers(0, len(sb), n)]
+        at = rng.permutation(n)[:400]
+        rn, rh, _, absnum = o.pt2(c, e0, ca[at], cb[at], with_scale=True)
+        da, db = (torch.from_numpy(x.astype(np.int64)).cuda() for x in (ca, cb))
+        ms = {}
+        for path in ("0", "1", ""):
+            monkeypatch.setenv("HINQS_PT2_TABLES", path)
+            num, hxx, score = (t.cpu().numpy() for t in s.pt2(cd, e0, da, db))
+            assert np.all(np.abs(num[at] - rn) <= 1e-12 * absnum + 1e-300)
+            assert np.all(np.abs(hxx[at] - rh) <= 1e-12 * np.abs(rh).max())
+            assert np.array_equal(score, num * num / np.abs(e0 - hxx))
+            ms[path] = _elapsed(lambda: s.pt2(cd, e0, da, db))
+        log(f"  {n} candidates, {nalpha} alpha strings: scan {ms['0']:.3f} tables {ms['1']:.3f} chosen {ms['']:.3f} ms")
+        assert ms[""] <= 1.5 * min(ms["0"], ms["1"])
+
+
 @pytest.mark.parametrize("per_lane", [False, True])
 @pytest.mark.parametrize("ndet", [1, 2, 31, 33, 63, 64, 65, 255, 1025])
 def test_couplings_both_enumerators(ndet, per_lane, monkeypatch):
