@@ -458,16 +458,23 @@ constexpr int lanes_per_coupling() {
 
 // Rows a team takes from its XCD's counter at a time; 0: fixed strides.  The
 // atomics on one counter come through at about 24 ns each (1e6 rows, runs of
-// one row: 3.0 ms, all of it the counters), so they pay only where X is many
-// times the L2s: strides / counters in us, k = 1 and 8, 20,000 rows with 356
-// couplings 33 / 170 and 54 / 140, 5e5 with 85 333 / 350 and 457 / 463, 2e5 with
-// 615 565 / 601 and 962 / 938, 1e6 with 156 1098 / 1086 and 1550 / 1505.
+// one row: 3.0 ms, all of it the counters), so they pay only where X is large
+// against the L2s (32 MB) and a row's work against its atomic: strides / counters
+// in us, k = 1 and 8, 20,000 rows with 356 couplings 33 / 170 and 54 / 140, 5e5
+// with 85 333 / 350 and 457 / 463, 2e5 with 615 565 / 601 and 962 / 938, 1e6 with
+// 156 1087 / 1086 and 1648 / 1506, 4e6 with 171 4425 / 4250 and 8321 / 6332, 1e7
+// with 13.5 1327 / 1664 and 2200 / 2554, 6e6 with 23.6 1264 / 1376 and 2110 / 2079,
+// 2e7 with 27 5718 / 5569 and 9390 / 8859; 3e5 with 856, k = 1 (X of 2.4 MB)
+// 1108 / 1150, k = 8 FP32 (9.6 MB) 1449 / 1514.
 constexpr int64_t SIGMA_STATIC_NNZ = 130000000;
+constexpr double SIGMA_COUNTER_ROW = 25.0;       // mean couplings
+constexpr int64_t SIGMA_COUNTER_X = 16 << 20;    // bytes of X
 constexpr double SIGMA_LONG_ROW = 256.0;  // mean couplings from which two rows make a run
 
-int row_run(const Ctx &c, const SigmaCfg &cfg) {
+int row_run(const Ctx &c, const SigmaCfg &cfg, int64_t xbytes) {
     if (cfg.run >= 0) return cfg.run;
-    if (c.nnz <= SIGMA_STATIC_NNZ) return 0;
+    if (c.nnz <= SIGMA_STATIC_NNZ || xbytes < SIGMA_COUNTER_X || (double)c.nnz < SIGMA_COUNTER_ROW * (double)c.ndet)
+        return 0;
     return (double)c.nnz >= SIGMA_LONG_ROW * (double)c.ndet ? 2 : 4;
 }
 
@@ -487,7 +494,7 @@ void launch_sigma_u(const Ctx &c, const SigmaCfg &cfg, const SigmaMask &mk, cons
     XcdRows ranges;
     for (int x = 0; x <= NUM_XCD; ++x) ranges.b[x] = c.xcd_rows[x];
     const int xmap = env_int("HINQS_SIGMA_XCDMAP", 1);
-    const int run = MASK ? 0 : row_run(c, cfg);
+    const int run = MASK ? 0 : row_run(c, cfg, c.ndet * K * (int64_t)sizeof(T));
     hipLaunchKernelGGL((k_sigma<T, K, TEAM, UNR, MASK>), dim3((unsigned)nblk), dim3(SIGMA_BLOCK), 0, s, ranges, mk,
                        xmap, c.rowptr.p, c.col.p, val, diag, X, ldx, S, lds, out,
                        run > 0 ? (ctr ? ctr : c.sigma_ctr.p) : (unsigned long long *)nullptr, std::max(1, run));
@@ -546,7 +553,12 @@ void dispatch_k(const Ctx &c, int k, const SigmaCfg &cfg, const T *val, const T 
 // lanes 94, 230 and 356 32 lanes 113 and 54, 64 lanes 117 and 53; k = 16, eight
 // lanes per coupling: 19 couplings 16 lanes 43 and 32 lanes 55, 356 64 lanes 67 and
 // 32 lanes 75), and the rows' teams fill the chip (5,000 rows of 13: 16 lanes
-// 5.9, 8 lanes 7.2).  Gathers in flight: eight per lane where the row has them
+// 5.9, 8 lanes 7.2).  The same holds for large sets (1e7 rows of 13.5, 8 / 16 / 32 /
+// 64 lanes: k = 1 1327 / 1579 / 2755 / 5527, k = 8 2361 / 2200 / 2460 / 3702; 2e7 of
+// 27, k = 8, 16 / 32 / 64 lanes 8859 / 9148 / 10568), but for their rows of 64 and
+// more (16 / 32 / 64 lanes, k = 1: 2e6 of 86 1372 / 1169 / 1460; k = 8: 2e6 of 86 1920 /
+// 1738 / 1682, 1e6 of 156 1665 / 1499 / 1506, 4e6 of 171 7780 / 6471 / 6332).
+// Gathers in flight: eight per lane where the row has them
 // (k = 8, 356 couplings 52 against 59 with four).  Workgroups per CU: more than are
 // resident even out rows of different length (60,000 rows, k = 8, 8 / 4: 114 / 117)
 // until the rows per team are many (4.9e7 couplings: 4 386, 8 400).
@@ -559,16 +571,12 @@ SigmaCfg default_cfg(const Ctx &c, int k, int precision) {
     const double want = avg / 8.0 * lpn;
     SigmaCfg g;
     g.unr = avg * lpn >= SIGMA_WIDE_ROW ? 4 : 2;
-    g.occ = 4;
-    if (c.nnz <= SIGMA_STATIC_NNZ) {
-        if (lpn >= 8) g.team = avg < 32 ? 16 : avg < 100 ? 32 : 64;
-        else g.team = want <= 3 ? 8 : want <= 16 ? 16 : 32;
-        while (g.team < 64 && c.ndet * g.team < (int64_t)256 * 1024) g.team *= 2;
-        if (c.nnz <= SIGMA_EVEN_NNZ) g.occ = 8;
-        if (c.ndet <= SIGMA_SMALL_ROWS) g.pipe = 2;
-    } else {
-        g.team = lpn >= 4 ? 64 : 32;  // 1e6 rows of 156: k = 8 1509 / 1525, k = 1 1240 / 1086
-    }
+    g.occ = c.nnz <= SIGMA_EVEN_NNZ ? 8 : 4;
+    if (lpn >= 8) g.team = avg < 32 ? 16 : avg < 100 ? 32 : 64;
+    else g.team = want <= 3 ? 8 : want <= 16 ? 16 : 32;
+    if (c.nnz > SIGMA_STATIC_NNZ && avg >= 64.0) g.team = lpn >= 4 ? 64 : 32;
+    while (g.team < 64 && c.ndet * g.team < (int64_t)256 * 1024) g.team *= 2;
+    if (c.ndet <= SIGMA_SMALL_ROWS) g.pipe = 2;
     return g;
 }
 

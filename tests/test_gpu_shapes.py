@@ -12,6 +12,20 @@ from tests.gpu_helpers import (gpu_rows_as_tuples, log, oracle_for, oracle_rows_
 pytestmark = pytest.mark.gpu
 
 
+def _elapsed(f, repeats=9):
+    """Median time of f in ms."""
+    f()
+    times = []
+    for _ in range(repeats):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        f()
+        t1.record()
+        t1.synchronize()
+        times.append(t0.elapsed_time(t1))
+    return sorted(times)[repeats // 2]
+
+
 @pytest.mark.parametrize("ndet", [1, 5, 8192, 8193])
 def test_sigma_either_side_of_the_small_set_rule(ndet):
     """One wave per row up to 8,192 rows, teams with staging above: widths that
@@ -153,20 +167,6 @@ def test_pt2_table_and_scan_paths(kind):
     with pytest.raises(hq.HinqsError) as ei:
         s.pt2(cd, e0, bad_a, cb)
     assert ei.value.name == "BAD_OCCUPATION"
-
-
-def _elapsed(f, repeats=9):
-    """Median time of f in ms."""
-    f()
-    times = []
-    for _ in range(repeats):
-        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        t0.record()
-        f()
-        t1.record()
-        t1.synchronize()
-        times.append(t0.elapsed_time(t1))
-    return sorted(times)[repeats // 2]
 
 
 def test_pt2_path_follows_the_candidates(monkeypatch):
@@ -365,3 +365,45 @@ def test_sigma_lanes_and_steps(ndet, team, unr, monkeypatch):
                 for P in (S, back):
                     err = np.abs(P.double().cpu().numpy()[rows] - ref)
                     assert np.all(err <= tol * bound + 1e-300), (k, dtype, run)
+
+
+def test_default_shape_of_a_large_set_with_short_rows(monkeypatch):
+    """1e7 rows of 13.5 couplings take as few lanes per row as those of a small set: the
+    untuned product against teams of 8 and 16 lanes in time (32 and 64 lanes take 1.7
+    to 4 times as long, bound at 1.4) and in value, and one row against the oracle."""
+    rng = np.random.default_rng(71)
+    norb, ne, n = 19, 9, 10_000_000
+    st = W.fci_strings(norb, ne)
+    key = np.unique(rng.integers(0, len(st) ** 2, n + n // 100))
+    key = rng.permutation(key)[:n]
+    a, b = st[key // len(st)], st[key % len(st)]
+    log(f"sigma of {n} rows, norb {norb}")
+    ints = W.gen_integrals(norb, 1, -2.0, -0.5, 72)
+    s = solver_for(ints, a, b, ne, ne)
+    perm = s.permutation().long()
+    for k in (1, 8):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(k)
+        X = torch.randn((n, k), dtype=torch.float64, device="cuda", generator=g)
+        out, ref, ms = torch.empty_like(X), torch.empty_like(X), {}
+        ms["default"] = _elapsed(lambda: s.sigma(X, out=out, sorted_order=True))
+        for team in ("8", "16"):
+            monkeypatch.setenv("HINQS_SIGMA_TEAM", team)
+            monkeypatch.setenv("HINQS_SIGMA_RUN", "0")
+            ms[team] = _elapsed(lambda: s.sigma(X, out=ref, sorted_order=True))
+            assert float((out - ref).abs().max()) <= 1e-12 * float(ref.abs().max())
+        monkeypatch.delenv("HINQS_SIGMA_TEAM")
+        monkeypatch.delenv("HINQS_SIGMA_RUN")
+        log(f"  k {k}: " + ", ".join(f"{t} {v:.3f} ms" for t, v in ms.items()))
+        assert ms["default"] <= 1.4 * min(ms["8"], ms["16"])
+    # the determinants at most two electrons from one of them
+    i = int(perm[n // 2])
+    near = np.flatnonzero(np.bitwise_count(a ^ a[i]).astype(int) + np.bitwise_count(b ^ b[i]) <= 4)
+    assert 2 <= len(near) <= 200
+    sub = oracle_for(ints, a[near], b[near], ne, ne)
+    x = np.random.default_rng(73).standard_normal(n)
+    got = float(s.sigma(torch.from_numpy(x).cuda())[i])
+    at = int(np.flatnonzero(near == i)[0])
+    want = float(sub.sigma_rows(x[near][:, None], np.array([at]))[0, 0])
+    _, r = oracle_rows_as_tuples(sub, np.array([at]))
+    assert abs(got - want) <= 1e-12 * row_bound(r, x[near][:, None], 1)[0, 0]
