@@ -52,11 +52,11 @@ struct BatchState {
     DBuf<int32_t> row_inst; // global row -> instance
     DBuf<int64_t> inst_row; // row offsets (ninst + 1), device copy
     bool dirty = true;      // inst_row and the XCD row ranges need a refresh
-    // launch shape of the batched iteration (chunk rows of the tall-skinny
-    // kernels, threads of the Rayleigh-Ritz kernel), per block-size index;
-    // tuned[k] says the shape was timed for the current instances
+    // launch shape of the batched iteration (most rows of a chunk of the
+    // tall-skinny kernels, threads of the Rayleigh-Ritz kernel), per block-size
+    // index; tuned_key says which instances it was timed for
     struct Shape {
-        int chunk = 0;  // 0: by the number of rows (default_chunk)
+        int chunk = 2048;
         int rr_threads = 1024;
         double ms_per_it = 0.0;
     };
@@ -1139,13 +1139,14 @@ struct Resources {  // released on every exit path
     }
 };
 
-// Rows per chunk before tuning: one workgroup works on a chunk, so a batch of
-// fewer than 256 * 2,048 rows takes smaller ones and keeps about one per CU
+// Rows of a chunk: at most `limit`, and fewer in a batch of under 256 chunks of
+// that size, since one workgroup works on a chunk and one per CU should be left
 // (67,500 rows in 12 instances, solve of 58 iterations with chunks of 2048 / 1024 /
 // 512 / 256 / 128 / 64 rows: 40.7 / 34.0 / 30.9 / 30.1 / 30.4 / 32.6 ms; the sums over
-// chunks grow with their number).
-int default_chunk(int64_t rows) {
-    return (int)std::min<int64_t>(2048, std::max<int64_t>(128, (rows / 256 + 63) / 64 * 64));
+// chunks grow with their number).  It holds for a tuned limit too: its smallest is
+// 1,024 rows, and a tuned small batch would be slower than an untuned one.
+int chunk_rows(int limit, int64_t rows) {
+    return (int)std::min<int64_t>(limit, std::max<int64_t>(128, (rows / 256 + 63) / 64 * 64));
 }
 
 template <int KK>
@@ -1161,7 +1162,8 @@ int batch_solve_k(Ctx &c, BatchState &B, const hinqs_opts &o, int mmax, const Ba
     const SigmaCfg scfg = sigma_config(B.g, KK, HINQS_FP64);
 
     // ---- chunk list: runs of at most CH rows of one instance
-    const int CH = std::max(64, env_or("HINQS_BATCH_CHUNK", shape.chunk > 0 ? shape.chunk : default_chunk(N)));
+    const int asked = env_or("HINQS_BATCH_CHUNK", 0);
+    const int CH = asked > 0 ? std::max(64, asked) : chunk_rows(shape.chunk, N);
     const int RRT = env_or("HINQS_BATCH_RR_THREADS", shape.rr_threads);
     if (RRT != 256 && RRT != 512 && RRT != 1024)
         throw Error(HINQS_E_INVALID_ARG, "Rayleigh-Ritz threads must be 256, 512 or 1024");
@@ -1437,7 +1439,7 @@ int batch_solve_k(Ctx &c, BatchState &B, const hinqs_opts &o, int mmax, const Ba
         stats->sigma_unroll = scfg.unr;
         stats->sigma_occupancy = scfg.occ;
         stats->sigma_elements = elements;
-        stats->chunk_rows = CH;
+        stats->chunk_rows = asked > 0 ? CH : shape.chunk;
         stats->rr_threads = RRT;
     }
     return nconv == nb ? HINQS_OK : HINQS_E_NOT_CONVERGED;
@@ -1477,7 +1479,7 @@ void batch_shape_store(const std::string &key, const BatchState::Shape &sh) {
 }
 
 // Times `iters` iterations of the batched solve for each candidate shape
-// (chunk rows 1024..8192, Rayleigh-Ritz threads 512 or 1024; every candidate
+// (chunks of at most 1024..8192 rows, Rayleigh-Ritz threads 512 or 1024; every candidate
 // starts from the same initial block) and returns the fastest per iteration.
 template <typename F>
 BatchState::Shape tune_batch_shape(const BatchState &B, int iters, F &&time_it) {
@@ -1485,8 +1487,11 @@ BatchState::Shape tune_batch_shape(const BatchState &B, int iters, F &&time_it) 
     static const int threads[] = {512, 1024};
     BatchState::Shape best;
     best.ms_per_it = 1e30;
+    int rows = 0;
     for (int ch : chunks) {
         if (ch > 2 * B.g.ndet / std::max<size_t>(1, B.meta.size()) && ch != chunks[0]) continue;
+        if (chunk_rows(ch, B.g.ndet) == rows) continue;  // the same chunks again
+        rows = chunk_rows(ch, B.g.ndet);
         for (int nt : threads) {
             BatchState::Shape sh;
             sh.chunk = ch;

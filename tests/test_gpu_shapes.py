@@ -407,3 +407,22 @@ def test_default_shape_of_a_large_set_with_short_rows(monkeypatch):
     want = float(sub.sigma_rows(x[near][:, None], np.array([at]))[0, 0])
     _, r = oracle_rows_as_tuples(sub, np.array([at]))
     assert abs(got - want) <= 1e-12 * row_bound(r, x[near][:, None], 1)[0, 0]
+
+
+def test_tuned_small_batch_runs_the_untuned_chunks(monkeypatch):
+    """A batch too small for 256 chunks of the tuner's smallest size is cut finer whether it
+    was tuned or not: with the threads and the product's shape held, both solves sum
+    in the same order, so energies and vectors are equal in every bit."""
+    for name, v in (("SIGMA_TEAM", 16), ("SIGMA_UNR", 4), ("SIGMA_OCC", 4), ("BATCH_RR_THREADS", 1024)):
+        monkeypatch.setenv("HINQS_" + name, str(v))
+    results = []
+    for tune in (False, True):
+        s = hq.Hinqs()
+        for i in (18, 29, 40, 51):
+            ints, a, b, spec = W.batch_instance(i, 0.1)
+            s.batch_add(ints.h, ints.eri, ints.e_core, a, b, spec["na"], spec["nb"])
+        e, c, info = s.batch_lowest_eigenpair(tol=1e-9, autotune=tune)
+        log(f"batch, tuned {tune}: {info['stats']['iterations']} iterations, {info['stats']['ms_iterations']:.2f} ms")
+        assert (info["stats"]["ms_tune"] > 0.0) == tune
+        results.append((e, c))
+    assert np.array_equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
