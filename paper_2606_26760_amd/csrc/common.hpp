@@ -433,8 +433,9 @@ void sigma_sorted(Ctx &c, int k, const void *X, int ldx, void *S, int lds, int p
                   hipStream_t s, unsigned long long *ctr = nullptr, const SigmaOut &out = SigmaOut{});
 
 // S = H X in one launch for a small set: X, S in caller order or sorted, any k
-// in [1, 16], any alignment.  False (nothing done) when the set or its tuned
-// shape takes the general kernel, or X and S share memory.
+// in [1, 16], any alignment.  False (nothing done) when the set, or for a product
+// that needs no staging its tuned shape, takes the general kernel, or X and S share
+// memory.
 bool sigma_small(const Ctx &c, int k, const void *X, void *S, int precision, bool sorted, hipStream_t s);
 
 // No-allocation sigma (noalloc.hip).  noalloc_setup: once per device, with

@@ -624,7 +624,12 @@ void sigma_sorted(Ctx &c, int k, const void *X, int ldx, void *S, int lds, int p
 
 bool sigma_small(const Ctx &c, int k, const void *X, void *S, int precision, bool sorted, hipStream_t s) {
     const int K = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
-    if (sigma_config(c, K, precision).pipe != 2) return false;
+    // A tuned shape was timed on products in sorted order, aligned and of K columns.
+    // Any other product of a small set would be staged first, which this launch
+    // saves, so no tuned shape takes it away.
+    const bool direct = sorted && K == k && (uintptr_t)X % 16 == 0 && (uintptr_t)S % 16 == 0;
+    const bool asked = std::getenv("HINQS_SIGMA_TEAM") || std::getenv("HINQS_SIGMA_PIPE");
+    if ((direct || asked || c.ndet > SIGMA_SMALL_ROWS) && sigma_config(c, K, precision).pipe != 2) return false;
     // the launch reads X while others of its waves write S: arrays that share
     // memory take the path that copies X first
     const size_t bytes = (size_t)c.ndet * k * (precision == HINQS_FP64 ? 8 : 4);

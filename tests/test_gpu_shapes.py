@@ -1,5 +1,9 @@
 """Edges of the kernels' size rules: the sizes where a launch shape, a tile or a
 class of rows changes, against the CPU oracle."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -10,6 +14,8 @@ from tests.gpu_helpers import (gpu_rows_as_tuples, log, oracle_for, oracle_rows_
                                solver_for)
 
 pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _elapsed(f, repeats=9):
@@ -426,3 +432,46 @@ def test_tuned_small_batch_runs_the_untuned_chunks(monkeypatch):
         assert (info["stats"]["ms_tune"] > 0.0) == tune
         results.append((e, c))
     assert np.array_equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+
+
+_TUNED_CHILD = """
+import sys
+import numpy as np, torch
+import paper_2606_26760_amd as hq
+import workloads as W
+ndet = int(sys.argv[1])
+ints, a, b, cfg = W.config_inputs(1, ndet=ndet)
+s = hq.Hinqs()
+s.set_integrals(ints.h, ints.eri, ints.e_core)
+s.set_determinants(a, b, cfg.na, cfg.nb)
+X = torch.from_numpy(W.random_block(ndet, 8, 5)).cuda()
+before = s.sigma(X)
+shape, ms = s.autotune(8, hq.HINQS_FP64)
+print("shape", *shape[:3], ms, int(torch.equal(before, s.sigma(X))), flush=True)
+"""
+
+
+def _tuned_child(path, ndet=3001):
+    """One process that reads the plans of ``path``: (team, unroll, workgroups), ms of the
+    plan, and whether a caller-order product kept its bits."""
+    env = dict(os.environ, HINQS_TUNE_CACHE=str(path), PYTHONPATH=ROOT)
+    for name in [n for n in env if n.startswith("HINQS_SIGMA_")]:
+        del env[name]
+    r = subprocess.run([sys.executable, "-c", _TUNED_CHILD, str(ndet)], cwd=ROOT, env=env, capture_output=True,
+                       text=True, timeout=100)
+    assert r.returncode == 0, r.stderr
+    f = r.stdout.split("shape", 1)[1].split()
+    return tuple(int(x) for x in f[:3]), float(f[3]), f[4] == "1"
+
+
+def test_tuned_shape_leaves_staged_products_of_small_sets_alone(tmp_path):
+    """A team shape tuned for a small set serves the products it was timed on (sorted,
+    aligned); a caller-order one keeps the launch that needs no staging, bit for bit."""
+    log("a plan with a team shape for 3,001 rows")
+    plans = tmp_path / "plans"
+    _tuned_child(plans)
+    key = plans.read_text().split()[0]
+    plans.write_text(f"{key} 16 4 4 0 0.125\n")
+    shape, ms, same = _tuned_child(plans)
+    assert shape == (16, 4, 4) and ms == 0.125
+    assert same
