@@ -1,8 +1,9 @@
 // Launch-shape autotuner of the block-sigma kernel: times the candidate
 // shapes (team width, software-pipeline depth, workgroups per CU) on the
-// problem at hand with HIP events and keeps the fastest.  Results are cached per process, keyed by device architecture,
-// precision, block size and problem-size class, and optionally in a text
-// file named by HINQS_TUNE_CACHE.
+// problem at hand with HIP events and keeps the fastest.  Results are cached
+// per process, keyed by device architecture, plan version, precision, block
+// size and problem-size class, and optionally in a text file named by
+// HINQS_TUNE_CACHE.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -29,14 +30,19 @@ int kindex(int k) { return k <= 1 ? 0 : k <= 2 ? 1 : k <= 4 ? 2 : k <= 8 ? 3 : 4
 std::mutex g_tune_mutex;
 std::map<std::string, SigmaCfg> g_tune_cache;
 
+// The kernels that a plan's numbers mean: raised when a field changes its meaning or
+// its kernel is replaced, so that plans saved for other kernels are tuned again.
+constexpr int PLAN_VERSION = 2;
+
 std::string tune_key(const Ctx &c, int k, int precision) {
     hipDeviceProp_t prop;
     std::string arch = "gpu";
     if (hipGetDeviceProperties(&prop, c.device) == hipSuccess) arch = prop.gcnArchName;
     const int dbucket = c.ndet > 0 ? (int)std::lround(2.0 * std::log2((double)c.ndet)) : 0;
     const int nbucket = c.ndet > 0 ? (int)std::lround((double)c.nnz / (double)c.ndet / 16.0) : 0;
-    return arch + "|p" + std::to_string(precision) + "|k" + std::to_string(k) + "|d" + std::to_string(dbucket) +
-           "|n" + std::to_string(nbucket);
+    // sets on either side of SIGMA_SMALL_ROWS take different kernels and share a bucket
+    return arch + "|v" + std::to_string(PLAN_VERSION) + "|p" + std::to_string(precision) + "|k" + std::to_string(k) +
+           (c.ndet <= SIGMA_SMALL_ROWS ? "|s" : "|d") + std::to_string(dbucket) + "|n" + std::to_string(nbucket);
 }
 
 void load_tune_file() {

@@ -475,3 +475,20 @@ def test_tuned_shape_leaves_staged_products_of_small_sets_alone(tmp_path):
     shape, ms, same = _tuned_child(plans)
     assert shape == (16, 4, 4) and ms == 0.125
     assert same
+
+
+def test_plans_of_other_kernels_and_of_the_other_size_class_are_not_used(tmp_path):
+    """A plan saved under a key without the kernels' version is tuned again, and so is a set
+    of 8,193 rows after one of 8,192, which runs another kernel."""
+    log("plans without a version; plans of 8,192 and 8,193 rows")
+    plans = tmp_path / "plans"
+    _tuned_child(plans)
+    key = plans.read_text().split()[0]
+    old = "|".join(p for p in key.split("|") if not p.startswith("v")).replace("|s", "|d")
+    plans.write_text(f"{old} 16 4 4 1 0.125\n")
+    assert _tuned_child(plans)[1] != 0.125
+    times = []
+    for ndet in (8192, 8193):
+        ints, a, b, cfg = W.config_inputs(1, ndet=ndet)
+        times.append(solver_for(ints, a, b, cfg.na, cfg.nb).autotune(4, hq.HINQS_FP32)[1])
+    assert times[0] != times[1]
