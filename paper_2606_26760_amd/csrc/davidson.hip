@@ -38,6 +38,7 @@
 #include <numeric>
 
 #include "common.hpp"
+#include "host_loops.hpp"
 
 namespace hinqs {
 
@@ -554,45 +555,6 @@ void jacobi_eig(int n, std::vector<double> A, std::vector<double> &w, std::vecto
         for (int k = 0; k < n; ++k) Z[(size_t)k * n + c] = V[(size_t)k * n + ord[c]];
     }
 }
-
-// Inner loops of the host eigensolver, built for the wide vectors of current
-// processors as well.
-#ifdef __HIP_DEVICE_COMPILE__
-#define HINQS_WIDE
-#else
-#define HINQS_WIDE __attribute__((target_clones("avx512f", "avx2", "default")))
-#endif
-// p[0:n) = sum_j x[j] a_j[0:n), rows a_j of a with leading dimension lda
-HINQS_WIDE void rows_combine(int n, int rows, const double *__restrict__ a, int lda,
-                             const double *__restrict__ x, double *__restrict__ p) {
-    for (int i = 0; i < n; ++i) p[i] = 0.0;
-    for (int j = 0; j < rows; ++j)
-        for (int i = 0; i < n; ++i) p[i] += x[j] * a[(size_t)j * lda + i];
-}
-// a -= v q^T + q v^T
-HINQS_WIDE void rank2_update(int n, double *__restrict__ a, int lda, const double *__restrict__ v,
-                             const double *__restrict__ q) {
-    for (int i = 0; i < n; ++i)
-        for (int j = 0; j < n; ++j) a[(size_t)i * lda + j] -= v[i] * q[j] + q[i] * v[j];
-}
-// rows z0, z1 <- c z0 + s z1, c z1 - s z0
-HINQS_WIDE void rotate_pair(int n, double c, double s, double *__restrict__ z0, double *__restrict__ z1) {
-    for (int q = 0; q < n; ++q) {
-        const double x = z0[q], y = z1[q];
-        z0[q] = c * x + s * y;
-        z1[q] = c * y - s * x;
-    }
-}
-// z -= (beta v) (v^T z) for the rows x nvec matrix z; t: nvec elements
-HINQS_WIDE void reflect(int rows, int nvec, double beta, const double *__restrict__ v, double *__restrict__ z,
-                        double *__restrict__ t) {
-    for (int q = 0; q < nvec; ++q) t[q] = 0.0;
-    for (int i = 0; i < rows; ++i)
-        for (int q = 0; q < nvec; ++q) t[q] += v[i] * z[(size_t)i * nvec + q];
-    for (int i = 0; i < rows; ++i)
-        for (int q = 0; q < nvec; ++q) z[(size_t)i * nvec + q] -= beta * v[i] * t[q];
-}
-#undef HINQS_WIDE
 
 // The lowest nvec eigenpairs of a symmetric n x n matrix (all eigenvalues,
 // ascending, in w; vectors as the columns of the n x nvec row-major Z) by

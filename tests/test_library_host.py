@@ -4,6 +4,7 @@ operator application.  No GPU computation happens here."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -86,3 +87,67 @@ def test_create_rejects_half_an_allocator():
     assert lib.hinqs_create(ctypes.byref(h), 0, None, alloc, hq.FREE_FN(), None) == -1
     assert lib.hinqs_create(ctypes.byref(h), 0, None, hq.ALLOC_FN(), free, None) == -1
     assert h.value is None
+
+
+_LOOPS = r"""
+#include <cstdio>
+#include <cstdint>
+#include <cstring>
+#include <vector>
+#include "host_loops.hpp"
+using namespace hinqs;
+static uint64_t seed = 12345;
+static double draw() {
+    seed = seed * 6364136223846793005ull + 1442695040888963407ull;
+    return (double)(int64_t)(seed >> 11) / 4503599627370496.0 - 1.0;
+}
+static std::vector<double> fill(size_t n) {
+    std::vector<double> v(n);
+    for (auto &x : v) x = draw();
+    return v;
+}
+static void show(const std::vector<double> &v) {
+    uint64_t h = 1469598103934665603ull;
+    for (double x : v) {
+        uint64_t b;
+        std::memcpy(&b, &x, 8);
+        h = (h ^ b) * 1099511628211ull;
+    }
+    std::printf("%016llx\n", (unsigned long long)h);
+}
+int main() {
+    for (int n : {1, 2, 3, 7, 8, 9, 17, 48}) {
+        auto a = fill((size_t)n * n), x = fill(n), y = fill(n), p = fill(n), z = fill((size_t)n * 8), t = fill(8);
+        rows_combine(n, n, a.data(), n, x.data(), p.data());
+        show(p);
+        rank2_update(n, a.data(), n, x.data(), y.data());
+        show(a);
+        reflect(n, 8, 0.7, x.data(), z.data(), t.data());
+        rotate_pair(n, 0.6, 0.8, x.data(), y.data());
+        show(z);
+        show(x);
+        show(y);
+    }
+}
+"""
+
+
+def test_host_eigensolver_loops_round_alike_on_every_processor(tmp_path):
+    """The loops are built for several processors and chosen when the library is loaded: the
+    builds that this processor runs give the same bits, so a solve does not depend on the
+    host.  Compiled here one by one, with the library's compiler."""
+    flags = open("/proc/cpuinfo").read().split()
+    src = tmp_path / "loops.cpp"
+    src.write_text(_LOOPS)
+    hashes = {}
+    for name, need, target in (("default", None, ""), ("arch=haswell", "fma", "arch=haswell"),
+                               ("avx512f", "avx512f", "avx512f")):
+        if need and need not in flags:
+            continue
+        wide = f'-DHINQS_WIDE=__attribute__((target("{target}")))' if target else "-DHINQS_WIDE="
+        exe = tmp_path / f"loops_{len(hashes)}"
+        subprocess.run(["/opt/rocm/llvm/bin/clang++", "-O3", "-std=c++17", "-ffp-contract=fast", wide, "-I",
+                        os.path.join(ROOT, "paper_2606_26760_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+        hashes[name] = subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout
+    assert len(hashes["default"].split()) == 40
+    assert len(hashes) >= 2 and len(set(hashes.values())) == 1, hashes
