@@ -492,3 +492,72 @@ def test_plans_of_other_kernels_and_of_the_other_size_class_are_not_used(tmp_pat
         ints, a, b, cfg = W.config_inputs(1, ndet=ndet)
         times.append(solver_for(ints, a, b, cfg.na, cfg.nb).autotune(4, hq.HINQS_FP32)[1])
     assert times[0] != times[1]
+
+
+@pytest.mark.parametrize("path", ["0", "1"])
+@pytest.mark.parametrize("n", [200, 700])
+def test_pt2_malformed_candidates_are_nan_alone(n, path, monkeypatch):
+    """Wrong counts and bits at or above norb, alone in a tile and among others that share
+    their strings: those outputs are NaN, every other one is that of the clean list."""
+    norb, na, nb, a, b = _pt2_set("large group")
+    log(f"pt2 with malformed candidates, {n} candidates, path {path}")
+    monkeypatch.setenv("HINQS_PT2_TABLES", path)
+    ints = W.gen_integrals(norb, 2, -2.0, -0.5, 88)
+    s = solver_for(ints, a, b, na, nb)
+    rng = np.random.default_rng(62)
+    cd = torch.from_numpy(rng.standard_normal(len(a))).cuda()
+    ua, ub = np.unique(a), np.unique(b)
+    ca, cb = ua[rng.integers(0, 6, n)], ub[rng.integers(0, len(ub), n)]
+    clean = [t.cpu().numpy() for t in s.pt2(cd, -1000.0, ca, cb)]
+    bad = rng.permutation(n)[:n // 10]
+    xa, xb = ca.copy(), cb.copy()
+    for i, at in enumerate(bad):
+        if i % 4 == 0:
+            xa[at] ^= np.uint64(1)                         # one electron more or less
+        elif i % 4 == 1:
+            xb[at] ^= np.uint64(1)
+        elif i % 4 == 2:
+            xa[at] |= np.uint64(1 << norb)
+        else:
+            xb[at] |= np.uint64(1 << 40)
+    da, db = (torch.from_numpy(x.view(np.int64)).cuda() for x in (xa, xb))
+    out = [torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(3)]
+    rc = s._lib.hinqs_pt2(s._h, s._ptr(cd), -1000.0, n, s._ptr(da), s._ptr(db), *[s._ptr(t) for t in out], 0)
+    assert rc != 0
+    with pytest.raises(hq.HinqsError) as ei:
+        s._check(rc)
+    assert ei.value.name == "BAD_OCCUPATION"
+    good = np.setdiff1d(np.arange(n), bad)
+    for got, ref in zip(out, clean):
+        got = got.cpu().numpy()
+        assert np.all(np.isnan(got[bad])) and np.array_equal(got[good], ref[good])
+
+
+@pytest.mark.parametrize("block,max_space", [(4, 24), (8, 48), (8, 60), (16, 96)])
+@pytest.mark.parametrize("ndet", [65, 1025])
+def test_solver_finds_the_lowest_state(ndet, block, max_space):
+    """With four or more roots followed, the state found is the lowest one: the residual's
+    norm (tol) bounds its distance from the dense spectrum's first value."""
+    log(f"lowest state of {ndet} rows, block {block}, max_space {max_space}")
+    ints = W.gen_integrals(9, 3, -2.0, -0.5, 41)
+    a, b = W.sample_determinants(9, 4, 5, ndet, 0.4, 0.0, 42 + ndet)
+    s, o = solver_for(ints, a, b, 4, 5), oracle_for(ints, a, b, 4, 5)
+    for mixed in (False, True):
+        e, _, st = s.lowest_eigenpair(block=block, max_space=max_space, tol=1e-9, max_iter=2000, mixed=mixed)
+        w = o.spectrum(ndet)
+        assert st["converged"] and abs(e - w[0]) <= 1e-9 + 1e-12 * np.abs(w).max(), (e, w[:4])
+
+
+@pytest.mark.parametrize("block,max_space", [(4, 24), (8, 48), (8, 56), (16, 64)])
+def test_batch_finds_the_lowest_states(block, max_space):
+    log(f"lowest states of a batch, block {block}, max_space {max_space}")
+    ints = W.gen_integrals(9, 3, -2.0, -0.5, 31)
+    s, ref = hq.Hinqs(), []
+    for n in (65, 129, 301, 1025):
+        a, b = W.sample_determinants(9, 4, 5, n, 0.4, 0.0, 32 + n)
+        s.batch_add(ints.h, ints.eri, ints.e_core, a, b, 4, 5)
+        ref.append(oracle_for(ints, a, b, 4, 5).spectrum(n))
+    e, _, info = s.batch_lowest_eigenpair(block=block, max_space=max_space, tol=1e-9, max_iter=600)
+    assert info["converged"]
+    for x, w in zip(e, ref):
+        assert abs(x - w[0]) <= 1e-9 + 1e-12 * np.abs(w).max(), (x, w[:4])
