@@ -241,9 +241,9 @@ constexpr int SIGMA_CTR_WORDS = 8 * 32;
 // flight per lane, workgroups per CU.
 struct SigmaCfg {
     int team = 0, unr = 0, occ = 0;
-    int pipe = 0;     // 2: small sets, one wave per row; 0 (or 1, in saved plans): teams
+    int pipe = 0;     // 2: small sets, one wave per row; otherwise teams
     int run = -1;     // rows a team takes from its XCD's row counter at a time, 0: fixed strides,
-                      // -1: by the size of the set (pipe 0)
+                      // -1: by the set and the width (teams)
     double ms = 0.0;  // measured time of one launch when chosen by the tuner
 };
 

@@ -241,7 +241,8 @@ __global__ __launch_bounds__(256) void k_connect_rows(ConnArgs a, int64_t *count
     __shared__ RowQueue<FILL ? RW : 1> queues[FILL ? 4 : 1];
     RowQueue<FILL ? RW : 1> &queue = queues[FILL ? threadIdx.x >> 6 : 0];
     const int lane = threadIdx.x & 63;
-    const int64_t t0 = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6)) * (int64_t)RW;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6));
+    const int64_t t0 = wave * (int64_t)RW;
     if (t0 >= a.ndet) return;
     const uint64_t below = ((uint64_t)1 << lane) - 1;
     int64_t row[RW], out[RW];
@@ -482,10 +483,10 @@ void build_connectivity(Ctx &c, bool xcd_rows) {
     const int64_t n = c.ndet;
     // lookups replace the scan only where a group is very long next to the
     // number of beta moves: a lookup is a binary search whose loads differ
-    // from lane to lane, while a scan step tests 16 candidates with loads that
-    // neighbouring threads share (measured: lookups in every group 4x slower
-    // on the sampled 1e6 set, and no faster on product spaces with groups of
-    // 1,716 and 3,432 rows)
+    // from lane to lane, while a scan step tests CONNECT_W candidates with loads
+    // that neighbouring threads share (against steps of 16 strings: lookups in
+    // every group 4x slower on the sampled 1e6 set, and no faster on product
+    // spaces with groups of 1,716 and 3,432 rows)
     const int32_t nmoves = c.nb * (c.norb - c.nb);
     const int32_t lookup_min = env_i32("HINQS_CONNECT_LOOKUP_MIN", std::max<int32_t>(4096, 64 * nmoves));
     ConnArgs a{n,          c.sa.p,        c.sb.p,        c.aidx.p,  c.bidx.p,

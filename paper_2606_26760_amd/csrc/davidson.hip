@@ -10,8 +10,9 @@
 // the caches, and its output Wn is appended to W afterwards.
 //
 // Per iteration:
-//   Rayleigh-Ritz on G = V^T W         host Householder + implicit QL, lowest vectors (cyclic
-//                                      Jacobi if QL does not converge), m <= 96
+//   Rayleigh-Ritz on G = V^T W         host Householder + implicit QL, lowest
+//                                      vectors (cyclic Jacobi if QL does not
+//                                      converge), m <= 96
 //   T = (W y - theta V y) / (theta - H_ii)   fused Ritz/residual/preconditioner
 //                                      (V y, W y on FP64 MFMA, like every
 //                                      tall-skinny product of the solver)
@@ -163,10 +164,12 @@ __global__ __launch_bounds__(GRAM_BLOCK) void k_gram(int64_t nrows, Mat A, int m
 // and 65 us for a pass of its own.  Y lies in LDS in operand order: held in
 // registers it leaves two waves per SIMD instead of four (203 us).
 template <int KB, int STEPS, bool PROJ>
-__global__ __launch_bounds__(256, STEPS <= 12 ? 4 : 2) void k_ritz(int64_t nrows, int m, Mat V, Mat W, const double *__restrict__ Y,
-                                              const double *__restrict__ theta, const double *__restrict__ diag,
-                                              double floor_, int nroots, double *__restrict__ T,
-                                              double *__restrict__ partial) {
+__global__ __launch_bounds__(256, STEPS <= 12 ? 4 : 2) void k_ritz(int64_t nrows, int m, Mat V, Mat W,
+                                                                   const double *__restrict__ Y,
+                                                                   const double *__restrict__ theta,
+                                                                   const double *__restrict__ diag, double floor_,
+                                                                   int nroots, double *__restrict__ T,
+                                                                   double *__restrict__ partial) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 15, kk = lane >> 4;
     __shared__ double yv[STEPS][64];  // Y in operand order
@@ -757,7 +760,7 @@ struct Solver {
         Wnm = Mat{Wn.p, K, (int64_t)bsz};
         small.ensure(96 * 96 * 2);
         nblk_gram = gram_blocks_for(D);
-partial.ensure(std::max<size_t>((size_t)nblk_gram * 96 * 16, (size_t)tall_grid() * (2 + nblocks * K) * K));
+        partial.ensure(std::max<size_t>((size_t)nblk_gram * 96 * 16, (size_t)tall_grid() * (2 + nblocks * K) * K));
         HQ_CHECK(hipMemsetAsync(Vb.p, 0, sizeof(double) * bsz * nblocks, s));
         HQ_CHECK(hipMemsetAsync(Wb.p, 0, sizeof(double) * bsz * nblocks, s));
         HQ_CHECK(hipMemsetAsync(T.p, 0, sizeof(double) * bsz, s));
@@ -812,12 +815,13 @@ partial.ensure(std::max<size_t>((size_t)nblk_gram * 96 * 16, (size_t)tall_grid()
         const int64_t ntiles = (D + 15) / 16;
         const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((ntiles + 3) / 4, 2048));
         dim3 g(grid), b(256);
+        double *const none = nullptr;
         if (nc <= 16) {
-            if (m <= 48) hipLaunchKernelGGL((k_tsmm<1, 12>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, (double *)nullptr);
-            else hipLaunchKernelGGL((k_tsmm<1, 24>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, (double *)nullptr);
+            if (m <= 48) hipLaunchKernelGGL((k_tsmm<1, 12>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, none);
+            else hipLaunchKernelGGL((k_tsmm<1, 24>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, none);
         } else {
-            if (m <= 48) hipLaunchKernelGGL((k_tsmm<2, 12>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, (double *)nullptr);
-            else hipLaunchKernelGGL((k_tsmm<2, 24>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, (double *)nullptr);
+            if (m <= 48) hipLaunchKernelGGL((k_tsmm<2, 12>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, none);
+            else hipLaunchKernelGGL((k_tsmm<2, 24>), g, b, 0, s, D, m, A, Bs, nc, alpha, beta, Out, none);
         }
         HQ_LAUNCH_CHECK();
     }
@@ -1136,7 +1140,8 @@ int davidson(Ctx &c, const hinqs_opts &o, const double *guess, double *energy, d
         std::fill(G.begin(), G.end(), 0.0);
         double *g = S.host_products();
         if ((size_t)mm * mm > S.H_RITZ) throw Error(HINQS_E_UNSUPPORTED, "basis after a restart too large");
-        for (int b0 = 0; b0 < mm; b0 += K) S.gram(S.V, mm, S.W.cols(b0), std::min(K, mm - b0), nullptr, g + (size_t)mm * b0);
+        for (int b0 = 0; b0 < mm; b0 += K)
+            S.gram(S.V, mm, S.W.cols(b0), std::min(K, mm - b0), nullptr, g + (size_t)mm * b0);
         wait_stream(S.s);
         for (int b0 = 0; b0 < mm; b0 += K) {
             const int nb = std::min(K, mm - b0);

@@ -1,14 +1,14 @@
 // Sigma product S = H_B X without any device allocation (the repeated product
 // of the Davidson iteration, Sec. 2.2, Step 3), for callers that cannot
-// allocate: the kernel's row counters and the sorted-order staging of X and S
-// live in one static device array per GPU instead of context buffers.  The
-// staging kernels (caller order and k padded to K in one pass each way) serve
-// hinqs_sigma too, with the context's buffers.
+// allocate: the kernel's row counters and the sorted-order copy of X live in
+// one static device array per GPU instead of context buffers.  The staging
+// kernel (caller order and k padded to K in one pass; the product writes S's
+// rows and columns itself) serves hinqs_sigma too, with the context's buffer.
 //
 // Layout of the array: [0, 4096) row counters (SIGMA_CTR_WORDS words, cleared
 // by a fill kernel on every call; no memset, so the call can be captured in a
-// graph); [4096, 4096 + B) staged X; [4096 + B, 4096 + 2B) staged S, where
-// B = ndet * K * element size rounded up to 256 bytes.
+// graph); [4096, 4096 + B) staged X, where B = ndet * K * element size rounded
+// up to 256 bytes.  Calls with 4096 + 2B beyond the array are refused.
 #include <mutex>
 
 #include "common.hpp"

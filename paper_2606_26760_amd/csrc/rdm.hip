@@ -20,7 +20,7 @@
 // pair for rdm1 / Sc / Sx, and for the doubles two unordered pairs and their
 // relative orientation (n (n - 1) / 2 = P pairs give P (P + 1) classes).
 //
-// Up to 16 orbitals one set of these sums (153 KB at 16) fits the LDS of a
+// Up to 16 orbitals one set of these sums (148 KB at 16) fits the LDS of a
 // workgroup: every double is one LDS add (two same-spin), and each workgroup
 // writes its table once.  The lanes of a wave hold couplings of one row, whose
 // moves differ, so their adds hardly ever meet.  What bounds it: the gathers

@@ -10,9 +10,11 @@
 // ga[g] .. ga[g+1] with ascending beta strings sb) and beta groups (distinct
 // beta strings ub, entries gb[g] .. gb[g+1] of the beta-major listing bperm
 // with their alpha strings bm_alpha).  A determinant is found by two binary
-// searches; every partner of a candidate is found by scanning at most
-// 2 + na (norb - na) groups.  Matrix elements follow slater.hpp, with the
-// packed integrals in LDS when they fit.
+// searches; every partner of a candidate lies in one of at most
+// 2 + na (norb - na) groups, which are scanned, or, for the groups one alpha move
+// away, looked up in tables of their members by the candidate's own beta moves.
+// Matrix elements follow slater.hpp, with the packed integrals in LDS when they
+// fit.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -996,7 +998,8 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
         if (use_lds) launch(T{}, S1{}, F{});
         else launch(F{}, S1{}, F{});
         const dim3 lg((unsigned)std::min<int64_t>((int64_t)cus * 2, ncand)), lb(PT_NT);
-        if (moves_b <= 64) hipLaunchKernelGGL(k_pt2_links<1>, lg, lb, 0, s, pa, keys, order, tiles, ntiles, nwords, tab);
+        if (moves_b <= 64)
+            hipLaunchKernelGGL(k_pt2_links<1>, lg, lb, 0, s, pa, keys, order, tiles, ntiles, nwords, tab);
         else if (moves_b <= 128)
             hipLaunchKernelGGL(k_pt2_links<2>, lg, lb, 0, s, pa, keys, order, tiles, ntiles, nwords, tab);
         else hipLaunchKernelGGL(k_pt2_links<4>, lg, lb, 0, s, pa, keys, order, tiles, ntiles, nwords, tab);

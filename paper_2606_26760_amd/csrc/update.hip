@@ -62,8 +62,9 @@ __global__ void k_new_list(const int32_t *keep, const int32_t *newidx, const int
 
 // o2n[old sorted position] = new sorted position or -1; n2o the inverse (-1
 // for appended rows, filled beforehand); bit p of kept_bits: p is kept.
-__global__ __launch_bounds__(256) void k_maps(const int32_t *perm_old, const int32_t *keep, const int32_t *newidx, const int32_t *inv_new,
-                       int64_t n_old, int32_t *o2n, int32_t *n2o, uint32_t *kept_bits) {
+__global__ __launch_bounds__(256) void k_maps(const int32_t *perm_old, const int32_t *keep, const int32_t *newidx,
+                                              const int32_t *inv_new, int64_t n_old, int32_t *o2n, int32_t *n2o,
+                                              uint32_t *kept_bits) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int32_t r = -1;
     if (p < n_old) {
