@@ -873,6 +873,13 @@ int64_t expand(Ctx &c, const double *coeffs, bool sorted, int64_t ntop, int64_t 
 
 namespace {
 
+// Strings of n among norb orbitals (at most 6e8).
+int64_t strings(int norb, int n) {
+    int64_t s = 1;
+    for (int i = 1; i <= n; ++i) s = s * (norb - n + i) / i;
+    return s;
+}
+
 // Times (us) of the linked class alone: scanning the groups, and through the
 // tables.  The scan's waves take PT2_RUN candidates one after another, 8,192 of
 // them at a time, and wait for each group in turn: about 0.4 us for a few
@@ -882,11 +889,15 @@ namespace {
 // 100 candidates 1028 / 409, 8,000 in as many tiles 1287 / 1685, 1e5 in 11,000
 // 2410 / 2780, 5.4e5 in 18,000 6536 / 5124; 1e5 rows, groups of 9, 2,000 in as
 // many 538 / 569, 30,000 in 8,600 823 / 1810, 5.3e6 in 88,000 25,900 / 23,250;
-// 1,000 rows, 1 candidate 82 / 127, 3,000 in 250 tiles 411 / 250.
+// 1,000 rows, 1 candidate 82 / 127, 3,000 in 250 tiles 411 / 250.  Lists of more than
+// a few hundred candidates are mostly excitations of the set's leading members, near
+// its large groups, and wait for the longest of their waves: half again (1e6 rows,
+// 54,500 excitations in 5,961 tiles 1823 / 1682, 1.6e5 in 10,900 2838 / 2850).
 double link_scan_us(const Ctx &c, int moves, int64_t ncand) {
     const double group = (double)c.ndet / c.nua;
     const double per_wave = ncand <= 8192 * PT2_RUN ? (double)std::min<int64_t>(ncand, PT2_RUN) : ncand / 8192.0;
-    return per_wave * moves * (0.4 + 0.55 * std::min(1.0, group / 64.0));
+    const double list = ncand > 256 ? 1.5 : 1.0;
+    return list * per_wave * moves * (0.4 + 0.55 * std::min(1.0, group / 64.0));
 }
 double link_table_us(size_t bytes, int moves, int64_t tiles) {
     return 40.0 + 0.5e-6 * bytes + moves * 1.4 * std::max(1.0, tiles / 512.0);
@@ -945,7 +956,9 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
     const double scan = link_scan_us(c, moves, ncand);
     const char *env = std::getenv("HINQS_PT2_TABLES");  // 0: scan, 1: tables wherever they fit
     const int asked = env && *env ? std::atoi(env) : -1;
+    // fewest and most tiles that the list can have: a partly filled one per alpha string
     const int64_t fewest = (ncand + PT2_TILE - 1) / PT2_TILE;
+    const int64_t most = std::min(ncand, (int64_t)(ncand / PT2_TILE + strings(c.norb, c.na)));
     bool lookup = fits && (asked >= 0 ? asked != 0 : link_table_us(table, moves, fewest) <= scan);
     int32_t *tiles = nullptr, *ntiles = nullptr;
     if (lookup) {
@@ -960,7 +973,7 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
                            ntiles);
         HQ_LAUNCH_CHECK();
         // the number of tiles is read back where it decides
-        if (asked < 0 && link_table_us(table, moves, ncand) > scan) {
+        if (asked < 0 && link_table_us(table, moves, most) > scan) {
             int32_t nt = 0;
             HQ_CHECK(hipMemcpyAsync(&nt, ntiles, sizeof(int32_t), hipMemcpyDeviceToHost, s));
             HQ_CHECK(hipStreamSynchronize(s));
