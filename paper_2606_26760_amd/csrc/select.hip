@@ -960,9 +960,21 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
     const int64_t fewest = (ncand + PT2_TILE - 1) / PT2_TILE;
     const int64_t most = std::min(ncand, (int64_t)(ncand / PT2_TILE + strings(c.norb, c.na)));
     bool lookup = fits && (asked >= 0 ? asked != 0 : link_table_us(table, moves, fewest) <= scan);
-    int32_t *tiles = nullptr, *ntiles = nullptr;
+    // the scan needs none of the tables' memory: where there is none, it runs
+    auto room = [&](auto &&get) {
+        try {
+            get();
+            return true;
+        } catch (const Error &e) {
+            if (e.code != HINQS_E_OOM) throw;
+            (void)hipGetLastError();
+            return false;
+        }
+    };
+    int32_t *flag = nullptr, *tiles = nullptr, *ntiles = nullptr;
+    uint2 *tab = nullptr;
+    lookup = lookup && room([&] { flag = c.cs.get<int32_t>(7, 3 * ncand + 1); });
     if (lookup) {
-        int32_t *flag = c.cs.get<int32_t>(7, 3 * ncand + 1);
         int32_t *fpos = flag + ncand;
         tiles = fpos + ncand;
         ntiles = tiles + ncand;
@@ -980,6 +992,7 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
             lookup = link_table_us(table, moves, nt) <= scan;
         }
     }
+    lookup = lookup && room([&] { tab = c.cs.get<uint2>(6, (size_t)c.nua * nwords); });
     // resident workgroups only (two per CU); they share the candidates through a counter
     const int64_t runs = (ncand + PT2_RUN - 1) / PT2_RUN;
     const unsigned grid =
@@ -1001,7 +1014,6 @@ void pt2(Ctx &c, const double *coeffs, bool sorted, double e0, int64_t ncand, co
     using S2 = std::integral_constant<int, 2>;
     using S4 = std::integral_constant<int, 4>;
     if (lookup) {
-        uint2 *tab = c.cs.get<uint2>(6, (size_t)c.nua * nwords);
         HQ_CHECK(hipMemsetAsync(tab, 0, table, s));
         hipLaunchKernelGGL(k_pt2_bits, dim3(grid_for(c.ndet, 256)), dim3(256), 0, s, c.ndet, c.aidx.p, c.bidx.p,
                            nwords, tab);

@@ -561,3 +561,44 @@ def test_batch_finds_the_lowest_states(block, max_space):
     assert info["converged"]
     for x, w in zip(e, ref):
         assert abs(x - w[0]) <= 1e-9 + 1e-12 * np.abs(w).max(), (x, w[:4])
+
+
+class _PoolUpTo(hq.TorchAllocator):
+    """PyTorch's pool; requests above ``limit`` bytes get nothing."""
+
+    def __init__(self):
+        super().__init__(0, torch.cuda.current_stream(0).cuda_stream)
+        self.limit, self.refused = 1 << 62, 0
+
+    def alloc(self, nbytes):
+        if nbytes > self.limit:
+            self.refused += 1
+            return 0
+        return super().alloc(nbytes)
+
+
+@pytest.mark.parametrize("refused_from", [0, 16_384])
+def test_pt2_without_memory_for_its_tables_scans(refused_from, monkeypatch):
+    """The member tables (214 KB) and the tile lists are memory that the scan does not need:
+    when the allocator has none for both, or for the tables alone, the scan's results come
+    back bit for bit."""
+    ints, a, b, cfg = W.config_inputs(3, ndet=60_000)
+    log(f"pt2 with requests above {refused_from} bytes refused")
+    pool = _PoolUpTo()
+    s = hq.Hinqs(allocator=pool)
+    s.set_integrals(ints.h, ints.eri, ints.e_core)
+    s.set_determinants(a, b, cfg.na, cfg.nb)
+    rng = np.random.default_rng(81)
+    cd = torch.from_numpy(rng.standard_normal(len(a))).cuda()
+    ca, cb = a[:600][rng.integers(0, 600, 1200)], b[rng.integers(0, len(b), 1200)]
+    monkeypatch.setenv("HINQS_PT2_TABLES", "0")
+    ref = s.pt2(cd, -1000.0, ca, cb)
+    monkeypatch.setenv("HINQS_PT2_TABLES", "1")
+    pool.limit = refused_from
+    got = s.pt2(cd, -1000.0, ca, cb)
+    assert pool.refused > 0
+    for x, y in zip(got, ref):
+        assert torch.equal(x, y)
+    pool.limit = 1 << 62
+    for x, y in list(zip(s.pt2(cd, -1000.0, ca, cb), ref))[:2]:
+        assert float((x - y).abs().max()) <= 1e-12 * float(y.abs().max())
