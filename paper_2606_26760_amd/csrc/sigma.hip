@@ -464,18 +464,24 @@ constexpr int lanes_per_coupling() {
 // with 85 333 / 350 and 457 / 463, 2e5 with 615 565 / 601 and 962 / 938, 1e6 with
 // 156 1087 / 1086 and 1648 / 1506, 4e6 with 171 4425 / 4250 and 8321 / 6332, 1e7
 // with 13.5 1327 / 1664 and 2200 / 2554, 6e6 with 23.6 1264 / 1376 and 2110 / 2079,
-// 2e7 with 27 5718 / 5569 and 9390 / 8859; 3e5 with 856, k = 1 (X of 2.4 MB)
-// 1108 / 1150, k = 8 FP32 (9.6 MB) 1449 / 1514.
+// 2e7 with 27 5718 / 5569 and 9390 / 8859.  By the bytes of X: 1e6 with 157, FP32, k = 1
+// (4 MB) 823 / 851, FP64, k = 1 (8 MB) 1093 / 1087; 1.5e6 with 236, k = 1 (12 MB) 2393 /
+// 2346; long rows keep their XCD's X together by themselves for longer, 3e5 with 856,
+// k = 4 (9.6 MB) 1553 / 1619, 7e5 with 870, k = 2 and 4 (11.2, 22.4 MB) 3203 / 3259 and
+// 4077 / 4083.
 constexpr int64_t SIGMA_STATIC_NNZ = 130000000;
-constexpr double SIGMA_COUNTER_ROW = 25.0;       // mean couplings
-constexpr int64_t SIGMA_COUNTER_X = 16 << 20;    // bytes of X
-constexpr double SIGMA_LONG_ROW = 256.0;  // mean couplings from which two rows make a run
+constexpr double SIGMA_COUNTER_ROW = 25.0;  // mean couplings
+constexpr double SIGMA_LONG_ROW = 256.0;    // mean couplings from which two rows make a run
+constexpr int64_t SIGMA_COUNTER_X = 6 << 20, SIGMA_COUNTER_X_LONG = 16 << 20;  // bytes of X
 
 int row_run(const Ctx &c, const SigmaCfg &cfg, int64_t xbytes) {
     if (cfg.run >= 0) return cfg.run;
-    if (c.nnz <= SIGMA_STATIC_NNZ || xbytes < SIGMA_COUNTER_X || (double)c.nnz < SIGMA_COUNTER_ROW * (double)c.ndet)
+    const double avg = (double)c.nnz / (double)c.ndet;
+    const bool long_rows = avg >= SIGMA_LONG_ROW;
+    if (c.nnz <= SIGMA_STATIC_NNZ || avg < SIGMA_COUNTER_ROW ||
+        xbytes < (long_rows ? SIGMA_COUNTER_X_LONG : SIGMA_COUNTER_X))
         return 0;
-    return (double)c.nnz >= SIGMA_LONG_ROW * (double)c.ndet ? 2 : 4;
+    return long_rows ? 2 : 4;
 }
 
 template <typename T, int K, int TEAM, int UNR, bool MASK>
